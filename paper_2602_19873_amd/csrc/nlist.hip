@@ -7,17 +7,25 @@
 // Traversal: depth-first from the root with an LDS stack; at an internal node
 // 64 lanes test up to 8 children against 8 boxes of the super-cluster and
 // push the survivors in reverse key order, so leaves come out in key order
-// and the list is sorted without a sort (Sec. II-A). At a leaf, 64 lanes test
-// the i-cluster boxes against the boxes of the leaf's candidate j-clusters;
-// each candidate with a nonempty i-cluster mask joins an LDS queue. Once 64
-// are queued (and at the end) the queue is drained in order, the
-// j-particles of a batch of queued candidates arriving with one load per
-// field while the previous batch's tests run. For cluster size 8 the exact
-// tests are lane-parallel over the batch's (candidate, i-cluster) tiles: a
-// group of 8 lanes takes one tile and steps through its 8 j-particles (see
-// drain_lanes); sizes 4 and 16 give each tile one 64-lane step. Box tests
-// are conservative under FP32 rounding (rounding is monotone), so they
-// never drop a pair the exact test keeps; the masks are exact.
+// and the list is sorted without a sort (Sec. II-A). The leaves' candidate
+// j-clusters collect 64 at a time, one per lane, and are tested against the
+// boxes of the super-cluster's particles 8 at a time; the survivors join an
+// LDS queue, whose batches of 64 j-particles arrive with one load per field
+// while the previous batch is tested. Box tests are conservative under FP32
+// rounding (rounding is monotone), so they never drop a pair the exact test
+// keeps; the masks are exact.
+//
+// Pair tests. The matrix cores evaluate all 64 x 64 squared distances of a
+// batch from split half-precision coordinates, with a bound E on their error;
+// a tile with a distance more than E below its squared radius is set, one with
+// none within E of it is clear, and the few left open (and the tiles of a
+// cluster with itself) are decided by the exact FP32 formula, so the list does
+// not depend on the filter. The former vector tests of the tiles whose boxes
+// met cost 8 vector instructions per 64 pairs and about 6,100 of a
+// super-cluster's 10,900; now a 64 x 64 block costs some 235. Both were bound
+// by vector issue and latency: 0.63 -> 0.53 ms on 2,097,152 uniform particles
+// (half list, cluster size 8), 1.74 -> 1.52 ms on the 4,000,037-particle 1/r
+// sphere (full list).
 //
 // The list is staged in 64-entry chunks with its encoded size computed on the
 // fly (a super-cluster's first chunk is its own, later ones come from 64
@@ -41,9 +49,9 @@ namespace {
 // encoder: a block's resources are released only when its slowest wave ends,
 // and super-clusters differ in work; measured 10 % faster than four.
 constexpr int kWavesPerBlock = 1;
-constexpr int kStackCap = 160;  // 1 + 7 * 21 pushes at most
+constexpr int kStackCap = 148;  // 1 + 7 * 21 records at most
 constexpr int kSegCap = 80;     // words of one 64-value segment: 2 + (64 + 512 + 7) / 8
-constexpr int kQueueCap = 96;   // queued candidates: drained at 64, one box step adds at most 16
+constexpr int kQueueCap = 128;  // queued candidates (a ring): fewer than 16 left over, one box step adds at most 64
 constexpr uint32_t kUnstaged = 0xFFFFFFFFu;  // sc_nj of a list that found no staging room
 
 __device__ __forceinline__ unsigned xcd_remap(unsigned b, unsigned g) {
@@ -79,14 +87,6 @@ __device__ __forceinline__ bool boxes_near(float4 alo, float4 ahi, float4 blo, f
 
 // Position for absent particles: any distance to it overflows to +inf.
 constexpr float kFar = 3.0e38f;
-
-// OR of the eight bytes of a ballot: bit k set iff some lane k + 8c is set.
-__device__ __forceinline__ uint32_t byte_or(uint64_t b) {
-    b |= b >> 32;
-    b |= b >> 16;
-    b |= b >> 8;
-    return (uint32_t)(b & 0xFFu);
-}
 
 __device__ __forceinline__ uint32_t nibbles_of(uint32_t v) { return (32u - (uint32_t)__clz((int)v) + 3u) >> 2; }
 
@@ -193,35 +193,13 @@ struct TravArgs {
     uint32_t *status;
 };
 
-// Lane roles of a super-cluster's wavefront for cluster size CS (64 / CS
-// i-clusters per super-cluster).
-//
-// Box tests: lane l pairs the box of i-cluster l % (64 / CS) with candidate
-// slot l / (64 / CS), so one ballot holds in consecutive groups of 64 / CS
-// bits the i-cluster mask of each candidate slot (8 slots of 8 bits for CS = 8,
-// 4 of 16 for CS = 4, 16 of 4 for CS = 16). Node tests pair child l / 8 with
-// the box of super-cluster particles [8g, 8g + 8), g = l % 8 (for CS = 16 the
-// box of the i-cluster holding them).
-//
-// Exact tests (one step is 64 particle pairs):
-//   CS = 8:  lane (il, jl) = (lane / 8, lane % 8); register k holds i-particle
-//            8k + il (i-cluster k); one step is one 8x8 cluster pair.
-//   CS = 4:  lane (q, il, jl) = (lane / 16, lane / 4 % 4, lane % 4); register
-//            k holds i-particle 16k + lane / 4 (i-cluster 4k + q); one step is
-//            four 4x4 pairs (i-clusters 4k .. 4k + 3 against one j-cluster).
-//   CS = 16: lane (il, jq) = (lane / 4, lane % 4); register k holds
-//            i-particle 16k + il (i-cluster k); a 16x16 pair takes four steps
-//            (j-particles 4t + jq).
+// Node tests pair child l / 8 with the box of super-cluster particles
+// [8g, 8g + 8), g = l % 8 (for CS = 16 the box of the i-cluster holding them).
 template <int CS>
 struct Shape {
-    static constexpr int kNsub = kScSize / CS;        // i-clusters per super-cluster
-    static constexpr int kNreg = CS == 8 ? 8 : 4;     // i-particles per lane
-    static constexpr int kNj = CS == 16 ? 4 : 1;      // j-particles per lane and candidate
+    static constexpr int kNsub = kScSize / CS;  // i-clusters per super-cluster
     static constexpr int kMaskBytes = kNsub > 8 ? 2 : 1;
-    static constexpr int kSlots = kWave / kNsub;      // candidate j-clusters per box step
     static constexpr uint32_t kFull = (1u << kNsub) - 1u;
-    __device__ static int ipart(int k, int lane) { return CS == 8 ? 8 * k + (lane >> 3) : 16 * k + (lane >> 2); }
-    __device__ static int jpart(int t, int lane) { return CS == 8 ? (lane & 7) : (CS == 4 ? (lane & 3) : 4 * t + (lane & 3)); }
 };
 
 __device__ __forceinline__ void box_union(float4 &lo, float4 &hi, float4 blo, float4 bhi) {
@@ -283,13 +261,171 @@ __device__ __forceinline__ float max_sq(float u, float v) {
     return __int_as_float(max(__float_as_int(u), __float_as_int(v)));
 }
 
-// Five waves per SIMD (at most 96 VGPRs).
+// ---------------------------------------------------------------------------
+// The matrix-core filter of the exact tests. For 32 i-particles (rows) and 32
+// j-particles (columns), one v_mfma_f32_32x32x16_f16 gives every pair's
+// |x_i|^2 + |x_j|^2 - 2 x_i . x_j minus one of the two squared radii, from
+// coordinates taken relative to the super-cluster, scaled by a power of two
+// and split into two halves each (x = h + l; the l l products are dropped),
+// and squares split into three. Slots k of the 16 products A_k B_k:
+//   3t .. 3t + 2  (axis t)  A = -2h, -2h, -2l   B = h, l, h
+//   9 .. 11                 A = the i-square    B = 1
+//   12 .. 14                A = 1               B = the j-square
+//   15                      0
+// A lane's first four registers hold slots 0-7, the others 8-15.
+// ---------------------------------------------------------------------------
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float float16_t __attribute__((ext_vector_type(16)));
+typedef uint32_t uint4_t __attribute__((ext_vector_type(4)));
+
+constexpr float kFar16 = 60000.0f;    // values above cannot be split into halves
+constexpr uint32_t kInf16 = 0x7C00u;  // an absent particle's square: no pair of it is near
+constexpr uint32_t kOnes16 = 0x3C003C00u;
+
+__device__ __forceinline__ uint32_t pack16(float a, float b) {
+    const half2_t v = {(_Float16)a, (_Float16)b};
+    return __builtin_bit_cast(uint32_t, v);
+}
+// v rounded to a half. The empty asm keeps the conversion one instruction: the
+// scalar and the packed conversion round ties differently, and a remainder
+// v - round16(v) needs the value that is packed.
+__device__ __forceinline__ float round16(float v) {
+    _Float16 t = (_Float16)v;
+    asm("" : "+v"(t));
+    return (float)t;
+}
+
+// lanes 32-63 of a change places with lanes 0-31 of b
+__device__ __forceinline__ void swap_halves(uint32_t &a, uint32_t &b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+}
+
+// One particle's operand in its own lane (8 registers), with a second form of
+// the two registers that hold the square: `row` selects A (rows: square, and
+// square minus the squared radius; an absent particle's are infinite) or B.
+// After the swaps lane l of plain[0] holds slots 8 (l / 32) .. of particle
+// l % 32 and plain[1] those of particle 32 + l % 32; other[] are the registers
+// kSquare and kSquare + 1 of the second form.
+constexpr int kSquareA = 0, kSquareB = 2;
+struct Operands {
+    uint4_t plain[2];
+    uint32_t other[2][2];
+};
+template <bool kRow>
+__device__ __forceinline__ Operands operands(float x, float y, float z, float sq, float sq_other, bool present) {
+    const float hx = round16(x), hy = round16(y), hz = round16(z);
+    const float lx = x - hx, ly = y - hy, lz = z - hz;
+    const float s0 = round16(sq), s1 = round16(sq - s0), s2 = sq - s0 - s1;
+    const float t0 = round16(sq_other), t1 = round16(sq_other - t0), t2 = sq_other - t0 - t1;
+    uint32_t r[8], u0, u1;
+    if (kRow) {
+        r[0] = pack16(-2.0f * hx, -2.0f * hx);
+        r[1] = pack16(-2.0f * lx, -2.0f * hy);
+        r[2] = pack16(-2.0f * hy, -2.0f * ly);
+        r[3] = pack16(-2.0f * hz, -2.0f * hz);
+        r[4] = pack16(-2.0f * lz, present ? s0 : INFINITY);
+        r[5] = present ? pack16(s1, s2) : 0u;
+        r[6] = kOnes16;
+        r[7] = kOnes16 & 0xFFFFu;
+        u0 = pack16(-2.0f * lz, present ? t0 : INFINITY);
+        u1 = present ? pack16(t1, t2) : 0u;
+    } else {
+        r[0] = pack16(hx, lx);
+        r[1] = pack16(hx, hy);
+        r[2] = pack16(ly, hy);
+        r[3] = pack16(hz, lz);
+        r[4] = pack16(hz, 1.0f);
+        r[5] = kOnes16;
+        r[6] = pack16(s0, s1);
+        r[7] = pack16(s2, 0.0f);
+        u0 = pack16(t0, t1);
+        u1 = pack16(t2, 0.0f);
+    }
+    constexpr int kS = kRow ? kSquareA : kSquareB;
+    uint32_t v0 = r[kS], v1 = r[kS + 1];
+#pragma unroll
+    for (int k = 0; k < 4; k++) swap_halves(r[k], r[4 + k]);
+    swap_halves(v0, u0);
+    swap_halves(v1, u1);
+    Operands o;
+    o.plain[0] = uint4_t{r[0], r[1], r[2], r[3]};
+    o.plain[1] = uint4_t{r[4], r[5], r[6], r[7]};
+    o.other[0][0] = v0;
+    o.other[0][1] = v1;
+    o.other[1][0] = u0;
+    o.other[1][1] = u1;
+    return o;
+}
+
+__device__ __forceinline__ float16_t pair_block(uint4_t a, uint4_t b) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b),
+                                                  float16_t{}, 0, 0, 0);
+}
+
+// bit k: lane k or k + 32 of a ballot
+__device__ __forceinline__ uint32_t fold_halves(uint64_t b) { return (uint32_t)b | (uint32_t)(b >> 32); }
+
+// v of the lane whose index differs as the DPP control says (the moves fold
+// into the consuming instruction)
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
+}
+
+// The i-cluster masks of a 64 x 64 block's candidates. Bit 8 b + 4 f + g of
+// `seen`, lane l: that lane saw a pair of one of the i-particles
+// 32 f + 8 g + 4 (l / 32) + {0..3} with j-particle 32 b + l % 32. Lane q gets
+// the mask of candidate q (q below 64 / CS; other lanes: unspecified).
+template <int CS>
+__device__ __forceinline__ uint32_t candidate_mask(uint32_t seen, int lane) {
+    // over the lanes of a j-cluster (4, 8 or 16 lanes of a half)
+    seen |= dpp_u<0xB1>(seen);  // quad_perm [1, 0, 3, 2]
+    seen |= dpp_u<0x4E>(seen);  // quad_perm [2, 3, 0, 1]
+    if constexpr (CS >= 8) seen |= dpp_u<0x141>(seen);   // row_half_mirror
+    if constexpr (CS == 16) seen |= dpp_u<0x140>(seen);  // row_mirror
+    if constexpr (CS == 4) {
+        // candidate 8b + c: lanes 4c .. 4c + 3 of the halves; i-cluster 8f + 2g + half
+        const int src = 4 * (lane & 7);
+        const uint32_t lo = (uint32_t)__shfl((int)seen, src, kWave), hi = (uint32_t)__shfl((int)seen, src + 32, kWave);
+        auto spread = [](uint32_t v) {  // bit k to bit 2k
+            v = (v | (v << 4)) & 0x0F0Fu;
+            v = (v | (v << 2)) & 0x3333u;
+            return (v | (v << 1)) & 0x5555u;
+        };
+        const int sh = lane & 8;  // byte b
+        return spread((lo >> sh) & 0xFFu) | (spread((hi >> sh) & 0xFFu) << 1);
+    } else {
+        uint32_t a = seen, b = seen;
+        swap_halves(a, b);
+        seen = a | b;  // both halves' rows
+        if constexpr (CS == 8) {  // candidate 4b + c: lanes 8c .. 8c + 7; i-cluster 4f + g
+            return ((uint32_t)__shfl((int)seen, 8 * (lane & 3), kWave) >> (8 * ((lane >> 2) & 1))) & 0xFFu;
+        } else {  // candidate 2b + c: lanes 16c .. 16c + 15; i-cluster 2f + g / 2
+            uint32_t v = ((uint32_t)__shfl((int)seen, 16 * (lane & 1), kWave) >> (8 * ((lane >> 1) & 1))) & 0xFFu;
+            v = (v | (v >> 1)) & 0x55u;
+            v = (v | (v >> 1)) & 0x33u;
+            return (v | (v >> 2)) & 0x0Fu;
+        }
+    }
+}
+
+// Five waves per SIMD: at most 96 VGPRs, and at most 7,680 bytes of LDS (four
+// waves: 0.56 against 0.53 ms on the 2M box).
 template <int CS, bool kHalf, bool kPbc>
-__global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_traverse(TravArgs a) {
+__global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(5, 5))) void k_traverse(TravArgs a) {
     using S = Shape<CS>;
-    constexpr int kNsub = S::kNsub, kNreg = S::kNreg, kNj = S::kNj, kSlots = S::kSlots;
+    constexpr int kNsub = S::kNsub;
+    constexpr int kBatch = kWave / CS;               // candidates per batch of 64 j-particles
+    constexpr int kBoxes = kNsub < 8 ? kNsub : 8;    // i-boxes of the box tests (CS = 4: of two clusters each)
+    constexpr bool kLaneTiles = CS == 8;
     __shared__ uint4 s_stack[kWavesPerBlock][kStackCap];
-    __shared__ uint2 s_queue[kWavesPerBlock][kQueueCap];
+    __shared__ uint32_t s_queue[kWavesPerBlock][kQueueCap];
+    __shared__ float4 s_box[kWavesPerBlock][2 * kBoxes];
+    __shared__ uint2 s_ent[kWavesPerBlock][kBatch];
+    __shared__ uint4_t s_a[kWavesPerBlock][4][kWave];  // the filter's i-operands: less[0], less[1], plain[0], plain[1]
     const int lane = sfc_lane();
     const int w = threadIdx.x / kWave;
     // wave-uniform: keep the super-cluster index (and all derived from it) scalar
@@ -304,95 +440,55 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
     }
     const int64_t n = a.n;
     const bool gather = a.p_active != nullptr;
-    // i particles; absent ones are put far away so that no test accepts them.
-    // Cluster size 8 keeps them in LDS for its lane-parallel tiles (lane l
-    // loads particle l; particle 8c + l' sits at 9c + l', a padding slot after
-    // each cluster keeps the clusters on distinct banks), the other sizes in
-    // the registers of their tile lanes.
-    constexpr bool kLaneTiles = CS == 8;
-    __shared__ float4 s_ip[kWavesPerBlock][kLaneTiles ? 72 : 1];
-    float ix[kNreg], iy[kNreg], iz[kNreg], ih2[kNreg];
-    float lh2 = 0.0f;  // cluster size 8: the squared radius of particle lane
+    const uint32_t own_c0 = s * kNsub;   // first i-cluster of this super-cluster
+    const uint32_t own_p0 = s * kScSize; // and its first particle
+    // i-particle `lane`; absent ones are put far away so that no test accepts them
     bool big = false;  // a radius reaches half a period
-    if constexpr (kLaneTiles) {
-        const int64_t i = (int64_t)s * kScSize + lane;
+    float ix, iy, iz, ih2;
+    bool ipresent;
+    {
+        const int64_t i = (int64_t)own_p0 + lane;
         const bool v = i < n;
-        float hh = v ? a.h[i] : 0.0f;
-        if (kPbc) big = !(hh < a.per.hmin);
-        if (gather && v && !a.p_active[i]) hh = 0.0f;  // counting list: flagged particles only
-        lh2 = hh * hh;
-        s_ip[w][9 * (lane >> 3) + (lane & 7)] = make_float4(v ? a.x[i] : kFar, v ? a.y[i] : kFar, v ? a.z[i] : kFar, lh2);
-    } else {
-#pragma unroll
-        for (int k = 0; k < kNreg; k++) {
-            const int64_t i = (int64_t)s * kScSize + S::ipart(k, lane);
-            const bool v = i < n;
-            ix[k] = v ? a.x[i] : kFar;
-            iy[k] = v ? a.y[i] : kFar;
-            iz[k] = v ? a.z[i] : kFar;
-            float hh = v ? a.h[i] : 0.0f;
-            if (kPbc) big = big || !(hh < a.per.hmin);
-            if (gather && v && !a.p_active[i]) hh = 0.0f;  // counting list: flagged particles only
-            ih2[k] = hh * hh;
-        }
+        const int64_t ic = v ? i : n - 1;
+        ix = a.x[ic];
+        iy = a.y[ic];
+        iz = a.z[ic];
+        float hh = a.h[ic];
+        if (kPbc) big = v && !(hh < a.per.hmin);
+        ipresent = v && ix + iy + iz == ix + iy + iz;  // (a batch's padding is NaN)
+        if (gather) ipresent = ipresent && a.p_active[ic];  // counting list: flagged particles only
+        if (!v) ix = iy = iz = kFar;
+        ih2 = v && (!gather || a.p_active[ic]) ? hh * hh : 0.0f;
     }
     if (kPbc && sfc_ballot(big) && lane == 0) atomicOr(&a.status[kStInputErr], 8u);
-    const uint32_t own_c0 = s * kNsub;  // first i-cluster of this super-cluster
-    const uint32_t own_p0 = s * kScSize;  // and its first particle
 
     constexpr bool half = kHalf;
-    const float4 empty_lo = make_float4(INFINITY, INFINITY, INFINITY, 0.0f);
-    const float4 empty_hi = make_float4(-INFINITY, -INFINITY, -INFINITY, 0.0f);
-    // box tests: the box of i-cluster lane % kNsub
-    float4 ilo, ihi;
-    {
-        const uint32_t ic = own_c0 + (uint32_t)(lane & (kNsub - 1));
-        const bool v = ic < a.nclu;
-        ilo = v ? a.bbox[2 * (size_t)ic] : empty_lo;
-        ihi = v ? a.bbox[2 * (size_t)ic + 1] : empty_hi;
-    }
     // node tests: the box of super-cluster particles [8g, 8g + 8), g = lane % 8
     // (for CS = 16 the box of their i-cluster)
-    float4 glo, ghi;
-    if (CS == 8) {
-        glo = ilo;
-        ghi = ihi;
-    } else {
+    float4 glo = make_float4(INFINITY, INFINITY, INFINITY, 0.0f), ghi = make_float4(-INFINITY, -INFINITY, -INFINITY, 0.0f);
+    {
         const int g = lane & 7;
-        const uint32_t c0 = own_c0 + (CS == 4 ? 2 * g : (g >> 1));
-        const bool v0 = c0 < a.nclu;
-        glo = v0 ? a.bbox[2 * (size_t)c0] : empty_lo;
-        ghi = v0 ? a.bbox[2 * (size_t)c0 + 1] : empty_hi;
+        const uint32_t c0 = own_c0 + (CS == 4 ? 2 * g : (CS == 8 ? g : (g >> 1)));
+        if (c0 < a.nclu) {
+            glo = a.bbox[2 * (size_t)c0];
+            ghi = a.bbox[2 * (size_t)c0 + 1];
+        }
         if (CS == 4 && c0 + 1 < a.nclu) box_union(glo, ghi, a.bbox[2 * (size_t)c0 + 2], a.bbox[2 * (size_t)c0 + 3]);
     }
-
     if (gather) {
-        // radii of the boxes: the largest flagged radius inside, from the i
-        // registers (a radius 0 box passes no test)
-        __shared__ float s_hmax[kWavesPerBlock][kScSize];
-        float *hm = s_hmax[w];
-        if constexpr (kLaneTiles) {
-            hm[lane] = __builtin_sqrtf(lh2);
-        } else {
+        // radii of the boxes: the largest flagged radius inside (a radius 0
+        // box passes no test): a maximum over the particles of each box
+        float r = ih2;
+        constexpr int kSpan = CS == 16 ? 16 : 8;
 #pragma unroll
-            for (int k = 0; k < kNreg; k++) {
-                if ((lane & 3) == 0) hm[S::ipart(k, lane)] = __builtin_sqrtf(ih2[k]);
-            }
-        }
-        wave_sync();
-        auto rmax = [&](int p0, int cnt) SFC_INLINE {
-            float r = 0.0f;
-            for (int q = 0; q < cnt; q++) r = fmaxf(r, hm[p0 + q]);
-            return r;
-        };
-        ilo.w = rmax((lane & (kNsub - 1)) * CS, CS);
-        if (CS == 8)
-            glo.w = ilo.w;
-        else if (CS == 4)
-            glo.w = rmax(8 * (lane & 7), 8);
-        else
-            glo.w = rmax(16 * ((lane & 7) >> 1), 16);
-        wave_sync();
+        for (int d = 1; d < kSpan; d <<= 1) r = fmaxf(r, __shfl_xor(r, d, kWave));
+        glo.w = __builtin_sqrtf(__shfl(r, CS == 16 ? 16 * ((lane & 7) >> 1) : 8 * (lane & 7), kWave));
+    }
+    // (for CS = 16 lanes 2k and 2k + 1 hold the same box)
+    if (CS == 16 ? (lane & 1) == 0 && lane < 2 * kBoxes : lane < kBoxes) {
+        const int k = CS == 16 ? lane >> 1 : lane;
+        s_box[w][2 * k] = glo;
+        s_box[w][2 * k + 1] = ghi;
     }
 
     // Periodic axes: a pair can take an image one period away only if the
@@ -402,12 +498,15 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
     // open-boundary tests; the margin on R keeps the decision on the safe side
     // of FP32 rounding, so no accepted pair changes.
     bool wraps = false;
-    IBox sbox;  // the super-cluster's box (positions), for the batches' own decision
+    float span_c[3] = {0.0f, 0.0f, 0.0f};  // the super-cluster's box centre
+    float reach2[3] = {0.0f, 0.0f, 0.0f};  // its half width and R: how far a j-particle's image matters
+    int nimages = 1;  // a wrapping super-cluster so wide that a second image of a j-particle can matter: 8
+    float wrap_err = 0.0f;
     if (kPbc) {
         float slo[3] = {glo.x, glo.y, glo.z}, shi[3] = {ghi.x, ghi.y, ghi.z};
         float r = glo.w;  // full build: replaced by the largest radius of all
 #pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
+        for (int d = 1; d < 8; d <<= 1) {  // (the boxes repeat every 8 lanes)
 #pragma unroll
             for (int t = 0; t < 3; t++) {
                 slo[t] = fminf(slo[t], __shfl_xor(slo[t], d, 64));
@@ -418,31 +517,89 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
         const float4 rlo = a.cs_box[0], rhi = a.cs_box[1];  // root box: the particles' span
         if (!gather) r = fmaxf(r, rlo.w);  // pairs use max(h_i, h_j)
         const float plo[3] = {rlo.x, rlo.y, rlo.z}, phi[3] = {rhi.x, rhi.y, rhi.z};
-        bool w_lane = false;
+        bool w_lane = false, far_lane = false;
 #pragma unroll
         for (int t = 0; t < 3; t++) {
             if (a.per.L[t] < INFINITY) {
                 const float reach = a.per.L[t] - 1.0001f * r - 1e-5f * a.per.L[t];
                 w_lane = w_lane || !(phi[t] - slo[t] <= reach) || !(shi[t] - plo[t] <= reach);
+                // the image nearest to the box's centre is the minimum image of
+                // every pair within R if half the box and R stay inside half
+                // a period
+                span_c[t] = 0.5f * slo[t] + 0.5f * shi[t];
+                reach2[t] = 1.0001f * (fmaxf(shi[t] - span_c[t], span_c[t] - slo[t]) + r);
+                far_lane = far_lane || !(reach2[t] < 0.4999f * a.per.L[t]);
+                wrap_err = fmaxf(wrap_err, a.per.L[t]);
             }
         }
         wraps = sfc_ballot(w_lane) != 0;
-#pragma unroll
-        for (int t = 0; t < 3; t++) {  // wave-uniform: scalar registers
-            sbox.lo[t] = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, slo[t])));
-            sbox.hi[t] = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, shi[t])));
-        }
+        if (wraps && sfc_ballot(far_lane)) nimages = 8;
     }
     const Period per = wraps ? a.per : Period{};
-    // minimum images of a pair's components on periodic axes
-    auto wrap = [&](float &dx, float &dy, float &dz) SFC_INLINE {
-        if (wraps) wave_min_image(dx, dy, dz, a.per);
-    };
+
+    // The filter's frame: positions relative to the middle particle, scaled so
+    // that the super-cluster and a radius around it fill +-64 or so
+    const int mid = sfc_popc(sfc_ballot(ix + iy + iz == ix + iy + iz && (int64_t)own_p0 + lane < n)) >> 1;
+    // (a wrapping super-cluster: on a periodic axis relative to its box's centre)
+    float cx = sfc_readlane_f(ix, mid), cy = sfc_readlane_f(iy, mid), cz = sfc_readlane_f(iz, mid);
+    if (kPbc && wraps) {
+        cx = a.per.L[0] < INFINITY ? span_c[0] : cx;
+        cy = a.per.L[1] < INFINITY ? span_c[1] : cy;
+        cz = a.per.L[2] < INFINITY ? span_c[2] : cz;
+    }
+    float sc, sc2;        // scale and its square
+    float range;          // bound on the scaled squares that the filter takes
+    float err_sq, err_0;  // its error bound's coefficients
+    float h2_min;         // smallest squared radius of the super-cluster's particles
+    {
+        float dx = ix - cx, dy = iy - cy, dz = iz - cz;
+        float m = ipresent ? fmaxf(__builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx)), ih2) : 0.0f;
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) m = fmaxf(m, __shfl_xor(m, d, kWave));
+        int k = 6 - ((__builtin_amdgcn_frexp_expf(m) + 1) >> 1);
+        k = k < -60 ? -60 : (k > 60 ? 60 : k);
+        sc = ldexpf(1.0f, k);
+        sc2 = ldexpf(1.0f, 2 * k);
+        const float reach_i = __builtin_sqrtf(m * sc2) * 1.0001f;  // a bound on the scaled |x_i| and h_i
+        dx *= sc;
+        dy *= sc;
+        dz *= sc;
+        const float sq = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
+        // infinite coordinates: every pair goes to the exact tests
+        const bool serves = reach_i < 128.0f;
+        range = serves ? kFar16 : -1.0f;
+        ipresent = ipresent && serves;
+        if (!ipresent) dx = dy = dz = 0.0f;
+        const Operands A = operands<true>(dx, dy, dz, sq, sq - ih2 * sc2, ipresent);
+        s_a[w][2][lane] = A.plain[0];
+        s_a[w][3][lane] = A.plain[1];
+        uint4_t f0 = A.plain[0], f1 = A.plain[1];
+        f0[kSquareA] = A.other[0][0];
+        f0[kSquareA + 1] = A.other[0][1];
+        f1[kSquareA] = A.other[1][0];
+        f1[kSquareA + 1] = A.other[1][1];
+        s_a[w][0][lane] = f0;
+        s_a[w][1][lane] = f1;
+        // the smallest squared radius: j-particles with none above it need no
+        // test of their own (a counting list's never do)
+        float hm = ipresent && !gather ? ih2 : INFINITY;
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) hm = fminf(hm, __shfl_xor(hm, d, kWave));
+        h2_min = hm;
+        // E = |x_j|^2 err_sq + h_j^2 2^-17 + err_0 (see test_batch), scaled; N^2 is
+        // at most 2 (reach_i^2 + |x_j|^2), 128 N at most N^2 + 64^2, and so on
+        const float werr = wraps ? wrap_err * sc * 0x1p-19f : 0.0f;  // times N, at most (N^2 + 128^2) / 256
+        err_sq = 0x1p-15f + werr * 0x1p-7f;
+        err_0 = reach_i * reach_i * err_sq + 0x1p-4f + werr * 64.0f;
+    }
+
+    float inf = INFINITY;
+    asm("" : "+v"(inf));  // kept in a register (see test_batch)
 
     // stack of node records {first, end, child count (0 = leaf), first child
     // slot}; a node is pushed only after its box passed the test
     uint4 *stack = s_stack[w];
-    uint2 *queue = s_queue[w];
+    uint32_t *queue = s_queue[w];
     int sp = 0;
     // the tree of this super-cluster's system; list entries are cluster
     // indices relative to the system's first cluster
@@ -457,7 +614,6 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
     sp = 1;
     wave_sync();
 
-    int64_t last = -1;  // highest j-cluster already tested
     uint32_t nj = 0, prevj = 0xFFFFFFFFu, seg_words = 0;
     // entries collect in lane (index % 64) of ej / em and leave 64 at a time
     // into the next staging chunk: one coalesced store each, and the
@@ -492,330 +648,312 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
         prevj = sfc_readlane(ej, (int)cnt - 1);
     };
 
-    // Exact tests of the queued candidates, in queue order. Lane (q, p) =
-    // (lane / CS, lane % CS) loads particle p of candidate b + q, so one load
-    // per field brings the j-particles of kBatch = 64 / CS candidates, and the
-    // next batch loads while the current one's tiles run; each tile's lanes
-    // then take their j-particle from lane q CS + p with ds_bpermute (a lane
-    // exchange, no memory access). Absent particles (past n) are put far away
-    // with a zero radius; counting lists use the i radius only (a zero j
-    // radius makes max(h_i^2, h_j^2) = h_i^2).
-    constexpr int kBatch = kWave / CS;
-    uint32_t qn = 0;
-    // The loads read a clamped index unconditionally, so they stay in flight
-    // while the current batch's tiles run (a load behind a branch, or one
-    // whose value is used at once, ends with a wait); validity and the squared
-    // radius apply when the batch is used (drains run with qn >= 1).
+    // The queue of candidate j-clusters whose boxes came near (a ring);
+    // batches of kBatch leave it in order. Lane (q, p) = (lane / CS, lane % CS)
+    // takes particle p of the batch's candidate q: the loads read a clamped
+    // index unconditionally, so the next batch's stay in flight while the
+    // current batch is tested (a load behind a branch, or one whose value is
+    // used at once, ends with a wait).
+    uint32_t qh = 0, qt = 0;
     struct JLoad {
         float x, y, z, h;
-        bool v;
     };
-    auto load_batch = [&](uint32_t b0, JLoad &f) SFC_INLINE {
-        const uint32_t e = b0 + (uint32_t)(lane / CS);
-        const uint32_t cj = queue[e < qn ? e : qn - 1u].x;
-        const int64_t p = (int64_t)cj * CS + (lane & (CS - 1));
-        const int64_t pc = p < n ? p : n - 1;
-        f.v = e < qn && p < n;
+    const uint32_t n_last = (uint32_t)(n - 1);
+    auto load_batch = [&](uint32_t b0, uint32_t cnt, JLoad &f) SFC_INLINE {
+        const uint32_t q = (uint32_t)(lane / CS);
+        const uint32_t p = queue[(b0 + (q < cnt ? q : 0u)) % kQueueCap] * CS + (uint32_t)(lane & (CS - 1));
+        const uint32_t pc = p < n_last ? p : n_last;
         f.x = a.x[pc];
         f.y = a.y[pc];
         f.z = a.z[pc];
         f.h = a.h[pc];
     };
-    auto batch_vals = [&](const JLoad &f) SFC_INLINE {
-        const float hh = f.v && !gather ? f.h : 0.0f;
-        return make_float4(f.v ? f.x : kFar, f.v ? f.y : kFar, f.v ? f.z : kFar, hh * hh);
-    };
-    auto lane_f = [](int src, float v) SFC_INLINE {  // v of lane src (ds_bpermute takes a byte address)
-        return __int_as_float(__builtin_amdgcn_ds_bpermute(src << 2, __float_as_int(v)));
-    };
 
-    // Cluster sizes 4 and 16: one step tests the 64 particle pairs of one
-    // tile (CS = 4: four), the queued candidates one after another.
-    auto drain_regs = [&]() SFC_INLINE {
-        wave_sync();
-        JLoad f;
-        load_batch(0, f);
-        for (uint32_t b0 = 0; b0 < qn; b0 += kBatch) {
-            const float4 c = batch_vals(f);
-            const float cx = c.x, cy = c.y, cz = c.z, ch2 = c.w;
-            if (b0 + kBatch < qn) load_batch(b0 + kBatch, f);
-            const uint32_t bn = qn - b0 < (uint32_t)kBatch ? qn - b0 : (uint32_t)kBatch;
-            for (uint32_t q = 0; q < bn; q++) {
-            const uint2 qe = queue[b0 + q];
-            const uint32_t cjv = (uint32_t)__builtin_amdgcn_readfirstlane((int)qe.x);
-            const uint32_t cmask = (uint32_t)__builtin_amdgcn_readfirstlane((int)qe.y);
-            float xj[kNj], yj[kNj], zj[kNj], hj2[kNj];
-#pragma unroll
-            for (int t = 0; t < kNj; t++) {
-                const int src = (int)q * CS + S::jpart(t, lane);
-                xj[t] = lane_f(src, cx);
-                yj[t] = lane_f(src, cy);
-                zj[t] = lane_f(src, cz);
-                hj2[t] = lane_f(src, ch2);
-            }
-            // the j-cluster is one of our own i-clusters: exclude i == j
-            // (full list) or keep only j > i (half list)
-            const int self_c = (cjv >= own_c0 && cjv < own_c0 + kNsub) ? (int)(cjv - own_c0) : -1;
-            auto keep = [&](int ci, int ipos, int jpos) SFC_INLINE {
-                return half ? (ci < self_c || (ci == self_c && jpos > ipos)) : (ci != self_c || jpos != ipos);
-            };
-            uint32_t mask = 0;
-            if constexpr (CS == 4) {
-                const int jl = lane & 3, il = (lane >> 2) & 3, q = lane >> 4;
-#pragma unroll
-                for (int k = 0; k < kNreg; k++) {
-                    if ((cmask >> (4 * k)) & 0xFu) {
-                        float dx = xj[0] - ix[k];
-                        float dy = yj[0] - iy[k];
-                        float dz = zj[0] - iz[k];
-                        if (kPbc) wrap(dx, dy, dz);
-                        const float dxx = dx * dx;
-                        const float d2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dxx));
-                        bool pr = d2 < max_sq(ih2[k], hj2[0]);
-                        if (self_c >= 0) pr = pr && keep(4 * k + q, il, jl);
-                        const uint64_t b = sfc_ballot(pr);
-                        const uint32_t g = (uint32_t)((b & 0xFFFFull) != 0) |
-                                           ((uint32_t)(((b >> 16) & 0xFFFFull) != 0) << 1) |
-                                           ((uint32_t)(((b >> 32) & 0xFFFFull) != 0) << 2) |
-                                           ((uint32_t)((b >> 48) != 0) << 3);
-                        mask |= g << (4 * k);
-                    }
-                }
-            } else {
-                const int jq = lane & 3, il = lane >> 2;
-#pragma unroll
-                for (int c = 0; c < kNreg; c++) {
-                    if ((cmask >> c) & 1u) {
-                        bool pr = false;
-#pragma unroll
-                        for (int t = 0; t < 4; t++) {
-                            float dx = xj[t] - ix[c];
-                            float dy = yj[t] - iy[c];
-                            float dz = zj[t] - iz[c];
-                            if (kPbc) wrap(dx, dy, dz);
-                            const float dxx = dx * dx;
-                            const float d2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dxx));
-                            bool p = d2 < max_sq(ih2[c], hj2[t]);
-                            if (self_c >= 0) {
-                                if (half)
-                                    p = p && (c < self_c || (c == self_c && 4 * t + jq > il));
-                                else if (c == self_c)
-                                    p = p && 4 * t + jq != il;
-                            }
-                            pr = pr || p;
-                        }
-                        if (sfc_ballot(pr)) mask |= 1u << c;
-                    }
-                }
-            }
-            if (mask) {
-                const bool mine = lane == (int)(nj & (kWave - 1));
-                ej = mine ? cjv - jbase : ej;
-                em = mine ? mask : em;
-                if ((++nj & (kWave - 1)) == 0) flush(kWave);
-            }
-            }
-        }
-        qn = 0;
-        wave_sync();
-    };
-
-    // Cluster size 8: lane-parallel tiles. A batch is 8 queued candidates;
-    // bit 8q + c of W says that the box test kept i-cluster c for candidate
-    // q. W's set bits, numbered in order, are the batch's tiles, and a round
-    // hands tiles 8r .. 8r + 7 to the eight groups of 8 lanes: lane (g, l)
-    // takes i-particle l of its tile's i-cluster and steps through the 8
-    // j-particles of its candidate, one pair per step, so one step tests one
-    // pair of each of 8 tiles. A tile passes if a lane of its group saw a
-    // pair; the results go back to W's bit positions (R), whose bytes are the
-    // candidates' masks. The j-particles of the batch wait in LDS (candidate
-    // q's particle p at 9q + p).
-    __shared__ float4 s_jp[kWavesPerBlock][kLaneTiles ? 72 : 1];
-    // tile t of the batch: byte offsets of its i-cluster in s_ip (bits 0-10),
-    // of its candidate's own i-cluster if it is one of ours, else 8 clusters
-    // (bits 11-21), and of its candidate in s_jp (bits 22-31)
+    // The exact FP32 tests of the tiles set in `aq` (lane q: i-cluster mask of
+    // the batch's candidate q, cluster `cj`); returns the mask of those holding
+    // a pair. Only the tiles that the filter left open come here: pairs within
+    // its error of the radius, and the tiles of an i-cluster with itself. They
+    // read their particles from memory again (few tiles: LDS copies of every
+    // batch would cost more, and a wave per SIMD). Absent particles are far
+    // away with a zero radius, as are a counting list's j radii and those of
+    // unflagged i-particles.
+    // Cluster size 8: a round gives one tile to each group of 8 lanes; lane
+    // (g, l) takes i-particle l of its tile and steps through the 8
+    // j-particles of its candidate, two of which it holds while the quad's
+    // other lanes supply the rest (DPP operands).
     __shared__ uint32_t s_tile[kWavesPerBlock][kLaneTiles ? 64 : 1];
-    __shared__ uint2 s_ent[kWavesPerBlock][kLaneTiles ? 8 : 1];
     __shared__ uint64_t s_hits[kWavesPerBlock][kLaneTiles ? 8 : 1];
-    if constexpr (kLaneTiles) s_tile[w][lane] = 0u;  // entries past a batch's tiles stay valid offsets
-    auto drain_lanes = [&]() SFC_INLINE {
-        wave_sync();
-        constexpr uint32_t kRow = 9 * sizeof(float4);  // one cluster's stride in s_ip and s_jp
-        constexpr uint64_t kBytes = 0x0101010101010101ull;
-        const int g = lane >> 3, l = lane & 7;
-        const char *ipb = reinterpret_cast<const char *>(s_ip[w]) + l * sizeof(float4);
-        const char *jpb = reinterpret_cast<const char *>(s_jp[w]);
-        JLoad f;
-        load_batch(0, f);
-        for (uint32_t b0 = 0; b0 < qn; b0 += kBatch) {
-            const float4 jv = batch_vals(f);
-            s_jp[w][9 * g + l] = jv;
-            // a wrapping super-cluster still skips the minimum images for a
-            // batch whose j-particles all lie within half a period of both
-            // ends of its box on every periodic axis (far_from_box)
-            bool bwrap = false;
-            if constexpr (kPbc) bwrap = wraps && sfc_ballot(b0 + (uint32_t)g < qn && far_from_box(jv, sbox, a.per)) != 0;
-            if (b0 + kBatch < qn) load_batch(b0 + kBatch, f);
-            // lane (g, l): candidate b0 + g against i-cluster l
-            const uint32_t e = b0 + (uint32_t)g;
-            const bool ev = e < qn;
-            const uint2 qe = queue[ev ? e : b0];
-            const uint32_t rel = qe.x - own_c0;  // below 8: the candidate is our own i-cluster rel
-            const bool bit = ev && ((qe.y >> l) & 1u);
+    if constexpr (kLaneTiles) s_tile[w][lane] = 0u;  // entries past a batch's tiles: some valid tile
+    auto particle = [&](uint32_t p, bool i_side) SFC_INLINE {
+        const bool v = p < (uint64_t)n;
+        const uint32_t pc = v ? p : (uint32_t)(n - 1);
+        float hh = a.h[pc];
+        if (gather && (!i_side || !a.p_active[pc])) hh = 0.0f;
+        return make_float4(v ? a.x[pc] : kFar, v ? a.y[pc] : kFar, v ? a.z[pc] : kFar, v ? hh * hh : 0.0f);
+    };
+    auto exact_tiles = [&](uint32_t aq, uint32_t cj) SFC_INLINE -> uint32_t {
+        if constexpr (kLaneTiles) {
+            const int g = lane >> 3, l = lane & 7;
+            const uint32_t am = (uint32_t)__shfl((int)aq, g, kWave);
+            const bool bit = (am >> l) & 1u;
             const uint64_t W = sfc_ballot(bit);
-            const bool mixed = sfc_ballot(ev && rel < 8u) != 0;  // a candidate of the batch is ours
             const int T = sfc_popc(W);
             const uint32_t k = __builtin_amdgcn_mbcnt_hi((uint32_t)(W >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)W, 0u));
-            if (bit) s_tile[w][k] = kRow * (uint32_t)l | (kRow * (rel < 8u ? rel : 8u)) << 11 | (kRow * (uint32_t)g) << 22;
+            if (bit) s_tile[w][k] = (uint32_t)(l | (g << 3));  // tile k: its i-cluster and candidate
             wave_sync();
             // s_hits[r]: round r's ballot (byte g: group g, i.e. tile 8r + g,
             // saw a pair); bytes of tiles past T are never read
             for (int r = 0; 8 * r < T; r++) {
-                const uint32_t tv = s_tile[w][8 * r + g];  // tiles past T: stale valid offsets, results unread
-                const uint32_t ioff = tv & 0x7FFu, soff = (tv >> 11) & 0x7FFu;
-                const float4 ip = *reinterpret_cast<const float4 *>(ipb + ioff);
-                // lane (g, l) holds j-particles l % 4 and 4 + l % 4 of its
-                // candidate; step p takes particle p from lane p % 4 of the
-                // quad (a DPP operand, no LDS traffic)
-                const float4 *jb = reinterpret_cast<const float4 *>(jpb + (tv >> 22));
-                const float4 ja = jb[l & 3], jz = jb[4 + (l & 3)];
-                // the round's tests; batches that can wrap take the minimum
-                // images (one wave-uniform choice per round keeps the 8 steps
-                // free of branches)
-                auto tests = [&](auto wrapc) SFC_INLINE {
-                    constexpr bool kW = decltype(wrapc)::value;
-                    uint64_t t = 0;
-                    if (!mixed) {
-                        static_for<CS>([&](auto pc) {
-                            constexpr int p = decltype(pc)::value;
-                            const float4 &jq = p < 4 ? ja : jz;
-                            float dx = quad_bcast<p & 3>(jq.x) - ip.x;
-                            float dy = quad_bcast<p & 3>(jq.y) - ip.y;
-                            float dz = quad_bcast<p & 3>(jq.z) - ip.z;
-                            if constexpr (kW) wave_min_image(dx, dy, dz, a.per);
-                            const float dxx = dx * dx;
-                            const float d2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dxx));
-                            t |= sfc_ballot(d2 < max_sq(quad_bcast<p & 3>(jq.w), ip.w));
-                        });
-                    } else {
-                        // pairs within our own super-cluster: i = 8c + l and
-                        // j = 8c' + p; the half list keeps j > i (c < c', or
-                        // c = c' and l < p), the full list all but i = j
-                        const uint64_t below = sfc_ballot(ioff < soff), same = sfc_ballot(ioff == soff);
-                        static_for<CS>([&](auto pc) {
-                            constexpr int p = decltype(pc)::value;
-                            const float4 &jq = p < 4 ? ja : jz;
-                            float dx = quad_bcast<p & 3>(jq.x) - ip.x;
-                            float dy = quad_bcast<p & 3>(jq.y) - ip.y;
-                            float dz = quad_bcast<p & 3>(jq.z) - ip.z;
-                            if constexpr (kW) wave_min_image(dx, dy, dz, a.per);
-                            const float dxx = dx * dx;
-                            const float d2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dxx));
-                            const uint64_t keep = half ? below | (same & (((1ull << p) - 1ull) * kBytes)) : ~(same & ((1ull << p) * kBytes));
-                            t |= sfc_ballot(d2 < max_sq(quad_bcast<p & 3>(jq.w), ip.w)) & keep;
-                        });
-                    }
-                    return t;
-                };
-                uint64_t acc;
-                if constexpr (kPbc) {
-                    if (bwrap)
-                        acc = tests(std::true_type{});
-                    else
-                        acc = tests(std::false_type{});
-                } else {
-                    acc = tests(std::false_type{});
-                }
-                if (lane == 0) s_hits[w][r] = acc;
+                const uint32_t tv = s_tile[w][8 * r + g];  // tiles past T: an older tile, results unread
+                const uint32_t ci = own_c0 + (tv & 7u), c = (uint32_t)__shfl((int)cj, (int)(tv >> 3), kWave);
+                const float4 ip = particle(8u * ci + (uint32_t)l, true);
+                const float4 ja = particle(8u * c + (uint32_t)(l & 3), false), jz = particle(8u * c + 4u + (uint32_t)(l & 3), false);
+                constexpr uint64_t kBytes = 0x0101010101010101ull;
+                const uint64_t same = sfc_ballot(ci == c);
+                uint64_t t = 0;
+                static_for<8>([&](auto pc) SFC_INLINE {
+                    constexpr int p = decltype(pc)::value;
+                    const float4 &jq = p < 4 ? ja : jz;
+                    float dx = quad_bcast<p & 3>(jq.x) - ip.x;
+                    float dy = quad_bcast<p & 3>(jq.y) - ip.y;
+                    float dz = quad_bcast<p & 3>(jq.z) - ip.z;
+                    if (kPbc && wraps) wave_min_image(dx, dy, dz, a.per);
+                    const float dxx = dx * dx;
+                    const float d2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dxx));
+                    // lane (g, l): i = l and j = p of the same cluster; the half
+                    // list keeps j > i, the full list all but i = j
+                    const uint64_t keep = half ? ~same | (((1ull << p) - 1ull) * kBytes) : ~(same & ((1ull << p) * kBytes));
+                    t |= sfc_ballot(d2 < max_sq(quad_bcast<p & 3>(jq.w), ip.w)) & keep;
+                });
+                if (lane == 0) s_hits[w][r] = t;
             }
             wave_sync();
             // W's bit of rank k: tile k, byte k % 8 of round k / 8
             const uint32_t hw = reinterpret_cast<const uint32_t *>(s_hits[w])[(k >> 2) & 15u];
             const uint64_t R = sfc_ballot(bit && ((hw >> (8 * (k & 3u))) & 0xFFu) != 0u);
-            // candidate g's mask is byte g of R; the nonempty ones join the
-            // list in queue order (lane (nj + rank) % 64 of ej / em)
-            const uint32_t mq = lane < kBatch ? (uint32_t)(R >> ((8 * lane) & 63)) & 0xFFu : 0u;
-            const uint64_t ne = sfc_ballot(mq != 0u);
-            if (ne) {
-                const uint32_t cnt = (uint32_t)sfc_popc(ne);
-                if (mq) {
-                    const uint32_t rk = __builtin_amdgcn_mbcnt_lo((uint32_t)ne, 0u);
-                    s_ent[w][rk] = make_uint2(queue[b0 + lane].x - jbase, mq);
-                }
-                wave_sync();
-                const uint32_t base = nj & (kWave - 1);
-                const uint32_t first = cnt < kWave - base ? cnt : kWave - base;
-                const uint32_t d = (uint32_t)lane - base;
-                if (d < first) {
-                    const uint2 v = s_ent[w][d];
-                    ej = v.x;
-                    em = v.y;
-                }
-                nj += first;
-                if ((nj & (kWave - 1)) == 0) flush(kWave);
-                if (cnt > first) {
-                    if ((uint32_t)lane < cnt - first) {
-                        const uint2 v = s_ent[w][first + lane];
-                        ej = v.x;
-                        em = v.y;
-                    }
-                    nj += cnt - first;
-                }
-                wave_sync();  // the next batch rewrites s_ent
-            }
-        }
-        qn = 0;
-        wave_sync();
-    };
-
-    auto drain = [&]() SFC_INLINE {
-        if constexpr (kLaneTiles)
-            drain_lanes();
-        else
-            drain_regs();
-    };
-
-    const uint64_t lt = sfc_lt_mask();
-    while (sp > 0) {
-        sp--;
-        const uint4 rv = stack[sp];
-        const uint32_t nfirst = (uint32_t)__builtin_amdgcn_readfirstlane((int)rv.x);
-        const uint32_t nend = (uint32_t)__builtin_amdgcn_readfirstlane((int)rv.y);
-        const uint32_t nchild = (uint32_t)__builtin_amdgcn_readfirstlane((int)rv.z);
-        const uint32_t cslot = (uint32_t)__builtin_amdgcn_readfirstlane((int)rv.w);
-        if (nend > (uint64_t)n || nfirst >= nend || cslot + nchild > a.nslots) {  // only on a broken tree
-            if (lane == 0) atomicOr(&a.status[kStTree], 16u);
-            break;
-        }
-        if (nchild == 0) {
-            int64_t c0 = nfirst / CS;
-            const int64_t c1 = (nend - 1) / CS;
-            if (c0 <= last) c0 = last + 1;
-            if (half && c0 < (int64_t)own_c0) c0 = own_c0;  // j-clusters wholly before i: no j > i
-            // candidate clusters cb .. cb + kSlots - 1: lane l tests i-cluster
-            // l % kNsub against the box of candidate cb + l / kNsub; the
-            // survivors (nonempty i-cluster masks) join the queue in order
-            for (int64_t cb = c0; cb <= c1; cb += kSlots) {
-                // unconditional loads from a clamped index (cluster indices
-                // fit 32 bits); the slots past c1 (repeats of c1) are left
-                // out of the ballot (one vector compare: a scalar mask took
-                // ten scalar instructions per step)
-                const uint32_t cjc = min((uint32_t)cb + (uint32_t)(lane / kNsub), (uint32_t)c1);
-                const float4 l = a.bbox[2 * (size_t)cjc], u = a.bbox[2 * (size_t)cjc + 1];
-                const float4 blo = make_float4(l.x, l.y, l.z, gather ? 0.0f : l.w);  // own radius only when counting
-                const int64_t nv = (c1 - cb + 1) * kNsub;  // lanes holding candidates cb .. c1
-                const uint64_t bal = sfc_ballot(boxes_near<kPbc>(ilo, ihi, blo, u, per) && lane < nv);
-                if (bal) {
-                    const int sl = lane < kSlots ? lane : 0;
-                    const uint32_t cm = lane < kSlots ? (uint32_t)(bal >> (sl * kNsub)) & S::kFull : 0u;
-                    const uint64_t sv = sfc_ballot(cm != 0u);
-                    if (cm) queue[qn + (uint32_t)sfc_popc(sv & lt)] = make_uint2((uint32_t)cb + (uint32_t)lane, cm);
-                    qn += (uint32_t)sfc_popc(sv);
-                    if (qn >= (uint32_t)kWave) drain();
-                }
-            }
-            if (c1 > last) last = c1;
+            return lane < kBatch ? (uint32_t)(R >> ((8 * lane) & 63)) & 0xFFu : 0u;
         } else {
+            // one tile at a time: CS = 4 on 16 lanes, CS = 16 in four steps
+            uint32_t out = 0;
+            for (uint64_t todo = sfc_ballot(aq != 0u); todo; todo &= todo - 1ull) {
+                const int q = __builtin_ctzll(todo);
+                const uint32_t c = sfc_readlane(cj, q);
+                uint32_t got = 0;
+                for (uint32_t am = sfc_readlane(aq, q); am; am &= am - 1u) {
+                    const uint32_t t = (uint32_t)__builtin_ctz(am);
+                    const int il = CS == 4 ? (lane >> 2) & 3 : lane >> 2;
+                    const float4 ip = particle((own_c0 + t) * CS + (uint32_t)il, true);
+                    bool pr = false;
+#pragma unroll
+                    for (int k = 0; k < CS / 4; k++) {
+                        const int jl = 4 * k + (lane & 3);
+                        const float4 jp = particle(c * CS + (uint32_t)jl, false);
+                        float dx = jp.x - ip.x;
+                        float dy = jp.y - ip.y;
+                        float dz = jp.z - ip.z;
+                        if (kPbc && wraps) wave_min_image(dx, dy, dz, a.per);
+                        const float dxx = dx * dx;
+                        const float d2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dxx));
+                        bool p = d2 < max_sq(ip.w, jp.w);
+                        if (c == own_c0 + t) p = p && (half ? jl > il : jl != il);
+                        pr = pr || p;
+                    }
+                    if (sfc_ballot(pr && (CS == 16 || lane < 16))) got |= 1u << t;
+                }
+                out = lane == q ? got : out;
+            }
+            return out;
+        }
+    };
+
+    // One batch: the filter decides every pair of the 64 x 64 block whose
+    // squared distance is not within E of the larger squared radius. E bounds
+    // the filter's error: with N >= |x_i| + |x_j| (scaled, so N is about 128),
+    // the split coordinates and dropped products leave 2^-18.4 N^2, the FP32
+    // accumulation of 16 products 2^-18.8 N^2, the rounding of x - c and of the
+    // exact formula 2^-21 N^2, and halves too small for their normal range
+    // (below 2^-14) 2^-11.4 N; 2^-16 N max(N, 128) + 2^-17 h_j^2 covers them with
+    // room, and on a wrapping axis the roundings of x - c and of the image add
+    // at most 2^-20.6 N L. A j-particle beyond the halves' range (or NaN: a
+    // batch's padding), or any when an i-particle is, has E = inf: all its
+    // pairs are open. Lanes without a particle hold some
+    // particle of the same cluster or of an unused candidate again, which
+    // changes no mask.
+    auto test_batch = [&](const JLoad &f, uint32_t cnt) SFC_INLINE {
+        const float hh = gather ? 0.0f : f.h;
+        const float h2 = hh * hh;
+        const bool both = sfc_ballot(h2 > h2_min) != 0;  // some max(h_i, h_j) may be h_j
+        uint32_t seen_any = 0;
+        uint64_t open_any[2] = {0, 0};  // lane l: j-particle l % 32 of either half has a pair within E of a radius
+        uint64_t bad_any = 0;
+        // Images of the batch: the nearest to the frame's centre; in a box only
+        // a few radii wide also the second nearest on each periodic axis
+        // (image bit t: axis t), where some j-particle's can reach. A pair is
+        // near in one image if and only if it is near in its minimum image, as
+        // every radius is below half a period.
+        for (int img = 0; img < (kPbc ? nimages : 1); img++) {
+            float dx = f.x - cx, dy = f.y - cy, dz = f.z - cz;
+            if (kPbc && wraps) {
+                dx = min_image(dx, a.per.L[0], a.per.hL[0]);
+                dy = min_image(dy, a.per.L[1], a.per.hL[1]);
+                dz = min_image(dz, a.per.L[2], a.per.hL[2]);
+                if (img) {
+                    if (img & 1) dx -= copysignf(a.per.L[0], dx);
+                    if (img & 2) dy -= copysignf(a.per.L[1], dy);
+                    if (img & 4) dz -= copysignf(a.per.L[2], dz);
+                    const bool near = !((img & 1) && fabsf(dx) > reach2[0]) && !((img & 2) && fabsf(dy) > reach2[1]) &&
+                                      !((img & 4) && fabsf(dz) > reach2[2]);
+                    if (!sfc_ballot(near)) continue;
+                }
+            }
+            dx *= sc;
+            dy *= sc;
+            dz *= sc;
+            const float sq = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
+            const float h2s = h2 * sc2;
+            const bool bad = !(sq + h2s < range);
+            float E = __builtin_fmaf(sq, err_sq, __builtin_fmaf(h2s, 0x1p-17f, err_0));
+            E = bad ? INFINITY : E;
+            Operands B = operands<false>(dx, dy, dz, sq, sq - h2s, true);
+            uint32_t e0 = (uint32_t)__float_as_int(E), e1 = e0;
+            swap_halves(e0, e1);  // e0: E of j-particle l % 32 of the first half, e1: of the second
+            uint32_t seen = 0;  // candidate_mask's bits, the first one pushed ends highest
+            static_for<2>([&](auto bc) SFC_INLINE {
+                constexpr int b = decltype(bc)::value;
+                const float Eb = __int_as_float((int)(b ? e1 : e0));
+                // least d^2 - max(h_i, h_j)^2 of the group's four pairs; one block's
+                // sums at a time (two would spill). (v_min3 from the register inf
+                // on: a minimum of two sums alone would first quiet both)
+                float x[2][4];
+                static_for<2>([&](auto fc) SFC_INLINE {
+                    constexpr int fh = decltype(fc)::value;
+                    __builtin_amdgcn_sched_barrier(0);
+                    const float16_t u = pair_block(s_a[w][fh][lane], B.plain[b]);  // d^2 - h_i^2
+                    static_for<4>([&](auto gc) SFC_INLINE {
+                        constexpr int g = decltype(gc)::value;
+                        x[fh][g] = fminf(fminf(inf, u[4 * g]), u[4 * g + 1]);
+                        x[fh][g] = fminf(fminf(x[fh][g], u[4 * g + 2]), u[4 * g + 3]);
+                    });
+                });
+                if (both) {
+                    B.plain[b][kSquareB] = B.other[b][0];
+                    B.plain[b][kSquareB + 1] = B.other[b][1];
+                    static_for<2>([&](auto fc) SFC_INLINE {
+                        constexpr int fh = decltype(fc)::value;
+                        __builtin_amdgcn_sched_barrier(0);
+                        const float16_t v = pair_block(s_a[w][2 + fh][lane], B.plain[b]);  // d^2 - h_j^2
+                        static_for<4>([&](auto gc) SFC_INLINE {
+                            constexpr int g = decltype(gc)::value;
+                            x[fh][g] = fminf(fminf(x[fh][g], v[4 * g]), v[4 * g + 1]);
+                            x[fh][g] = fminf(fminf(x[fh][g], v[4 * g + 2]), v[4 * g + 3]);
+                        });
+                    });
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                float near = inf;
+                static_for<8>([&](auto kc) SFC_INLINE {
+                    constexpr int k = decltype(kc)::value;
+                    const float v = x[k / 4][k % 4];
+                    near = fminf(near, fabsf(v));
+                    // the sign of x + E joins from the right (v_alignbit)
+                    seen = __builtin_amdgcn_alignbit(seen, (uint32_t)__float_as_int(v + Eb), 31u);
+                });
+                open_any[b] |= sfc_ballot(!(near > Eb));
+            });
+            __builtin_amdgcn_sched_barrier(0);
+            seen_any |= seen;
+            bad_any |= sfc_ballot(bad);  // (bit l: j-particle l)
+        }
+        uint32_t mq = candidate_mask<CS>(__brev(seen_any) >> 16, lane);
+        // lane q: candidate q of the batch; its tiles left open
+        const uint32_t cj = queue[(qh + (uint32_t)(lane < (int)cnt ? lane : 0)) % kQueueCap];
+        const bool used = lane < (int)cnt;
+        const uint32_t rel = cj - own_c0;  // below kNsub: our own i-cluster rel
+        uint32_t aq = 0;
+        if (open_any[0] | open_any[1]) {
+            const uint64_t oj = (uint64_t)fold_halves(open_any[0]) | ((uint64_t)fold_halves(open_any[1]) << 32);
+            constexpr uint64_t kMine = (1ull << CS) - 1ull;
+            const int sh = (lane * CS) & 63;
+            if ((bad_any >> sh) & kMine) mq = 0;  // not even a number
+            if (used && ((oj >> sh) & kMine)) aq = ~mq & S::kFull;
+        }
+        if (used && rel < (uint32_t)kNsub) {
+            const uint32_t own = 1u << rel;
+            if (half) {  // i-clusters after the candidate have no j > i in it
+                mq &= own - 1u;
+                aq &= own - 1u;
+            } else {
+                mq &= ~own;
+            }
+            aq |= own;
+        }
+        if (sfc_ballot(aq != 0u)) mq |= exact_tiles(aq, cj);
+        // the candidates with a nonempty mask join the list in queue order
+        // (lane (nj + rank) % 64 of ej / em)
+        if (!used) mq = 0u;
+        const uint64_t ne = sfc_ballot(mq != 0u);
+        if (ne) {
+            const uint32_t c = (uint32_t)sfc_popc(ne);
+            if (mq) s_ent[w][__builtin_amdgcn_mbcnt_lo((uint32_t)ne, 0u)] = make_uint2(cj - jbase, mq);
+            wave_sync();
+            const uint32_t base = nj & (kWave - 1);
+            const uint32_t first = c < kWave - base ? c : kWave - base;
+            const uint32_t d = (uint32_t)lane - base;
+            if (d < first) {
+                const uint2 e = s_ent[w][d];
+                ej = e.x;
+                em = e.y;
+            }
+            nj += first;
+            if ((nj & (kWave - 1)) == 0) flush(kWave);
+            if (c > first) {
+                if ((uint32_t)lane < c - first) {
+                    const uint2 e = s_ent[w][first + lane];
+                    ej = e.x;
+                    em = e.y;
+                }
+                nj += c - first;
+            }
+            wave_sync();  // the next batch rewrites s_ent
+        }
+    };
+
+    // Candidate clusters of the leaves collect one per lane (cn of them, the
+    // current leaf's from pos to pos_end next); 64 at a time are tested against
+    // the boxes of the super-cluster's particles 8 at a time (their boxes from
+    // LDS), the survivors join the queue in order and its whole batches are
+    // tested.
+    const uint64_t lt = sfc_lt_mask();
+    uint32_t cand = 0, cn = 0, pos = 0, pos_end = 0;
+    for (bool more = true; more;) {
+        if (pos < pos_end) {
+            const uint32_t room = kWave - cn, left = pos_end - pos;
+            const uint32_t take = left < room ? left : room;
+            const uint32_t d = (uint32_t)lane - cn;
+            if (d < take) cand = pos + d;
+            cn += take;
+            pos += take;
+            if (cn < (uint32_t)kWave) continue;
+        } else if (sp > 0) {
+            sp--;
+            const uint4 rv = stack[sp];
+            const uint32_t nfirst = (uint32_t)__builtin_amdgcn_readfirstlane((int)rv.x);
+            const uint32_t nend = (uint32_t)__builtin_amdgcn_readfirstlane((int)rv.y);
+            const uint32_t nchild = (uint32_t)__builtin_amdgcn_readfirstlane((int)rv.z);
+            const uint32_t cslot = (uint32_t)__builtin_amdgcn_readfirstlane((int)rv.w);
+            if (nend > (uint64_t)n || nfirst >= nend || cslot + nchild > a.nslots) {  // only on a broken tree
+                if (lane == 0) atomicOr(&a.status[kStTree], 16u);
+                sp = 0;
+                continue;
+            }
+            if (nchild == 0) {  // a leaf: its clusters not collected yet (pos_end: all before are)
+                const uint32_t c0 = nfirst / CS;
+                pos = c0 > pos_end ? c0 : pos_end;
+                if (half && pos < own_c0) pos = own_c0;  // j-clusters wholly before i: no j > i
+                const uint32_t e = (nend - 1) / CS + 1;
+                pos_end = e > pos_end ? e : pos_end;
+                continue;
+            }
             // lane (ch, g): child ch = lane / 8 of the node against group g's box
             const int ch = lane >> 3;
             const bool act = ch < (int)nchild;
@@ -827,12 +965,15 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
             const uint4 crec = a.cs_rec[slot];
             const float4 lo = make_float4(l.x, l.y, l.z, gather ? 0.0f : l.w);  // own radius only when counting
             // a half list never needs a node that ends before the super-cluster
-            const bool hit = act && boxes_near<kPbc>(glo, ghi, lo, hi, per) && (!half || crec.y > own_p0);
+            const int gb = CS == 16 ? (lane & 7) >> 1 : lane & 7;
+            const bool hit = act && boxes_near<kPbc>(s_box[w][2 * gb], s_box[w][2 * gb + 1], lo, hi, per) &&
+                             (!half || crec.y > own_p0);
             const uint32_t keep = nonzero_bytes(sfc_ballot(hit));
             const int cnt = __popc(keep);
             if (sp + cnt > kStackCap) {  // cannot happen in a valid octree (depth <= 21)
                 if (lane == 0) atomicOr(&a.status[kStTree], 8u);
-                break;
+                sp = 0;
+                continue;
             }
             if ((lane & 7) == 0 && ((keep >> ch) & 1u)) {
                 const int r = __popc(keep & ((1u << ch) - 1u));
@@ -840,9 +981,38 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
             }
             sp += cnt;
             wave_sync();
+            continue;
+        } else {
+            more = false;  // the last box step, then the rest of the queue
+        }
+        if (cn) {
+            const float4 l = a.bbox[2 * (size_t)cand], u = a.bbox[2 * (size_t)cand + 1];  // (lanes past cn: an older candidate)
+            const float4 blo = make_float4(l.x, l.y, l.z, gather ? 0.0f : l.w);  // own radius only when counting
+            bool hit = false;
+#pragma unroll
+            for (int k = 0; k < kBoxes; k++)
+                hit = hit | boxes_near<kPbc>(s_box[w][2 * k], s_box[w][2 * k + 1], blo, u, per);
+            hit = hit && (uint32_t)lane < cn;
+            cn = 0;
+            const uint64_t sv = sfc_ballot(hit);
+            if (hit) queue[(qt + (uint32_t)sfc_popc(sv & lt)) % kQueueCap] = cand;
+            qt += (uint32_t)sfc_popc(sv);
+            wave_sync();
+        }
+        uint32_t total = qt - qh;  // whole batches, but at the end
+        if (more) total = total / kBatch * kBatch;
+        if (total == 0) continue;
+        JLoad f;
+        load_batch(qh, total < (uint32_t)kBatch ? total : (uint32_t)kBatch, f);
+        while (total) {
+            const uint32_t cnt = total < (uint32_t)kBatch ? total : (uint32_t)kBatch;
+            const JLoad c = f;
+            total -= cnt;
+            if (total) load_batch(qh + cnt, total < (uint32_t)kBatch ? total : (uint32_t)kBatch, f);
+            test_batch(c, cnt);
+            qh += cnt;
         }
     }
-    if (qn) drain();
     if (nj & (kWave - 1)) flush(nj & (kWave - 1));
     if (lane == 0) {
         const uint32_t mwords = (nj * S::kMaskBytes + 3u) / 4u;
