@@ -16,6 +16,9 @@ namespace sfcnl {
 namespace {
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kIn = SFCNL_HSEED_NFEAT;  // 8 features
@@ -23,6 +26,11 @@ constexpr int kHid = 64;
 constexpr int kOffW1 = 0, kOffB1 = 512, kOffW2 = 576, kOffB2 = 4672, kOffW3 = 4736, kOffB3 = 4800;
 constexpr int kNParam = SFCNL_MLP_NPARAM;  // 4801
 constexpr int kWaves = 4;
+constexpr int kInferBlocks = 512;  // inference: two blocks per CU share the samples (256: 3 % slower, 1,024: 1 %)
+constexpr int kRedWords = 4 * (16 + 16) + 2;  // registers of a wave's partial gradient and loss
+// Row stride of the 64-wide weight rows in LDS: 34 words, so that the 16 rows
+// of a fragment read lie on different banks (64 shorts: all on one).
+constexpr int kRowW = kHid + 4;
 
 // float -> bfloat16, round to nearest even (NaN stays NaN)
 __device__ __forceinline__ short f2bf(float f) {
@@ -40,28 +48,41 @@ __device__ __forceinline__ f32x4 mfma(bf16x4 a, bf16x4 b, f32x4 c) {
 // Weights of one block, rounded to bf16 once.
 struct WeightsLds {
     short W1[kHid * 16];     // [unit][feature], features 8..15 zero
-    short W2[kHid * kHid];   // [out unit][in unit]
-    short W2T[kHid * kHid];  // [in unit][out unit]
+    short W2[kHid * kRowW];   // [out unit][in unit]
+    short W2T[kHid * kRowW];  // [in unit][out unit]
     float b1[kHid], b2[kHid], w3q[kHid];
     float b3;
 };
 
-__device__ void load_weights(WeightsLds &L, const float *__restrict__ p) {
-    for (int t = threadIdx.x; t < kHid * 16; t += blockDim.x) {
-        const int u = t / 16, f = t % 16;
-        L.W1[t] = f < kIn ? f2bf(p[kOffW1 + u * kIn + f]) : (short)0;
+// (256 threads; every load is in flight before the first is used)
+__device__ __forceinline__ void load_weights(WeightsLds &L, const float *__restrict__ p) {
+    constexpr int kT = 256;
+    const int t = threadIdx.x;
+    float w1[kHid * kIn / kT], w2[kHid * kHid / kT];
+#pragma unroll
+    for (int k = 0; k < kHid * kHid / kT; k++) w2[k] = p[kOffW2 + k * kT + t];
+#pragma unroll
+    for (int k = 0; k < kHid * kIn / kT; k++) w1[k] = p[kOffW1 + k * kT + t];
+    const float v1 = p[kOffB1 + (t & 63)], v2 = p[kOffB2 + (t & 63)], v3 = p[kOffW3 + (t & 63)], v4 = p[kOffB3];
+#pragma unroll
+    for (int k = 0; k < kHid * kHid / kT; k++) {
+        const int e = k * kT + t, u = e / kHid, f = e % kHid;
+        const short w = f2bf(w2[k]);
+        L.W2[u * kRowW + f] = w;
+        L.W2T[f * kRowW + u] = w;
     }
-    for (int t = threadIdx.x; t < kHid * kHid; t += blockDim.x) {
-        const short w = f2bf(p[kOffW2 + t]);
-        L.W2[t] = w;
-        L.W2T[(t % kHid) * kHid + t / kHid] = w;
+#pragma unroll
+    for (int k = 0; k < kHid * kIn / kT; k++) {
+        const int e = k * kT + t, u = e / kIn, f = e % kIn;
+        L.W1[u * 16 + f] = f2bf(w1[k]);
+        L.W1[u * 16 + kIn + f] = 0;
     }
-    for (int t = threadIdx.x; t < kHid; t += blockDim.x) {
-        L.b1[t] = p[kOffB1 + t];
-        L.b2[t] = p[kOffB2 + t];
-        L.w3q[t] = qbf(p[kOffW3 + t]);
+    if (t < kHid) {
+        L.b1[t] = v1;
+        L.b2[t] = v2;
+        L.w3q[t] = qbf(v3);
     }
-    if (threadIdx.x == 0) L.b3 = p[kOffB3];
+    if (t == 0) L.b3 = v4;
     __syncthreads();
 }
 
@@ -105,7 +126,7 @@ __device__ __forceinline__ void forward_tile(const WeightsLds &L, bf16x4 x, int 
     for (int mt = 0; mt < 4; mt++) {
         f32x4 acc = {0, 0, 0, 0};
 #pragma unroll
-        for (int kt = 0; kt < 4; kt++) acc = mfma(lds4(&L.W2[(mt * 16 + s) * kHid + kt * 16 + 4 * g]), F.h1[kt], acc);
+        for (int kt = 0; kt < 4; kt++) acc = mfma(lds4(&L.W2[(mt * 16 + s) * kRowW + kt * 16 + 4 * g]), F.h1[kt], acc);
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             const int u = mt * 16 + 4 * g + i;
@@ -123,25 +144,137 @@ __device__ __forceinline__ void forward_tile(const WeightsLds &L, bf16x4 x, int 
     F.y = part + L.b3 - f0 * (1.0f / 3.0f);
 }
 
-__global__ __launch_bounds__(256) void k_mlp_infer(const float *__restrict__ params, int64_t n,
+// Inference keeps its weights in registers: a wave loads its fragments once and
+// runs groups of 64 samples through them, four tiles of 16. Lane l reads sample
+// l of the group (16 bytes per lane, the next group's behind this one's layers)
+// and tile k takes the features where they are, in the slots of lane group k,
+// with zeros from the other groups against weights that every group holds. The
+// layers use the 32-deep form (v_mfma_f32_16x16x32_bf16; lane (s, g) holds 8
+// values of k per operand): slot j of lane group g stands for unit
+// 32 kt + 4 g + j (j < 4) or 32 kt + 16 + 4 g + j - 4, in the weights as in the
+// activations, so two accumulator fragments of a layer are the next layer's
+// operand as they are. Biases are the accumulators' start, relu and the bf16
+// rounding take three vector instructions per two values, and the output layer
+// is a product too (w3 in rows 0, 4, 8 and 12, so that each lane group has
+// every output and lane l keeps its own sample's). Before, every tile read its
+// weights from LDS (all 16 rows of a fragment on one bank), rounded with six
+// integer instructions per value and waited for its features: 77 -> 22 us for
+// 1,000,003 samples.
+union Frag8 {
+    bf16x8_t v;
+    bf16x2_t p[4];
+};
+
+__device__ __forceinline__ bf16x2_t round2(float a, float b) {
+    return __builtin_convertvector(f32x2{a, b}, bf16x2_t);
+}
+__device__ __forceinline__ f32x4 mfma32(const Frag8 &a, const Frag8 &b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
+}
+// units of slots 4h .. 4h + 3 of fragment kt in lane group g
+__device__ __forceinline__ int unit_of(int kt, int h, int g) { return 32 * kt + 16 * h + 4 * g; }
+
+// relu and rounding of two accumulator fragments into one operand. relu is the
+// median of v, 0 and `inf`, a register holding +inf: one instruction, 0 for NaN
+// (a maximum, or a median of constants, would quiet v first).
+__device__ __forceinline__ Frag8 activate(f32x4 a, f32x4 b, float inf) {
+    auto relu = [&](float v) { return __builtin_amdgcn_fmed3f(v, 0.0f, inf); };
+    Frag8 f;
+    f.p[0] = round2(relu(a[0]), relu(a[1]));
+    f.p[1] = round2(relu(a[2]), relu(a[3]));
+    f.p[2] = round2(relu(b[0]), relu(b[1]));
+    f.p[3] = round2(relu(b[2]), relu(b[3]));
+    return f;
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_mlp_infer(const float *__restrict__ params, int64_t n,
                                                    const uint16_t *__restrict__ feat, float *__restrict__ out) {
-    __shared__ WeightsLds L;
-    load_weights(L, params);
     const int lane = sfc_lane(), s = lane & 15, g = lane >> 4;
-    const int64_t ntiles = (n + 15) / 16;
+    const int64_t ngroups = (n + kWave - 1) / kWave;
     const int64_t wave = (int64_t)blockIdx.x * kWaves + threadIdx.x / kWave;
     const int64_t nw = (int64_t)gridDim.x * kWaves;
-    for (int64_t t = wave; t < ntiles; t += nw) {
-        const int64_t idx = t * 16 + s;
-        const bool v = idx < n;
-        Fwd F;
-        forward_tile(L, load_x(feat, idx, v, g), s, g, F);
-        if (v && g == 0) out[idx] = F.y;
+    if (wave >= ngroups) return;
+    // the next group's features load while this one's layers run
+    auto load = [&](int64_t t) {
+        const int64_t idx = t * kWave + lane;
+        return *reinterpret_cast<const uint4 *>(feat + (idx < n ? idx : n - 1) * kIn);
+    };
+    uint4 next = load(wave);
+    Frag8 w1[4], w2[4][2], w3[2];
+    f32x4 b1[4], b2[4];
+#pragma unroll
+    for (int mt = 0; mt < 4; mt++) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const float *r = params + kOffW1 + (mt * 16 + s) * kIn + 2 * q;
+            w1[mt].p[q] = round2(r[0], r[1]);
+        }
+#pragma unroll
+        for (int kt = 0; kt < 2; kt++)
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const float *r = params + kOffW2 + (mt * 16 + s) * kHid + unit_of(kt, q >> 1, g) + 2 * (q & 1);
+                w2[mt][kt].p[q] = round2(r[0], r[1]);
+            }
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            b1[mt][i] = params[kOffB1 + mt * 16 + 4 * g + i];
+            b2[mt][i] = params[kOffB2 + mt * 16 + 4 * g + i];
+        }
+    }
+#pragma unroll
+    for (int kt = 0; kt < 2; kt++)
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const float *r = params + kOffW3 + unit_of(kt, q >> 1, g) + 2 * (q & 1);
+            const bf16x2_t w = round2(r[0], r[1]);
+            w3[kt].p[q] = (s & 3) == 0 ? w : bf16x2_t{0, 0};
+        }
+    const float b3 = params[kOffB3];
+    float inf = INFINITY;
+    asm("" : "+v"(inf));
+    for (int64_t t = wave; t < ngroups; t += nw) {
+        const uint4 f = next;
+        if (t + nw < ngroups) next = load(t + nw);
+        float out_l = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const bool mine = g == k;
+            Frag8 x;
+            x.v = __builtin_bit_cast(bf16x8_t, make_uint4(mine ? f.x : 0u, mine ? f.y : 0u, mine ? f.z : 0u, mine ? f.w : 0u));
+            f32x4 z[4];
+#pragma unroll
+            for (int mt = 0; mt < 4; mt++) z[mt] = mfma32(w1[mt], x, b1[mt]);
+            const Frag8 h0 = activate(z[0], z[1], inf), h1 = activate(z[2], z[3], inf);
+#pragma unroll
+            for (int mt = 0; mt < 4; mt++) z[mt] = mfma32(w2[mt][1], h1, mfma32(w2[mt][0], h0, b2[mt]));
+            const Frag8 k0 = activate(z[0], z[1], inf), k1 = activate(z[2], z[3], inf);
+            const f32x4 y = mfma32(w3[1], k1, mfma32(w3[0], k0, f32x4{0, 0, 0, 0}));
+            out_l = mine ? y[0] : out_l;
+        }
+        // residual on the cube-root rule: -feature0 / 3 = log((target / (n+1))^(1/3))
+        const float f0 = __uint_as_float(f.x << 16);
+        const int64_t idx = t * kWave + lane;
+        if (idx < n) out[idx] = out_l + b3 - f0 * (1.0f / 3.0f);
     }
 }
 
+// Sum over the 16 lanes that share lane / 16 (DPP: quad swaps, then the
+// mirrored half row and row).
+template <int CTRL>
+__device__ __forceinline__ float dpp_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float row_sum(float v) {
+    return dpp_add<0x140>(dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(v))));
+}
+
 // Gradient of the mean squared error over a batch: each wave accumulates its
-// tiles and writes one partial gradient (kNParam floats) and partial loss.
+// tiles, the block's four waves join theirs in LDS, and the block writes one
+// partial gradient (kNParam floats) and partial loss. One tile per wave up to
+// the block limit: at batch 8,192 128 blocks of one tile per wave and 128 rows
+// for the reduction, against 64 blocks of two tiles per wave and 256 rows,
+// whose lane sums went through LDS exchanges (192 per wave): 32 -> 18 us.
 __global__ __launch_bounds__(256) void k_mlp_grad(const float *__restrict__ params, int64_t nsamp,
                                                   const uint16_t *__restrict__ feat, const float *__restrict__ target,
                                                   int64_t batch, int64_t start, int64_t mul, int64_t add,
@@ -200,7 +333,7 @@ __global__ __launch_bounds__(256) void k_mlp_grad(const float *__restrict__ para
         for (int mt = 0; mt < 4; mt++) {
             f32x4 acc = {0, 0, 0, 0};
 #pragma unroll
-            for (int kt = 0; kt < 4; kt++) acc = mfma(lds4(&L.W2T[(mt * 16 + s) * kHid + kt * 16 + 4 * g]), d2b[kt], acc);
+            for (int kt = 0; kt < 4; kt++) acc = mfma(lds4(&L.W2T[(mt * 16 + s) * kRowW + kt * 16 + 4 * g]), d2b[kt], acc);
 #pragma unroll
             for (int i = 0; i < 4; i++) {
                 const float d1 = F.z1[mt][i] > 0.0f ? acc[i] : 0.0f;
@@ -243,19 +376,45 @@ __global__ __launch_bounds__(256) void k_mlp_grad(const float *__restrict__ para
     for (int mt = 0; mt < 4; mt++) {
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-#pragma unroll
-            for (int d = 1; d < 16; d <<= 1) {
-                dw3[mt][i] += __shfl_xor(dw3[mt][i], d, 64);
-                db2[mt][i] += __shfl_xor(db2[mt][i], d, 64);
-                db1[mt][i] += __shfl_xor(db1[mt][i], d, 64);
-            }
+            dw3[mt][i] = row_sum(dw3[mt][i]);
+            db2[mt][i] = row_sum(db2[mt][i]);
+            db1[mt][i] = row_sum(db1[mt][i]);
         }
     }
     for (int d = 1; d < 64; d <<= 1) {
         db3 += __shfl_xor(db3, d, 64);
         loss += __shfl_xor(loss, d, 64);
     }
-    float *out = partial + wave * (kNParam + 1);
+    // join the waves' registers in LDS, register by register (the lane sums
+    // once per row: lane 16 g holds registers i of group g)
+    __shared__ float s_red[kWaves / 2][kRedWords][kWave];
+    auto registers = [&](auto &&f) __attribute__((always_inline)) {
+        int k = 0;
+#pragma unroll
+        for (int mt = 0; mt < 4; mt++) {
+#pragma unroll
+            for (int nt = 0; nt < 4; nt++)
+#pragma unroll
+                for (int i = 0; i < 4; i++) dW2[mt][nt][i] = f(k++, dW2[mt][nt][i]);
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                dW1[mt][i] = f(k++, dW1[mt][i]);
+                dw3[mt][i] = f(k++, dw3[mt][i]);
+                db2[mt][i] = f(k++, db2[mt][i]);
+                db1[mt][i] = f(k++, db1[mt][i]);
+            }
+        }
+        db3 = f(k++, db3);
+        loss = f(k++, loss);
+    };
+    for (int half = kWaves / 2; half > 0; half >>= 1) {
+        if (w >= half && w < 2 * half) registers([&](int k, float v) { return s_red[w - half][k][lane] = v; });
+        __syncthreads();
+        if (w < half) registers([&](int k, float v) { return v + s_red[w][k][lane]; });
+        __syncthreads();
+    }
+    if (w != 0) return;
+    float *out = partial + (int64_t)blockIdx.x * (kNParam + 1);
 #pragma unroll
     for (int mt = 0; mt < 4; mt++) {
 #pragma unroll
@@ -277,13 +436,32 @@ __global__ __launch_bounds__(256) void k_mlp_grad(const float *__restrict__ para
     }
 }
 
-// Sum of the wave partials; index kNParam is the loss (mean over the batch).
-__global__ __launch_bounds__(256) void k_mlp_reduce(const float *__restrict__ partial, int nwaves, int64_t batch,
+// Sum of the block partials; index kNParam is the loss (mean over the batch).
+// A block takes 64 parameters, its four waves every fourth row each (eight rows
+// in flight at a time), and joins the four sums in LDS: 76 blocks of four
+// chains instead of 19 blocks whose threads each walked 256 rows one load after
+// another (57 -> 4 us at batch 8,192).
+__global__ __launch_bounds__(256) void k_mlp_reduce(const float *__restrict__ partial, int nrows, int64_t batch,
                                                     float *__restrict__ grad, float *__restrict__ loss) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > kNParam) return;
+    __shared__ float s_sum[kWaves][kWave];
+    const int lane = sfc_lane(), w = threadIdx.x / kWave;
+    const int p = blockIdx.x * kWave + lane;
+    const int pc = p <= kNParam ? p : kNParam;
     float acc = 0.0f;
-    for (int w = 0; w < nwaves; w++) acc += partial[(size_t)w * (kNParam + 1) + p];
+    for (int r0 = w; r0 < nrows; r0 += 8 * kWaves) {
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const int r = r0 + k * kWaves;
+            v[k] = partial[(size_t)(r < nrows ? r : w) * (kNParam + 1) + pc];
+        }
+#pragma unroll
+        for (int k = 0; k < 8; k++) acc += r0 + k * kWaves < nrows ? v[k] : 0.0f;
+    }
+    s_sum[w][lane] = acc;
+    __syncthreads();
+    if (w != 0 || p > kNParam) return;
+    acc = (s_sum[0][lane] + s_sum[1][lane]) + (s_sum[2][lane] + s_sum[3][lane]);
     if (p < kNParam)
         grad[p] = acc;
     else if (loss)
@@ -333,10 +511,23 @@ __global__ __launch_bounds__(256) void k_mlp_init(uint64_t seed, float *__restri
 //        closest to h
 //   6 log2(edge_0 / h) - L0 (where h falls between levels)
 //   7 log(target / 100)
-__device__ __forceinline__ uint32_t lower_bound_key(const uint64_t *keys, uint32_t lo, uint32_t hi, uint64_t v) {
+//
+// The cells' ends are found by binary searches in the sorted keys. A cell around
+// the particle lies in a narrow run of keys around it (mostly a few hundred at
+// the coarsest level asked for), so each block stages the keys of its particles
+// and kKeyPad to either side in LDS and searches there, the finer cells inside
+// the coarser ones; an end beyond the window is searched in memory. (Searching
+// the whole array, each step waited on a load: 82 -> 42 us for 1,000,003
+// particles.)
+constexpr int kFeatThreads = 256;
+constexpr int kKeyPad = 896;  // 2,048 keys in LDS: 16 KB
+
+// first index in [lo, hi) whose key is not below v
+template <typename F>
+__device__ __forceinline__ uint32_t lower_bound_key(F &&key, uint32_t lo, uint32_t hi, uint64_t v) {
     while (lo < hi) {
         const uint32_t mid = lo + (hi - lo) / 2;
-        if (keys[mid] < v)
+        if (key(mid) < v)
             lo = mid + 1;
         else
             hi = mid;
@@ -361,11 +552,20 @@ __device__ __forceinline__ float diag(float lx, float ly, float lz, float hx, fl
 // multiples of 64): the 8-particle cluster box and the super-cluster box come
 // from min / max over lane groups; absent particles are NaN, which fminf and
 // fmaxf ignore.
-__global__ __launch_bounds__(256) void k_features(int64_t n, const uint64_t *__restrict__ keys,
+__global__ __launch_bounds__(kFeatThreads) void k_features(int64_t n, const uint64_t *__restrict__ keys,
                                                   const float *__restrict__ x, const float *__restrict__ y,
                                                   const float *__restrict__ z, const float *__restrict__ h,
                                                   const int32_t *__restrict__ nnb, float edge0, int target,
                                                   uint16_t *__restrict__ feat, SegTable seg) {
+    constexpr int kWin = kFeatThreads + 2 * kKeyPad;
+    __shared__ uint64_t s_key[kWin];
+    const int64_t b0 = (int64_t)blockIdx.x * kFeatThreads - kKeyPad;  // index of s_key[0] (may be negative)
+#pragma unroll
+    for (int k = 0; k < kWin / kFeatThreads; k++) {
+        const int64_t a = b0 + k * kFeatThreads + threadIdx.x;
+        s_key[k * kFeatThreads + threadIdx.x] = keys[a < 0 ? 0 : (a < n ? a : n - 1)];
+    }
+    __syncthreads();
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool in = i < n;
     const float px = in ? x[i] : NAN, py = in ? y[i] : NAN, pz = in ? z[i] : NAN;
@@ -395,14 +595,33 @@ __global__ __launch_bounds__(256) void k_features(int64_t n, const uint64_t *__r
     const float lev = log2f(edge0 / hi);
     int L0 = (int)rintf(lev);
     L0 = L0 < 2 ? 2 : (L0 > 20 ? 20 : L0);
-    const uint64_t key = keys[i];
+    const uint64_t key = s_key[kKeyPad + threadIdx.x];
+    // the cell's run of keys at the three levels, each inside the coarser one's:
+    // [ca, cb) holds it; the part of [ca, cb) in the window is [wa, wb)
+    uint32_t ca = klo, cb = khi;
+    const uint32_t w0 = b0 < 0 ? 0u : (uint32_t)b0;
+    const uint32_t w1 = b0 + kWin < n ? (uint32_t)(b0 + kWin) : (uint32_t)n;
+    const uint32_t base = (uint32_t)b0;  // (window indices wrap to below kWin)
+    auto in_lds = [&](uint32_t k) { return s_key[k - base]; };
+    auto in_mem = [&](uint32_t k) { return keys[k]; };
 #pragma unroll
     for (int d = -1; d <= 1; d++) {
-        const int L = L0 + d;
-        const int shift = 3 * (21 - L);
+        const int shift = 3 * (21 - (L0 + d));
         const uint64_t pre = key >> shift;
-        const uint32_t a = lower_bound_key(keys, klo, khi, pre << shift);
-        const uint32_t b = lower_bound_key(keys, klo, khi, (pre + 1) << shift);
+        const uint64_t va = pre << shift, vb = (pre + 1) << shift;
+        const uint32_t wa = ca > w0 ? ca : w0, wb = cb < w1 ? cb : w1;
+        // (particle i is inside: the start is at most i, the end above it)
+        uint32_t a, b;
+        if (wa > ca && in_lds(wa) >= va)
+            a = lower_bound_key(in_mem, ca, wa, va);
+        else
+            a = lower_bound_key(in_lds, wa, (uint32_t)i, va);
+        if (wb < cb && in_lds(wb - 1u) < vb)
+            b = lower_bound_key(in_mem, wb, cb, vb);
+        else
+            b = lower_bound_key(in_lds, (uint32_t)i + 1u, wb, vb);
+        ca = a;
+        cb = b;
         f[4 + d] = logf(1.0f + (float)(b - a)) - lt;
     }
     f[6] = lev - (float)L0;
@@ -414,7 +633,7 @@ __global__ __launch_bounds__(256) void k_features(int64_t n, const uint64_t *__r
     *reinterpret_cast<uint4 *>(feat + i * kIn) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-constexpr int kGradMaxWaves = 256;
+constexpr int kGradMaxRows = 256;  // blocks of the gradient kernel, one partial gradient each
 
 }  // namespace
 }  // namespace sfcnl
@@ -434,9 +653,8 @@ extern "C" int sfcnl_mlp_infer(sfcnl_ctx ctx, const float *d_params, int64_t n, 
     if (n < 0) return set_err(ctx, SFCNL_E_ARG, "sfcnl_mlp_infer: n < 0");
     if (n == 0) return SFCNL_OK;
     if (!d_params || !d_feat || !d_out) return set_err(ctx, SFCNL_E_ARG, "sfcnl_mlp_infer: null pointer");
-    const int64_t ntiles = (n + 15) / 16;
-    int64_t blocks = (ntiles + kWaves - 1) / kWaves;
-    if (blocks > 4096) blocks = 4096;
+    int64_t blocks = (n + kWave * kWaves - 1) / (kWave * kWaves);
+    if (blocks > kInferBlocks) blocks = kInferBlocks;
     k_mlp_infer<<<(unsigned)blocks, 256, 0, ctx->stream>>>(d_params, n, d_feat, d_out);
     SFCNL_LAUNCHED(ctx);
     return SFCNL_OK;
@@ -444,7 +662,7 @@ extern "C" int sfcnl_mlp_infer(sfcnl_ctx ctx, const float *d_params, int64_t n, 
 
 extern "C" int sfcnl_mlp_grad_workspace(int64_t batch, size_t *ws_bytes) {
     if (batch < 1 || !ws_bytes) return SFCNL_E_ARG;
-    *ws_bytes = (size_t)kGradMaxWaves * (kNParam + 1) * sizeof(float);
+    *ws_bytes = (size_t)kGradMaxRows * (kNParam + 1) * sizeof(float);
     return SFCNL_OK;
 }
 
@@ -460,13 +678,13 @@ extern "C" int sfcnl_mlp_grad(sfcnl_ctx ctx, const float *d_params, int64_t nsam
     sfcnl_mlp_grad_workspace(batch, &need);
     if (ws_bytes < need) return set_err(ctx, SFCNL_E_ARG, "sfcnl_mlp_grad: workspace %zu < %zu", ws_bytes, need);
     const int64_t ntiles = (batch + 15) / 16;
-    int64_t waves = ntiles < kGradMaxWaves ? ntiles : kGradMaxWaves;
-    waves = (waves + kWaves - 1) / kWaves * kWaves;
+    int64_t blocks = (ntiles + kWaves - 1) / kWaves;
+    if (blocks > kGradMaxRows) blocks = kGradMaxRows;
     float *partial = reinterpret_cast<float *>(d_ws);
-    k_mlp_grad<<<(unsigned)(waves / kWaves), 256, 0, ctx->stream>>>(d_params, nsamp, d_feat, d_target, batch, start,
-                                                                    mul, add, partial);
+    k_mlp_grad<<<(unsigned)blocks, 256, 0, ctx->stream>>>(d_params, nsamp, d_feat, d_target, batch, start, mul, add,
+                                                          partial);
     SFCNL_LAUNCHED(ctx);
-    k_mlp_reduce<<<blocks_for(kNParam + 1, 256), 256, 0, ctx->stream>>>(partial, (int)waves, batch, d_grad, d_loss);
+    k_mlp_reduce<<<blocks_for(kNParam + 1, kWave), 256, 0, ctx->stream>>>(partial, (int)blocks, batch, d_grad, d_loss);
     SFCNL_LAUNCHED(ctx);
     return SFCNL_OK;
 }
@@ -486,7 +704,7 @@ extern "C" int sfcnl_mlp_adam(sfcnl_ctx ctx, float *d_params, const float *d_gra
 int sfcnl::features_impl(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys, const float *d_x, const float *d_y,
                          const float *d_z, const float *d_h, const int32_t *d_nnb, float box_edge, int target,
                          uint16_t *d_feat, const SegTable &seg) {
-    k_features<<<blocks_for(n, 256), 256, 0, ctx->stream>>>(n, d_keys, d_x, d_y, d_z, d_h, d_nnb, box_edge, target,
+    k_features<<<blocks_for(n, kFeatThreads), kFeatThreads, 0, ctx->stream>>>(n, d_keys, d_x, d_y, d_z, d_h, d_nnb, box_edge, target,
                                                             d_feat, seg);
     SFCNL_LAUNCHED(ctx);
     return SFCNL_OK;

@@ -287,8 +287,9 @@ __device__ __forceinline__ uint32_t pack16(float a, float b) {
     const half2_t v = {(_Float16)a, (_Float16)b};
     return __builtin_bit_cast(uint32_t, v);
 }
-// v rounded to a half. The empty asm keeps the conversion one instruction: the
-// scalar and the packed conversion round ties differently, and a remainder
+// v rounded to a half. The empty asm keeps the conversion one instruction of its
+// own: joined with the arithmetic before it (v_fma_mixlo) it would round v's
+// exact value, which near a tie is another half than v's, and a remainder
 // v - round16(v) needs the value that is packed.
 __device__ __forceinline__ float round16(float v) {
     _Float16 t = (_Float16)v;
