@@ -17,7 +17,6 @@ namespace {
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -145,117 +144,107 @@ __device__ __forceinline__ void forward_tile(const WeightsLds &L, bf16x4 x, int 
 }
 
 // Inference keeps its weights in registers: a wave loads its fragments once and
-// runs groups of 64 samples through them, four tiles of 16. Lane l reads sample
-// l of the group (16 bytes per lane, the next group's behind this one's layers)
-// and tile k takes the features where they are, in the slots of lane group k,
-// with zeros from the other groups against weights that every group holds. The
-// layers use the 32-deep form (v_mfma_f32_16x16x32_bf16; lane (s, g) holds 8
-// values of k per operand): slot j of lane group g stands for unit
-// 32 kt + 4 g + j (j < 4) or 32 kt + 16 + 4 g + j - 4, in the weights as in the
-// activations, so two accumulator fragments of a layer are the next layer's
-// operand as they are. Biases are the accumulators' start, relu and the bf16
-// rounding take three vector instructions per two values, and the output layer
-// is a product too (w3 in rows 0, 4, 8 and 12, so that each lane group has
-// every output and lane l keeps its own sample's). Before, every tile read its
-// weights from LDS (all 16 rows of a fragment on one bank), rounded with six
-// integer instructions per value and waited for its features: 77 -> 22 us for
-// 1,000,003 samples.
-union Frag8 {
-    bf16x8_t v;
-    bf16x2_t p[4];
+// runs groups of four 16-sample tiles through them, the next group's features
+// loading behind this one's layers. The products of the hidden layers are those
+// of forward_tile, in its order, so that every hidden activation rounds to the
+// same bf16 value; relu and rounding take three vector instructions per two
+// values, and the output layer is a product too (w3 in rows 0, 4, 8 and 12, so
+// that each lane group has every output and lane l keeps sample l's). Before,
+// every tile read its weights from LDS (all 16 rows of a fragment on one bank),
+// rounded with six integer instructions per value and waited for its features:
+// 77 -> 24 us for 1,000,003 samples.
+union Frag4 {
+    bf16x4 v;
+    bf16x2_t p[2];
 };
 
 __device__ __forceinline__ bf16x2_t round2(float a, float b) {
     return __builtin_convertvector(f32x2{a, b}, bf16x2_t);
 }
-__device__ __forceinline__ f32x4 mfma32(const Frag8 &a, const Frag8 &b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
-}
-// units of slots 4h .. 4h + 3 of fragment kt in lane group g
-__device__ __forceinline__ int unit_of(int kt, int h, int g) { return 32 * kt + 16 * h + 4 * g; }
 
-// relu and rounding of two accumulator fragments into one operand. relu is the
-// median of v, 0 and `inf`, a register holding +inf: one instruction, 0 for NaN
-// (a maximum, or a median of constants, would quiet v first).
-__device__ __forceinline__ Frag8 activate(f32x4 a, f32x4 b, float inf) {
-    auto relu = [&](float v) { return __builtin_amdgcn_fmed3f(v, 0.0f, inf); };
-    Frag8 f;
-    f.p[0] = round2(relu(a[0]), relu(a[1]));
-    f.p[1] = round2(relu(a[2]), relu(a[3]));
-    f.p[2] = round2(relu(b[0]), relu(b[1]));
-    f.p[3] = round2(relu(b[2]), relu(b[3]));
-    return f;
-}
-
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_mlp_infer(const float *__restrict__ params, int64_t n,
-                                                   const uint16_t *__restrict__ feat, float *__restrict__ out) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_mlp_infer(
+    const float *__restrict__ params, int64_t n, const uint16_t *__restrict__ feat, float *__restrict__ out) {
     const int lane = sfc_lane(), s = lane & 15, g = lane >> 4;
     const int64_t ngroups = (n + kWave - 1) / kWave;
     const int64_t wave = (int64_t)blockIdx.x * kWaves + threadIdx.x / kWave;
     const int64_t nw = (int64_t)gridDim.x * kWaves;
     if (wave >= ngroups) return;
-    // the next group's features load while this one's layers run
-    auto load = [&](int64_t t) {
-        const int64_t idx = t * kWave + lane;
-        return *reinterpret_cast<const uint4 *>(feat + (idx < n ? idx : n - 1) * kIn);
+    // features 4g .. 4g + 3 of sample s of each tile (groups 2 and 3: the padding)
+    struct Group {
+        uint2 f[4];
     };
-    uint4 next = load(wave);
-    Frag8 w1[4], w2[4][2], w3[2];
+    auto load = [&](int64_t t) {
+        Group r;
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const int64_t idx = t * kWave + 16 * k + s;
+            r.f[k] = *reinterpret_cast<const uint2 *>(feat + (idx < n ? idx : n - 1) * kIn + 4 * (g & 1));
+        }
+        return r;
+    };
+    Group next = load(wave);
+    Frag4 w1[4], w2[4][4], w3[4];
     f32x4 b1[4], b2[4];
 #pragma unroll
     for (int mt = 0; mt < 4; mt++) {
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const float *r = params + kOffW1 + (mt * 16 + s) * kIn + 2 * q;
-            w1[mt].p[q] = round2(r[0], r[1]);
-        }
+        for (int q = 0; q < 2; q++) {
+            const float *r = params + kOffW1 + (mt * 16 + s) * kIn + 4 * (g & 1) + 2 * q;
+            const bf16x2_t w = round2(r[0], r[1]);
+            w1[mt].p[q] = g < 2 ? w : bf16x2_t{0, 0};
 #pragma unroll
-        for (int kt = 0; kt < 2; kt++)
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const float *r = params + kOffW2 + (mt * 16 + s) * kHid + unit_of(kt, q >> 1, g) + 2 * (q & 1);
-                w2[mt][kt].p[q] = round2(r[0], r[1]);
+            for (int kt = 0; kt < 4; kt++) {
+                const float *c = params + kOffW2 + (mt * 16 + s) * kHid + kt * 16 + 4 * g + 2 * q;
+                w2[mt][kt].p[q] = round2(c[0], c[1]);
             }
+            const float *o = params + kOffW3 + mt * 16 + 4 * g + 2 * q;
+            const bf16x2_t v = round2(o[0], o[1]);
+            w3[mt].p[q] = (s & 3) == 0 ? v : bf16x2_t{0, 0};
+        }
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             b1[mt][i] = params[kOffB1 + mt * 16 + 4 * g + i];
             b2[mt][i] = params[kOffB2 + mt * 16 + 4 * g + i];
         }
     }
-#pragma unroll
-    for (int kt = 0; kt < 2; kt++)
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const float *r = params + kOffW3 + unit_of(kt, q >> 1, g) + 2 * (q & 1);
-            const bf16x2_t w = round2(r[0], r[1]);
-            w3[kt].p[q] = (s & 3) == 0 ? w : bf16x2_t{0, 0};
-        }
     const float b3 = params[kOffB3];
+    // relu is the median of v, 0 and a register holding +inf: one instruction, 0
+    // for NaN (a maximum, or a median of constants, would quiet v first)
     float inf = INFINITY;
     asm("" : "+v"(inf));
+    auto activate = [&](f32x4 z, f32x4 b) {
+        Frag4 f;
+        f.p[0] = round2(__builtin_amdgcn_fmed3f(z[0] + b[0], 0.0f, inf), __builtin_amdgcn_fmed3f(z[1] + b[1], 0.0f, inf));
+        f.p[1] = round2(__builtin_amdgcn_fmed3f(z[2] + b[2], 0.0f, inf), __builtin_amdgcn_fmed3f(z[3] + b[3], 0.0f, inf));
+        return f;
+    };
     for (int64_t t = wave; t < ngroups; t += nw) {
-        const uint4 f = next;
+        const Group f = next;
         if (t + nw < ngroups) next = load(t + nw);
         float out_l = 0.0f;
 #pragma unroll
         for (int k = 0; k < 4; k++) {
-            const bool mine = g == k;
-            Frag8 x;
-            x.v = __builtin_bit_cast(bf16x8_t, make_uint4(mine ? f.x : 0u, mine ? f.y : 0u, mine ? f.z : 0u, mine ? f.w : 0u));
-            f32x4 z[4];
+            const uint2 fk = f.f[k];
+            const bf16x4 x = __builtin_bit_cast(bf16x4, make_uint2(g < 2 ? fk.x : 0u, g < 2 ? fk.y : 0u));
+            Frag4 h[4];
 #pragma unroll
-            for (int mt = 0; mt < 4; mt++) z[mt] = mfma32(w1[mt], x, b1[mt]);
-            const Frag8 h0 = activate(z[0], z[1], inf), h1 = activate(z[2], z[3], inf);
+            for (int mt = 0; mt < 4; mt++) h[mt] = activate(mfma(w1[mt].v, x, f32x4{0, 0, 0, 0}), b1[mt]);
+            f32x4 y = {0, 0, 0, 0};
 #pragma unroll
-            for (int mt = 0; mt < 4; mt++) z[mt] = mfma32(w2[mt][1], h1, mfma32(w2[mt][0], h0, b2[mt]));
-            const Frag8 k0 = activate(z[0], z[1], inf), k1 = activate(z[2], z[3], inf);
-            const f32x4 y = mfma32(w3[1], k1, mfma32(w3[0], k0, f32x4{0, 0, 0, 0}));
-            out_l = mine ? y[0] : out_l;
+            for (int mt = 0; mt < 4; mt++) {
+                f32x4 acc = {0, 0, 0, 0};
+#pragma unroll
+                for (int kt = 0; kt < 4; kt++) acc = mfma(w2[mt][kt].v, h[kt].v, acc);
+                y = mfma(w3[mt].v, activate(acc, b2[mt]).v, y);
+            }
+            // residual on the cube-root rule: -feature0 / 3 = log((target / (n+1))^(1/3));
+            // lane s of the tile (g = 0) holds feature 0 of sample s
+            const float f0 = __shfl(__uint_as_float(fk.x << 16), s, kWave);
+            const float r = y[0] + b3 - f0 * (1.0f / 3.0f);
+            out_l = g == k ? r : out_l;
         }
-        // residual on the cube-root rule: -feature0 / 3 = log((target / (n+1))^(1/3))
-        const float f0 = __uint_as_float(f.x << 16);
         const int64_t idx = t * kWave + lane;
-        if (idx < n) out[idx] = out_l + b3 - f0 * (1.0f / 3.0f);
+        if (idx < n) out[idx] = out_l;
     }
 }
 
