@@ -348,14 +348,49 @@ __device__ __forceinline__ float sfc_readlane_f(float v, int lane) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
+// Inclusive prefix sum over the wave: DPP row shifts inside each row of 16 lanes,
+// then the rows' last lanes broadcast to the rows after them (seven vector
+// instructions; through __shfl_up it is six LDS exchanges with a compare, a
+// select and an add each).
 __device__ __forceinline__ uint32_t sfc_incl_scan(uint32_t v) {
-    const int l = sfc_lane();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t t = __shfl_up(v, d, 64);
-        if (l >= d) v += t;
-    }
-    return v;
+    int x = (int)v;
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);   // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);   // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);   // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);   // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2 and 3
+    return (uint32_t)x;
+}
+
+// v of the lane before (lane 0: unspecified). All lanes call it: a lane that is
+// off when it is read gives 0.
+__device__ __forceinline__ uint32_t sfc_prev_lane(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xF, 0xF, true);  // wave_shr:1
+}
+
+// f over the wave (f a minimum or maximum of two floats), in every lane: DPP
+// inside the rows of 16 lanes, then the rows' and the halves' exchange.
+template <int CTRL>
+__device__ __forceinline__ float sfc_dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+template <typename F>
+__device__ __forceinline__ float sfc_wave_reduce(float v, F f) {
+    v = f(v, sfc_dpp<0xB1>(v));   // quad_perm [1, 0, 3, 2]
+    v = f(v, sfc_dpp<0x4E>(v));   // quad_perm [2, 3, 0, 1]
+    v = f(v, sfc_dpp<0x141>(v));  // row_half_mirror
+    v = f(v, sfc_dpp<0x140>(v));  // row_mirror
+    const auto r = __builtin_amdgcn_permlane16_swap((uint32_t)__float_as_int(v), (uint32_t)__float_as_int(v), false, false);
+    v = f(__int_as_float((int)r[0]), __int_as_float((int)r[1]));
+    const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)__float_as_int(v), (uint32_t)__float_as_int(v), false, false);
+    return f(__int_as_float((int)h[0]), __int_as_float((int)h[1]));
+}
+__device__ __forceinline__ float sfc_wave_max(float v) {
+    return sfc_wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
+}
+__device__ __forceinline__ float sfc_wave_min(float v) {
+    return sfc_wave_reduce(v, [](float a, float b) { return fminf(a, b); });
 }
 
 // Gap along one axis between two boxes (or a point and a box), from

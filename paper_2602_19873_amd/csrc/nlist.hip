@@ -555,8 +555,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
     {
         float dx = ix - cx, dy = iy - cy, dz = iz - cz;
         float m = ipresent ? fmaxf(__builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx)), ih2) : 0.0f;
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) m = fmaxf(m, __shfl_xor(m, d, kWave));
+        m = sfc_wave_max(m);
         int k = 6 - ((__builtin_amdgcn_frexp_expf(m) + 1) >> 1);
         k = k < -60 ? -60 : (k > 60 ? 60 : k);
         sc = ldexpf(1.0f, k);
@@ -583,10 +582,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
         s_a[w][1][lane] = f1;
         // the smallest squared radius: j-particles with none above it need no
         // test of their own (a counting list's never do)
-        float hm = ipresent && !gather ? ih2 : INFINITY;
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) hm = fminf(hm, __shfl_xor(hm, d, kWave));
-        h2_min = hm;
+        h2_min = sfc_wave_min(ipresent && !gather ? ih2 : INFINITY);
         // E = |x_j|^2 err_sq + h_j^2 2^-17 + err_0 (see test_batch), scaled; N^2 is
         // at most 2 (reach_i^2 + |x_j|^2), 128 N at most N^2 + 64^2, and so on
         const float werr = wraps ? wrap_err * sc * 0x1p-19f : 0.0f;  // times N, at most (N^2 + 128^2) / 256
@@ -641,7 +637,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
             a.list_j[(size_t)chunk * kWave + lane] = ej;
             a.list_m[(size_t)chunk * kWave + lane] = (uint16_t)em;
         }
-        const uint32_t up = __shfl_up(ej, 1, 64);
+        const uint32_t up = sfc_prev_lane(ej);
         const uint32_t v = ej - (lane == 0 ? prevj : up);
         const uint32_t nib = (uint32_t)lane < cnt ? (v == 1u ? 0u : (v <= 9u ? 1u : 1u + nibbles_of(v))) : 0u;
         const uint32_t tot = sfc_readlane(sfc_incl_scan(nib), kWave - 1);
@@ -1117,7 +1113,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) void k_encode(EncArgs a) {
             if (valid) out[b0 + lane] = j;
             continue;
         }
-        uint32_t jprev = __shfl_up(j, 1, 64);
+        uint32_t jprev = sfc_prev_lane(j);
         if (lane == 0) jprev = prevj;
         const uint32_t v = j - jprev;
         const bool nonone = valid && v != 1u;
