@@ -5,13 +5,18 @@
 // without masks (differences from -1, nibble segments of 64 values,
 // Sec. II-B/II-C); rows follow each other in particle order.
 //
-// Build: from a full cluster list. One wavefront per particle decodes its
-// super-cluster's list 64 entries at a time, keeps the entries whose mask has
-// the particle's i-cluster bit (a ballot compaction into LDS), tests the
-// particles of 64 / CS of those j-clusters per step with the exact FP32 pair
-// formula, appends the survivors (already in ascending order) to a pending
-// buffer in LDS and encodes a segment whenever 64 are pending. A sizing run
-// and a writing run around a prefix sum place the rows deterministically.
+// Build: from a full cluster list. One wavefront takes 8 consecutive particles
+// (one cluster of 8, two of 4, half of one of 16): it decodes their
+// super-cluster's list 64 entries at a time, keeps the entries whose mask holds
+// one of their i-clusters (a ballot compaction into LDS), and fetches the
+// particles of 64 / CS of those j-clusters at a time, one per lane; each of the
+// 8 particles then tests all 64 with the exact FP32 pair formula and appends the
+// survivors (already in ascending order) to its pending buffer in LDS, and a
+// segment is encoded whenever 64 are pending. A sizing run and a writing run
+// around a prefix sum place the rows deterministically. (One wavefront per
+// particle decoded the list and fetched the candidates 8 times as often, and
+// placed the nibbles one LDS atomic at a time: sizing 729 -> 331 us, writing
+// 893 -> 521 us for 500,009 uniform particles of ~240 neighbours.)
 //
 // Pass: one wavefront per particle decodes 64 neighbours per step and
 // evaluates each lane's pair once; no tile of a cluster pair is wasted.
@@ -46,53 +51,90 @@ struct RowArgs {
     uint32_t *status;
 };
 
+constexpr int kRowGroup = 8;  // particles per wavefront
+
+// The nibbles of v from its most significant hex digit on, the first in the low
+// bits (nd digits, v > 0).
+__device__ __forceinline__ uint32_t digits_first(uint32_t v, uint32_t nd) {
+    v <<= 4u * (8u - nd);                                              // the first digit on top
+    v = __builtin_bswap32(v);                                          // bytes, then the nibbles in them, reversed
+    return ((v >> 4) & 0x0F0F0F0Fu) | ((v & 0x0F0F0F0Fu) << 4);
+}
+
+// ORs `bits` (fewer than 9 nibbles) into the nibble stream at words[] from
+// nibble t on.
+__device__ __forceinline__ void put_nibbles(uint32_t *words, uint32_t t, uint32_t bits) {
+    const uint64_t b = (uint64_t)bits << (4u * (t & 7u));
+    atomicOr(&words[t >> 3], (uint32_t)b);
+    if ((uint32_t)(b >> 32)) atomicOr(&words[(t >> 3) + 1u], (uint32_t)(b >> 32));
+}
+
 template <int CS, bool kCompIn, bool kWrite, bool kPbc>
-__global__ __launch_bounds__(256) void k_rows(RowArgs a) {
+__global__ __launch_bounds__(kWave) void k_rows(RowArgs a) {
     constexpr int kPerStep = kWave / CS;  // candidate j-clusters tested per step
-    __shared__ uint32_t s_cand[kWavesPerBlock][kWave];
-    __shared__ uint32_t s_pend[kWavesPerBlock][2 * kWave];
-    __shared__ uint32_t s_seg[kWavesPerBlock][kSegCap];
+    __shared__ uint32_t s_cand[kWave];
+    __shared__ uint32_t s_pend[kRowGroup][2 * kWave];
+    __shared__ uint32_t s_seg[kSegCap + 1];
     const int lane = sfc_lane();
-    const int w = threadIdx.x / kWave;
     const uint64_t lt = sfc_lt_mask();
-    const uint32_t i =
-        (uint32_t)__builtin_amdgcn_readfirstlane((int)(xcd_remap(blockIdx.x, gridDim.x) * kWavesPerBlock + w));
-    if (i >= a.n) return;
-    const uint32_t s = i / kScSize, c = (i % kScSize) / CS;
-    const float xi = a.x[i], yi = a.y[i], zi = a.z[i], hi = a.h[i];
-    const float hi2 = hi * hi;
+    const uint32_t n = (uint32_t)a.n;
+    const uint32_t grp = xcd_remap(blockIdx.x, gridDim.x);
+    const uint32_t i0 = grp * kRowGroup;
+    if (i0 >= n) return;
+    const uint32_t rows = n - i0 < (uint32_t)kRowGroup ? n - i0 : (uint32_t)kRowGroup;
+    const uint32_t s = i0 / kScSize, g = (i0 % kScSize) / kRowGroup;
+    // entries with a mask bit of one of our i-clusters
+    const uint32_t pick = CS == 4 ? 3u << (2 * g) : (CS == 8 ? 1u << g : 1u << (g >> 1));
+    // the rows' particles, wave-uniform (rows past the end: the last particle
+    // again, whose pairs are dropped)
+    float xi[kRowGroup], yi[kRowGroup], zi[kRowGroup], hi2[kRowGroup];
+    {
+        const uint32_t p = i0 + ((uint32_t)lane < rows ? (uint32_t)lane : rows - 1u);
+        const float px = a.x[p], py = a.y[p], pz = a.z[p], ph = a.h[p];
+#pragma unroll
+        for (int r = 0; r < kRowGroup; r++) {
+            xi[r] = sfc_readlane_f(px, r);
+            yi[r] = sfc_readlane_f(py, r);
+            zi[r] = sfc_readlane_f(pz, r);
+            const float h = sfc_readlane_f(ph, r);
+            hi2[r] = h * h;
+        }
+    }
     const uint32_t off = a.sc_info[2 * s], nj = a.sc_info[2 * s + 1];
     const uint8_t *mbytes = reinterpret_cast<const uint8_t *>(a.pool + off);
     const uint16_t *mshorts = reinterpret_cast<const uint16_t *>(a.pool + off);
     uint32_t p = off + (nj * (CS == 4 ? 2u : 1u) + 3u) / 4u;
 
-    uint32_t *out = nullptr;
+    // row state in lane r: words and neighbours emitted, the last neighbour
+    // emitted (differences start from -1), and where the row goes
+    uint32_t st_words = 0, st_count = 0, st_prev = 0xFFFFFFFFu, st_off = 0;
+    uint32_t fits = 0;  // rows that fit the pool
     if (kWrite) {
-        const uint32_t ro = a.row_off[i], re = a.row_off[i + 1];
-        if ((uint64_t)re > a.out_words) {  // the pool is too small: an empty row, reported
-            if (lane == 0) {
-                a.row_info[2 * (size_t)i] = ro;
-                a.row_info[2 * (size_t)i + 1] = 0u;
-                atomicOr(&a.status[kStPoolOverflow], 1u);
+        uint32_t end = 0;
+        if ((uint32_t)lane < rows) {
+            st_off = a.row_off[i0 + lane];
+            end = a.row_off[i0 + lane + 1];
+        }
+        fits = (uint32_t)sfc_ballot((uint32_t)lane < rows && (uint64_t)end <= a.out_words);
+        if (fits == 0) {
+            if ((uint32_t)lane < rows) {
+                a.row_info[2 * (size_t)(i0 + lane)] = st_off;
+                a.row_info[2 * (size_t)(i0 + lane) + 1] = 0u;
             }
+            if (lane == 0) atomicOr(&a.status[kStPoolOverflow], 1u);
             return;
         }
-        out = a.out + ro;
     }
-    uint32_t *cand = s_cand[w];
-    uint32_t *pend = s_pend[w];
-    uint32_t *seg = s_seg[w];
-    uint32_t npend = 0, count = 0, words = 0;
-    uint32_t prevrow = 0xFFFFFFFFu;  // last neighbour emitted (differences start from -1)
-
-    // emits the first m pending neighbours as one segment (or raw words)
-    auto flush = [&](uint32_t m) {
+    // emits the first m pending neighbours of row r as one segment (or raw words)
+    auto flush = [&](uint32_t r, uint32_t m) __attribute__((always_inline)) {
         const bool valid = (uint32_t)lane < m;
-        const uint32_t j = valid ? pend[lane] : 0u;
+        const uint32_t j = s_pend[r][lane];  // (lanes past m: unused)
+        const uint32_t words = sfc_readlane(st_words, (int)r);
+        uint32_t add = m;
         if (a.compress) {
-            uint32_t jprev = __shfl_up(j, 1, 64);
-            if (lane == 0) jprev = prevrow;
-            const uint32_t v = j - jprev;
+            const uint32_t prev = sfc_readlane(st_prev, (int)r);
+            const uint32_t up = sfc_prev_lane(j);
+            const uint32_t v = j - (lane == 0 ? prev : up);
             const bool nonone = valid && v != 1u;
             const uint64_t mk = sfc_ballot(nonone);
             const bool small = v <= 9u;
@@ -101,38 +143,35 @@ __global__ __launch_bounds__(256) void k_rows(RowArgs a) {
             const uint32_t ninfo = (uint32_t)sfc_popc(mk);
             const uint32_t incl = sfc_incl_scan(ndata);
             const uint32_t total_nib = ninfo + sfc_readlane(incl, kWave - 1);
-            const uint32_t segw = 2u + (total_nib + 7u) / 8u;
-            if (kWrite) {
-                const uint32_t info = small ? v + 6u : nn - 1u;
-                const uint32_t ipos = (uint32_t)sfc_popc(mk & lt);
-                const uint32_t dpos = ninfo + incl - ndata;
-                for (uint32_t q = lane; q < segw; q += kWave) seg[q] = 0u;
+            add = 2u + (total_nib + 7u) / 8u;
+            if (kWrite && ((fits >> r) & 1u)) {
+                uint32_t *out = a.out + sfc_readlane(st_off, (int)r) + words;
+                s_seg[lane] = 0u;
+                if (lane < kSegCap + 1 - kWave) s_seg[kWave + lane] = 0u;
                 wave_sync();
-                if (lane == 0) {
-                    seg[0] = (uint32_t)mk;
-                    seg[1] = (uint32_t)(mk >> 32);
-                }
                 if (nonone) {
-                    atomicOr(&seg[2 + ipos / 8], info << (4 * (ipos % 8)));
-                    for (uint32_t d = 0; d < ndata; d++) {
-                        const uint32_t nib = (v >> (4 * (ndata - 1 - d))) & 0xFu;
-                        const uint32_t t = dpos + d;
-                        atomicOr(&seg[2 + t / 8], nib << (4 * (t % 8)));
-                    }
+                    const uint32_t info = small ? v + 6u : nn - 1u;
+                    put_nibbles(s_seg + 2, (uint32_t)sfc_popc(mk & lt), info);
+                    if (!small) put_nibbles(s_seg + 2, ninfo + incl - ndata, digits_first(v, nn));
                 }
                 wave_sync();
-                for (uint32_t q = lane; q < segw; q += kWave) out[words + q] = seg[q];
+                const uint32_t lo = (uint32_t)mk, hi = (uint32_t)(mk >> 32);
+                for (uint32_t q = (uint32_t)lane; q < add; q += kWave) out[q] = q == 0 ? lo : (q == 1 ? hi : s_seg[q]);
+                wave_sync();
             }
-            words += segw;
-        } else {
-            if (kWrite && valid) out[words + lane] = j;
-            words += m;
+        } else if (kWrite && ((fits >> r) & 1u)) {
+            if (valid) a.out[sfc_readlane(st_off, (int)r) + words + lane] = j;
         }
-        prevrow = sfc_readlane(j, (int)m - 1);
-        count += m;
-        wave_sync();
+        const uint32_t lastj = sfc_readlane(j, (int)m - 1);
+        const bool mine = (uint32_t)lane == r;
+        st_prev = mine ? lastj : st_prev;
+        st_words += mine ? add : 0u;
+        st_count += mine ? m : 0u;
     };
 
+    uint32_t npend[kRowGroup];
+#pragma unroll
+    for (int r = 0; r < kRowGroup; r++) npend[r] = 0;
     uint32_t prevj = 0xFFFFFFFFu;  // decoding state of the cluster list
     for (uint32_t b0 = 0; b0 < nj; b0 += kWave) {
         const uint32_t cntb = nj - b0 < (uint32_t)kWave ? nj - b0 : (uint32_t)kWave;
@@ -144,47 +183,81 @@ __global__ __launch_bounds__(256) void k_rows(RowArgs a) {
         uint32_t mv = 0u;
         if ((uint32_t)lane < cntb) mv = CS == 4 ? (uint32_t)mshorts[b0 + lane] : (uint32_t)mbytes[b0 + lane];
         prevj = sfc_readlane(jv, (int)cntb - 1);
-        // the entries whose mask holds our i-cluster, in list (ascending) order
-        const bool sel = (uint32_t)lane < cntb && ((mv >> c) & 1u);
+        // the entries whose mask holds one of our i-clusters, in list (ascending) order
+        const bool sel = (mv & pick) != 0u;
         const uint64_t bsel = sfc_ballot(sel);
         const uint32_t ncand = (uint32_t)sfc_popc(bsel);
-        if (sel) cand[sfc_popc(bsel & lt)] = jv;
+        wave_sync();  // the last block's reads of s_cand are done
+        if (sel) s_cand[sfc_popc(bsel & lt)] = jv;
         wave_sync();
-        for (uint32_t k0 = 0; k0 < ncand; k0 += kPerStep) {
+        struct JLoad {
+            float x, y, z, h;
+            uint32_t j;
+        };
+        // lane (q, p): particle p of candidate k0 + q; the loads read a clamped
+        // index and the next step's stay in flight behind this one's tests
+        auto load = [&](uint32_t k0, JLoad &f) __attribute__((always_inline)) {
             const uint32_t kk = k0 + (uint32_t)(lane / CS);
-            const uint32_t j = (kk < ncand ? cand[kk < ncand ? kk : 0] : 0u) * CS + (uint32_t)(lane % CS);
-            const bool valid = kk < ncand && j < a.n;
-            float dx = valid ? a.x[j] - xi : 0.0f;
-            float dy = valid ? a.y[j] - yi : 0.0f;
-            float dz = valid ? a.z[j] - zi : 0.0f;
-            if (kPbc) wave_min_image(dx, dy, dz, a.per);
-            const float hj = valid ? a.h[j] : 0.0f;
-            const float dxx = dx * dx;
-            const float d2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dxx));
-            const bool in = valid && j != i && d2 < fmaxf(hi2, hj * hj);
-            const uint64_t b = sfc_ballot(in);
-            if (in) pend[npend + (uint32_t)sfc_popc(b & lt)] = j;
-            npend += (uint32_t)sfc_popc(b);
-            wave_sync();
-            if (npend >= (uint32_t)kWave) {
-                flush(kWave);
-                const uint32_t rest = npend - kWave;
-                const uint32_t tmp = (uint32_t)lane < rest ? pend[kWave + lane] : 0u;
+            f.j = kk < ncand ? s_cand[kk] * CS + (uint32_t)(lane % CS) : n;
+            const uint32_t jc = f.j < n ? f.j : n - 1u;
+            f.x = a.x[jc];
+            f.y = a.y[jc];
+            f.z = a.z[jc];
+            f.h = a.h[jc];
+        };
+        if (ncand == 0) continue;
+        JLoad nx;
+        load(0, nx);
+        for (uint32_t k0 = 0; k0 < ncand; k0 += kPerStep) {
+            const JLoad f = nx;
+            if (k0 + kPerStep < ncand) load(k0 + kPerStep, nx);
+            const bool valid = f.j < n;
+            const float hj2 = f.h * f.h;
+            const uint32_t jr = f.j - i0;  // below kRowGroup: our own particle jr
+            uint32_t full = 0;  // rows with a segment pending
+#pragma unroll
+            for (int r = 0; r < kRowGroup; r++) {
+                float dx = f.x - xi[r];
+                float dy = f.y - yi[r];
+                float dz = f.z - zi[r];
+                if (kPbc) wave_min_image(dx, dy, dz, a.per);
+                const float dxx = dx * dx;
+                const float d2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dxx));
+                const bool in = (int)valid & (int)(d2 < fmaxf(hi2[r], hj2)) & (int)(jr != (uint32_t)r);
+                const uint64_t b = sfc_ballot(in);
+                if (in) s_pend[r][npend[r] + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] = f.j;
+                npend[r] += (uint32_t)sfc_popc(b);
+                full |= npend[r] >= (uint32_t)kWave ? 1u << r : 0u;
+            }
+            if (full) {
                 wave_sync();
-                if ((uint32_t)lane < rest) pend[lane] = tmp;
-                npend = rest;
-                wave_sync();
+                for (uint32_t todo = full; todo; todo &= todo - 1u) {
+                    const uint32_t r = (uint32_t)__builtin_ctz(todo);
+                    flush(r, kWave);
+                    s_pend[r][lane] = s_pend[r][kWave + lane];  // (a lane reads before any writes)
+                    wave_sync();
+                }
+#pragma unroll
+                for (int r = 0; r < kRowGroup; r++) npend[r] -= ((full >> r) & 1u) * (uint32_t)kWave;
             }
         }
-        wave_sync();  // cand is refilled by the next block
     }
-    if (npend) flush(npend);
-    if (lane == 0) {
+    wave_sync();
+#pragma unroll 1
+    for (uint32_t r = 0; r < rows; r++) {
+        uint32_t m = npend[0];
+#pragma unroll
+        for (int k = 1; k < kRowGroup; k++) m = r == (uint32_t)k ? npend[k] : m;
+        if (m) flush(r, m);
+    }
+    if ((uint32_t)lane < rows) {
         if (kWrite) {
-            a.row_info[2 * (size_t)i] = a.row_off[i];
-            a.row_info[2 * (size_t)i + 1] = count;
+            const bool ok = (fits >> lane) & 1u;
+            a.row_info[2 * (size_t)(i0 + lane)] = st_off;
+            a.row_info[2 * (size_t)(i0 + lane) + 1] = ok ? st_count : 0u;  // a row that did not fit is empty, reported
+            if (!ok) atomicOr(&a.status[kStPoolOverflow], 1u);
         } else {
-            a.row_words[i] = words;
+            a.row_words[i0 + lane] = st_words;
         }
     }
 }
@@ -255,9 +328,9 @@ __global__ __launch_bounds__(256) void k_pass_rows(RowPassArgs a) {
 template <int CS, bool kWrite, bool kPbc>
 void launch_rows(bool comp_in, unsigned g, hipStream_t st, const RowArgs &a) {
     if (comp_in)
-        k_rows<CS, true, kWrite, kPbc><<<g, 256, 0, st>>>(a);
+        k_rows<CS, true, kWrite, kPbc><<<g, kWave, 0, st>>>(a);
     else
-        k_rows<CS, false, kWrite, kPbc><<<g, 256, 0, st>>>(a);
+        k_rows<CS, false, kWrite, kPbc><<<g, kWave, 0, st>>>(a);
 }
 
 template <bool kWrite, bool kPbc>
@@ -334,7 +407,7 @@ extern "C" int build_rows(sfcnl_ctx ctx, int64_t n, int cluster_size, int list_c
     RowArgs a{n, d_sc_info, d_pool, d_x, d_y, d_z, d_h, per, compress, ws.row_words, ws.row_off, d_row_info,
               d_row_pool, pool_bytes / 4, ctx->d_status};
     hipStream_t st = ctx->stream;
-    const unsigned g = blocks_for(n, kWavesPerBlock);
+    const unsigned g = blocks_for(n, kRowGroup);
     int rc = fill_u32(ctx, ctx->d_status + kStPoolOverflow, 1, 0u);
     if (rc) return rc;
     if (per.on())
