@@ -369,7 +369,8 @@ __device__ __forceinline__ uint32_t sfc_prev_lane(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xF, 0xF, true);  // wave_shr:1
 }
 
-// f over the wave (f a minimum or maximum of two floats), in every lane: DPP
+// f over the wave (f commutative and associative but for rounding: minimum,
+// maximum, sum), in every lane: DPP
 // inside the rows of 16 lanes, then the rows' and the halves' exchange.
 template <int CTRL>
 __device__ __forceinline__ float sfc_dpp(float v) {

@@ -18,8 +18,12 @@
 // placed the nibbles one LDS atomic at a time: sizing 729 -> 331 us, writing
 // 893 -> 521 us for 500,009 uniform particles of ~240 neighbours.)
 //
-// Pass: one wavefront per particle decodes 64 neighbours per step and
-// evaluates each lane's pair once; no tile of a cluster pair is wasted.
+// Pass: one wavefront per row brings the row's words into LDS with one or two
+// coalesced loads, decodes 64 neighbours per step from there and evaluates each
+// lane's pair once, a step's particles loading while the next one is decoded; no
+// tile of a cluster pair is wasted. (Decoding from memory, every step waited in
+// turn for its bitmask, its info nibbles, its data nibbles and its particles: 517
+// -> 292 us for 500,009 particles; 8 rows per wavefront from one staging: 314.)
 #include "internal.h"
 #include "pass_common.h"
 
@@ -51,7 +55,12 @@ struct RowArgs {
     uint32_t *status;
 };
 
-constexpr int kRowGroup = 8;  // particles per wavefront
+// Rows per wavefront of the build: a wavefront of 8 shares most, but takes as
+// long as its rows need one after another, so small systems, which leave the GPU
+// half empty, take 4 or 1. Build of 8,000 / 32,000 / 128,000 / 500,009 particles
+// in us with 1: 61, 122, 387, 1,427; with 4: 65, 109, 279, 908; with 8: 83, 117,
+// 280, 843.
+constexpr int64_t kRows4Min = 12000, kRows8Min = 128000;
 
 // The nibbles of v from its most significant hex digit on, the first in the low
 // bits (nd digits, v > 0).
@@ -69,30 +78,30 @@ __device__ __forceinline__ void put_nibbles(uint32_t *words, uint32_t t, uint32_
     if ((uint32_t)(b >> 32)) atomicOr(&words[(t >> 3) + 1u], (uint32_t)(b >> 32));
 }
 
-template <int CS, bool kCompIn, bool kWrite, bool kPbc>
+template <int CS, int kRows, bool kCompIn, bool kWrite, bool kPbc>
 __global__ __launch_bounds__(kWave) void k_rows(RowArgs a) {
     constexpr int kPerStep = kWave / CS;  // candidate j-clusters tested per step
     __shared__ uint32_t s_cand[kWave];
-    __shared__ uint32_t s_pend[kRowGroup][2 * kWave];
+    __shared__ uint32_t s_pend[kRows][2 * kWave];
     __shared__ uint32_t s_seg[kSegCap + 1];
     const int lane = sfc_lane();
     const uint64_t lt = sfc_lt_mask();
     const uint32_t n = (uint32_t)a.n;
     const uint32_t grp = xcd_remap(blockIdx.x, gridDim.x);
-    const uint32_t i0 = grp * kRowGroup;
+    const uint32_t i0 = grp * kRows;
     if (i0 >= n) return;
-    const uint32_t rows = n - i0 < (uint32_t)kRowGroup ? n - i0 : (uint32_t)kRowGroup;
-    const uint32_t s = i0 / kScSize, g = (i0 % kScSize) / kRowGroup;
+    const uint32_t rows = n - i0 < (uint32_t)kRows ? n - i0 : (uint32_t)kRows;
+    const uint32_t s = i0 / kScSize, g = (i0 % kScSize) / 8u;
     // entries with a mask bit of one of our i-clusters
     const uint32_t pick = CS == 4 ? 3u << (2 * g) : (CS == 8 ? 1u << g : 1u << (g >> 1));
     // the rows' particles, wave-uniform (rows past the end: the last particle
     // again, whose pairs are dropped)
-    float xi[kRowGroup], yi[kRowGroup], zi[kRowGroup], hi2[kRowGroup];
+    float xi[kRows], yi[kRows], zi[kRows], hi2[kRows];
     {
         const uint32_t p = i0 + ((uint32_t)lane < rows ? (uint32_t)lane : rows - 1u);
         const float px = a.x[p], py = a.y[p], pz = a.z[p], ph = a.h[p];
 #pragma unroll
-        for (int r = 0; r < kRowGroup; r++) {
+        for (int r = 0; r < kRows; r++) {
             xi[r] = sfc_readlane_f(px, r);
             yi[r] = sfc_readlane_f(py, r);
             zi[r] = sfc_readlane_f(pz, r);
@@ -169,9 +178,9 @@ __global__ __launch_bounds__(kWave) void k_rows(RowArgs a) {
         st_count += mine ? m : 0u;
     };
 
-    uint32_t npend[kRowGroup];
+    uint32_t npend[kRows];
 #pragma unroll
-    for (int r = 0; r < kRowGroup; r++) npend[r] = 0;
+    for (int r = 0; r < kRows; r++) npend[r] = 0;
     uint32_t prevj = 0xFFFFFFFFu;  // decoding state of the cluster list
     for (uint32_t b0 = 0; b0 < nj; b0 += kWave) {
         const uint32_t cntb = nj - b0 < (uint32_t)kWave ? nj - b0 : (uint32_t)kWave;
@@ -213,10 +222,10 @@ __global__ __launch_bounds__(kWave) void k_rows(RowArgs a) {
             if (k0 + kPerStep < ncand) load(k0 + kPerStep, nx);
             const bool valid = f.j < n;
             const float hj2 = f.h * f.h;
-            const uint32_t jr = f.j - i0;  // below kRowGroup: our own particle jr
+            const uint32_t jr = f.j - i0;  // below kRows: our own particle jr
             uint32_t full = 0;  // rows with a segment pending
 #pragma unroll
-            for (int r = 0; r < kRowGroup; r++) {
+            for (int r = 0; r < kRows; r++) {
                 float dx = f.x - xi[r];
                 float dy = f.y - yi[r];
                 float dz = f.z - zi[r];
@@ -238,7 +247,7 @@ __global__ __launch_bounds__(kWave) void k_rows(RowArgs a) {
                     wave_sync();
                 }
 #pragma unroll
-                for (int r = 0; r < kRowGroup; r++) npend[r] -= ((full >> r) & 1u) * (uint32_t)kWave;
+                for (int r = 0; r < kRows; r++) npend[r] -= ((full >> r) & 1u) * (uint32_t)kWave;
             }
         }
     }
@@ -247,7 +256,7 @@ __global__ __launch_bounds__(kWave) void k_rows(RowArgs a) {
     for (uint32_t r = 0; r < rows; r++) {
         uint32_t m = npend[0];
 #pragma unroll
-        for (int k = 1; k < kRowGroup; k++) m = r == (uint32_t)k ? npend[k] : m;
+        for (int k = 1; k < kRows; k++) m = r == (uint32_t)k ? npend[k] : m;
         if (m) flush(r, m);
     }
     if ((uint32_t)lane < rows) {
@@ -271,53 +280,106 @@ struct RowPassArgs {
     int32_t *nnb;
 };
 
+constexpr int kStageWords = 256;  // words of a row in LDS (longer rows are read from memory)
+
+// As decode_segment, from the words at w[p..] (LDS or memory); the last word
+// read is the segment's last.
+template <typename W>
+__device__ __forceinline__ uint32_t decode_row_segment(W w, uint32_t &p, uint32_t cnt, uint32_t prevj) {
+    const int lane = sfc_lane();
+    const uint64_t m = ((uint64_t)w[p + 1] << 32) | w[p];
+    const bool valid = (uint32_t)lane < cnt;
+    const bool nonone = valid && ((m >> lane) & 1ull);
+    const uint32_t ninfo = (uint32_t)sfc_popc(m);
+    uint32_t v = 1u, nd = 0u;
+    if (nonone) {
+        const uint32_t t = (uint32_t)sfc_popc(m & sfc_lt_mask());
+        const uint32_t inf = (w[p + 2 + (t >> 3)] >> (4u * (t & 7u))) & 0xFu;
+        if (inf >= 8u)
+            v = inf - 6u;
+        else
+            nd = inf + 1u;
+    }
+    const uint32_t incl = sfc_incl_scan(nd);
+    if (nd) {  // its digits, the first in the low bits
+        const uint32_t t = ninfo + incl - nd, sh = 4u * (t & 7u);
+        uint64_t b = w[p + 2 + (t >> 3)];
+        if ((t & 7u) + nd > 8u) b |= (uint64_t)w[p + 3 + (t >> 3)] << 32;
+        v = digits_first((uint32_t)(b >> sh), 8u) >> (4u * (8u - nd));
+    }
+    const uint32_t total_nib = ninfo + sfc_readlane(incl, kWave - 1);
+    p += 2u + (total_nib + 7u) / 8u;
+    return prevj + sfc_incl_scan(valid ? v : 0u);
+}
+
 // Density and counts from the rows: the own-radius subset of each row.
 template <bool kCompress, bool kMass, bool kCount, bool kPbc>
-__global__ __launch_bounds__(256) void k_pass_rows(RowPassArgs a) {
+__global__ __launch_bounds__(kWave) void k_pass_rows(RowPassArgs a) {
+    __shared__ uint32_t s_words[kCompress ? kStageWords : 1];
     const int lane = sfc_lane();
-    const int w = threadIdx.x / kWave;
-    const uint32_t i =
-        (uint32_t)__builtin_amdgcn_readfirstlane((int)(xcd_remap(blockIdx.x, gridDim.x) * kWavesPerBlock + w));
-    if (i >= a.n) return;
+    const uint32_t n = (uint32_t)a.n;
+    const uint32_t i = xcd_remap(blockIdx.x, gridDim.x);
+    if (i >= n) return;
+    const uint32_t off = a.row_info[2 * (size_t)i], cnt = a.row_info[2 * (size_t)i + 1];
     const float xi = a.x[i], yi = a.y[i], zi = a.z[i], hi = a.h[i];
     const float hi2 = hi * hi;
     const float hinv = 1.0f / hi;
-    const uint32_t off = a.row_info[2 * (size_t)i], cnt = a.row_info[2 * (size_t)i + 1];
-    uint32_t p = off;
+    bool staged = false;
+    if (kCompress && i + 1 < n) {  // the next row begins where this one ends
+        const uint32_t len = a.row_info[2 * (size_t)i + 2] - off;
+        staged = len <= (uint32_t)kStageWords;
+        if (staged) {
+            for (uint32_t q = (uint32_t)lane; q < len; q += kWave) s_words[q] = a.pool[off + q];
+            wave_sync();
+        }
+    }
+    uint32_t p = staged ? 0u : off;
     uint32_t prevj = 0xFFFFFFFFu;
     float acc = 0.0f;
     uint32_t nb = 0;
-    for (uint32_t b0 = 0; b0 < cnt; b0 += kWave) {
+    struct Step {
+        float x, y, z, m;
+    };
+    // decodes neighbours b0 .. and loads their particles (lanes past the end:
+    // the row's own particle)
+    auto next = [&](uint32_t b0, Step &f) __attribute__((always_inline)) {
         const uint32_t c = cnt - b0 < (uint32_t)kWave ? cnt - b0 : (uint32_t)kWave;
         uint32_t jv;
-        if (kCompress)
-            jv = decode_segment(a.pool, p, c, prevj);
-        else
+        if (!kCompress) {
             jv = (uint32_t)lane < c ? a.pool[off + b0 + lane] : 0u;
-        prevj = sfc_readlane(jv, (int)c - 1);
-        const bool valid = (uint32_t)lane < c;
-        float dx = valid ? a.x[jv] - xi : 0.0f;
-        float dy = valid ? a.y[jv] - yi : 0.0f;
-        float dz = valid ? a.z[jv] - zi : 0.0f;
+        } else {
+            jv = staged ? decode_row_segment((const uint32_t *)s_words, p, c, prevj)
+                        : decode_row_segment(a.pool, p, c, prevj);
+            prevj = sfc_readlane(jv, (int)c - 1);
+        }
+        const uint32_t jc = (uint32_t)lane < c ? jv : i;
+        f.x = a.x[jc];
+        f.y = a.y[jc];
+        f.z = a.z[jc];
+        f.m = kMass ? a.m[jc] : 1.0f;
+    };
+    Step nx;
+    if (cnt) next(0, nx);
+    for (uint32_t b0 = 0; b0 < cnt; b0 += kWave) {
+        const Step f = nx;
+        if (b0 + kWave < cnt) next(b0 + kWave, nx);
+        float dx = f.x - xi;
+        float dy = f.y - yi;
+        float dz = f.z - zi;
         if (kPbc) wave_min_image(dx, dy, dz, a.per);
         const float dxx = dx * dx;
         const float d2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dxx));
-        const bool in = valid && d2 < hi2;
-        const uint64_t bal = sfc_ballot(in);
-        if (bal) {
-            nb += (uint32_t)sfc_popc(bal);
-            const float q = __builtin_amdgcn_sqrtf(d2) * hinv;
-            const float t1 = q - 1.0f;
-            const float q2 = q * q;
-            const float inner = __builtin_fmaf(3.0f * q2, t1, 0.5f);
-            const float outer = -(t1 * t1) * t1;
-            const float wq = q < 0.5f ? inner : outer;
-            const float mj = kMass ? (in ? a.m[jv] : 0.0f) : 1.0f;
-            acc = in ? __builtin_fmaf(mj, wq, acc) : acc;
-        }
+        const bool in = (int)(b0 + (uint32_t)lane < cnt) & (int)(d2 < hi2);
+        nb += (uint32_t)sfc_popc(sfc_ballot(in));
+        const float q = __builtin_amdgcn_sqrtf(d2) * hinv;
+        const float t1 = q - 1.0f;
+        const float q2 = q * q;
+        const float inner = __builtin_fmaf(3.0f * q2, t1, 0.5f);
+        const float outer = -(t1 * t1) * t1;
+        const float wq = q < 0.5f ? inner : outer;
+        acc = in ? __builtin_fmaf(kMass ? f.m : 1.0f, wq, acc) : acc;
     }
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) acc += __shfl_xor(acc, d, 64);
+    acc = sfc_wave_reduce(acc, [](float u, float v) { return u + v; });
     if (lane == 0) {
         const float norm = 2.5464790894703255f * hinv * hinv * hinv;  // 8 / pi
         a.rho[i] = norm * __builtin_fmaf(2.0f, acc, kMass ? a.m[i] : 1.0f);
@@ -325,35 +387,51 @@ __global__ __launch_bounds__(256) void k_pass_rows(RowPassArgs a) {
     }
 }
 
-template <int CS, bool kWrite, bool kPbc>
-void launch_rows(bool comp_in, unsigned g, hipStream_t st, const RowArgs &a) {
+template <int CS, int kRows, bool kWrite, bool kPbc>
+void launch_rows(bool comp_in, hipStream_t st, const RowArgs &a) {
+    const unsigned g = blocks_for(a.n, kRows);
     if (comp_in)
-        k_rows<CS, true, kWrite, kPbc><<<g, kWave, 0, st>>>(a);
+        k_rows<CS, kRows, true, kWrite, kPbc><<<g, kWave, 0, st>>>(a);
     else
-        k_rows<CS, false, kWrite, kPbc><<<g, kWave, 0, st>>>(a);
+        k_rows<CS, kRows, false, kWrite, kPbc><<<g, kWave, 0, st>>>(a);
 }
 
-template <bool kWrite, bool kPbc>
-void launch_rows_cs(int cs, bool comp_in, unsigned g, hipStream_t st, const RowArgs &a) {
+template <int kRows, bool kWrite, bool kPbc>
+void launch_rows_cs(int cs, bool comp_in, hipStream_t st, const RowArgs &a) {
     if (cs == 4)
-        launch_rows<4, kWrite, kPbc>(comp_in, g, st, a);
+        launch_rows<4, kRows, kWrite, kPbc>(comp_in, st, a);
     else if (cs == 16)
-        launch_rows<16, kWrite, kPbc>(comp_in, g, st, a);
+        launch_rows<16, kRows, kWrite, kPbc>(comp_in, st, a);
     else
-        launch_rows<8, kWrite, kPbc>(comp_in, g, st, a);
+        launch_rows<8, kRows, kWrite, kPbc>(comp_in, st, a);
+}
+
+template <bool kWrite>
+void launch_rows_any(int cs, bool comp_in, hipStream_t st, const RowArgs &a) {
+    const bool pbc = a.per.on();
+    if (a.n >= kRows8Min) {
+        if (pbc) launch_rows_cs<8, kWrite, true>(cs, comp_in, st, a);
+        else launch_rows_cs<8, kWrite, false>(cs, comp_in, st, a);
+    } else if (a.n >= kRows4Min) {
+        if (pbc) launch_rows_cs<4, kWrite, true>(cs, comp_in, st, a);
+        else launch_rows_cs<4, kWrite, false>(cs, comp_in, st, a);
+    } else {
+        if (pbc) launch_rows_cs<1, kWrite, true>(cs, comp_in, st, a);
+        else launch_rows_cs<1, kWrite, false>(cs, comp_in, st, a);
+    }
 }
 
 template <bool kPbc>
 void launch_pass_rows(int variant, unsigned g, hipStream_t st, const RowPassArgs &a) {
     switch (variant) {
-        case 7: k_pass_rows<true, true, true, kPbc><<<g, 256, 0, st>>>(a); break;
-        case 6: k_pass_rows<true, true, false, kPbc><<<g, 256, 0, st>>>(a); break;
-        case 5: k_pass_rows<true, false, true, kPbc><<<g, 256, 0, st>>>(a); break;
-        case 4: k_pass_rows<true, false, false, kPbc><<<g, 256, 0, st>>>(a); break;
-        case 3: k_pass_rows<false, true, true, kPbc><<<g, 256, 0, st>>>(a); break;
-        case 2: k_pass_rows<false, true, false, kPbc><<<g, 256, 0, st>>>(a); break;
-        case 1: k_pass_rows<false, false, true, kPbc><<<g, 256, 0, st>>>(a); break;
-        default: k_pass_rows<false, false, false, kPbc><<<g, 256, 0, st>>>(a); break;
+        case 7: k_pass_rows<true, true, true, kPbc><<<g, kWave, 0, st>>>(a); break;
+        case 6: k_pass_rows<true, true, false, kPbc><<<g, kWave, 0, st>>>(a); break;
+        case 5: k_pass_rows<true, false, true, kPbc><<<g, kWave, 0, st>>>(a); break;
+        case 4: k_pass_rows<true, false, false, kPbc><<<g, kWave, 0, st>>>(a); break;
+        case 3: k_pass_rows<false, true, true, kPbc><<<g, kWave, 0, st>>>(a); break;
+        case 2: k_pass_rows<false, true, false, kPbc><<<g, kWave, 0, st>>>(a); break;
+        case 1: k_pass_rows<false, false, true, kPbc><<<g, kWave, 0, st>>>(a); break;
+        default: k_pass_rows<false, false, false, kPbc><<<g, kWave, 0, st>>>(a); break;
     }
 }
 
@@ -407,20 +485,13 @@ extern "C" int build_rows(sfcnl_ctx ctx, int64_t n, int cluster_size, int list_c
     RowArgs a{n, d_sc_info, d_pool, d_x, d_y, d_z, d_h, per, compress, ws.row_words, ws.row_off, d_row_info,
               d_row_pool, pool_bytes / 4, ctx->d_status};
     hipStream_t st = ctx->stream;
-    const unsigned g = blocks_for(n, kRowGroup);
     int rc = fill_u32(ctx, ctx->d_status + kStPoolOverflow, 1, 0u);
     if (rc) return rc;
-    if (per.on())
-        launch_rows_cs<false, true>(cluster_size, list_compress, g, st, a);
-    else
-        launch_rows_cs<false, false>(cluster_size, list_compress, g, st, a);
+    launch_rows_any<false>(cluster_size, list_compress, st, a);
     SFCNL_LAUNCHED(ctx);
     rc = scan_u32(ctx, ws.row_words, ws.row_off, n, ws.row_off + n, ws.scan_tmp);
     if (rc) return rc;
-    if (per.on())
-        launch_rows_cs<true, true>(cluster_size, list_compress, g, st, a);
-    else
-        launch_rows_cs<true, false>(cluster_size, list_compress, g, st, a);
+    launch_rows_any<true>(cluster_size, list_compress, st, a);
     SFCNL_LAUNCHED(ctx);
     k_rows_total<<<1, 1, 0, st>>>(ws.row_off + n, ctx->d_status);
     SFCNL_LAUNCHED(ctx);
@@ -444,8 +515,8 @@ extern "C" int rows_pass(sfcnl_ctx ctx, int64_t n, int compress, const uint32_t 
         return set_err(ctx, SFCNL_E_ARG, "rows_pass: null pointer");
     RowPassArgs a{n, d_row_info, d_row_pool, d_x, d_y, d_z, d_h, d_m, make_period(h_period), d_rho, d_nnb};
     const int variant = (compress ? 4 : 0) | (d_m ? 2 : 0) | (d_nnb ? 1 : 0);
-    const unsigned g = blocks_for(n, kWavesPerBlock);
     prof_mark(ctx, kStagePass, false);
+    const unsigned g = blocks_for(n, 1);
     if (a.per.on())
         launch_pass_rows<true>(variant, g, ctx->stream, a);
     else
