@@ -30,8 +30,11 @@ using namespace passk;
 
 constexpr float kAway = 1.0e38f;
 
-// One wavefront (one super-cluster) per block, as for the density passes.
-constexpr int kLjWaves = 1;
+// A block is one super-cluster: one wavefront, or several that share its list
+// (pass_split). LDS per wavefront at cluster size 8: the j-particles of a
+// batch (x, y, z, charge), and in the half pass their sums and hit flags.
+constexpr int kLjLds = kWave * 16;
+constexpr int kLjLdsHalf = kWave * (16 + 16 + 4);
 
 struct LjArgs {
     int64_t n;
@@ -45,6 +48,7 @@ struct LjArgs {
     float kc;     // Coulomb prefactor
     float *fx, *fy, *fz, *ep;
     Period per;   // periodic axes (used by the kPbc kernels)
+    uint32_t split;  // wavefronts per super-cluster
 };
 
 // orders a wave's LDS accesses around it (the wave runs in lockstep)
@@ -104,17 +108,23 @@ __device__ __forceinline__ void lj_tile(float xj, float yj, float zj, float qj, 
 // faster); cluster size 16 spills heavily under that cap and keeps its own
 // register count.
 template <int CS, bool kCompress, bool kQ, bool kE, bool kPbc>
-__global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_eu(CS == 16 ? 1 : 6))) void k_pass_lj(LjArgs a) {
+__global__ __launch_bounds__(kWave * kPassSplitMax) __attribute__((amdgpu_waves_per_eu(CS == 16 ? 1 : 6))) void k_pass_lj(LjArgs a) {
     constexpr int kNsub = kScSize / CS;
     constexpr int kNreg = CS == 8 ? 8 : 4;
     constexpr int kNj = CS == 16 ? 4 : 1;
     constexpr int kGroup = CS == 8 ? 8 : 4;
     const int lane = sfc_lane();
-    const int w = threadIdx.x / kWave;
-    const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)(xcd_remap(blockIdx.x, gridDim.x) * kLjWaves + w));
+    const uint32_t part = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const uint32_t s = (uint32_t)xcd_remap(blockIdx.x, gridDim.x);
     if (s >= a.nsc) return;
     const int64_t n = a.n;
     const int jl = lane & (kGroup - 1);
+    // the i-registers of this part, and their mask bits in an entry
+    uint32_t regs = 0, mine = 0;
+    for (uint32_t k = part; k < (uint32_t)kNreg; k += a.split) {
+        regs |= 1u << k;
+        mine |= (CS == 4 ? 0xFu << (4 * k) : 1u << k);
+    }
 
     float ix[kNreg], iy[kNreg], iz[kNreg], ikq[kNreg];
 #pragma unroll
@@ -155,7 +165,8 @@ __global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_e
     auto batch_wraps = [&](float4 jp, bool used) __attribute__((always_inline)) {
         return sfc_ballot(used && far_from_box(jp, ib, a.per)) != 0;
     };
-    __shared__ float4 s_jb[kLjWaves][CS == 8 ? kWave : 1];  // x, y, z, charge
+    extern __shared__ float4 s_lj[];
+    float4 *s_jb = s_lj + (size_t)part * kWave;  // x, y, z, charge
     auto entries8 = [&](uint32_t mvl, uint32_t jvl, uint32_t cnt) __attribute__((always_inline)) {
         const int il = lane >> 3;
         for (uint32_t q0 = 0; q0 < cnt; q0 += 8) {
@@ -169,14 +180,14 @@ __global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_e
             const float bq = kQ ? a.q[pc] : 0.0f;
             lj_wave_sync();  // the previous batch's reads are done
             const float4 jv4 = make_float4(pv ? bx : -kAway, pv ? by : -kAway, pv ? bz : -kAway, pv ? bq : 0.0f);
-            s_jb[w][lane] = jv4;
+            s_jb[lane] = jv4;
             lj_wave_sync();
             const uint32_t bn = cnt - q0 < 8u ? cnt - q0 : 8u;
             const bool wrap = kPbc && batch_wraps(jv4, (uint32_t)(lane >> 3) < bn);
             for (uint32_t q = 0; q < bn; q++) {
                 const uint32_t mk = sfc_readlane(mvl, (int)(q0 + q));
                 const uint32_t cj = sfc_readlane(jvl, (int)(q0 + q));
-                const float4 jb = s_jb[w][q * 8 + jl];
+                const float4 jb = s_jb[q * 8 + jl];
                 const int self_c = (cj >= own_c0 && cj < own_c0 + kNsub) ? (int)(cj - own_c0) : -1;
 #pragma unroll
                 for (int c = 0; c < kNreg; c++)
@@ -187,7 +198,7 @@ __global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_e
         }
     };
     for (uint32_t b0 = 0; b0 < nj; b0 += kWave) {
-        const uint32_t cnt = nj - b0 < (uint32_t)kWave ? nj - b0 : (uint32_t)kWave;
+        uint32_t cnt = nj - b0 < (uint32_t)kWave ? nj - b0 : (uint32_t)kWave;
         uint32_t jv;
         if (kCompress)
             jv = decode_segment(a.pool, p, cnt, prevj);
@@ -196,6 +207,18 @@ __global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_e
         uint32_t mv = 0u;
         if ((uint32_t)lane < cnt) mv = CS == 4 ? (uint32_t)mshorts[b0 + lane] : (uint32_t)mbytes[b0 + lane];
         prevj = sfc_readlane(jv, (int)cnt - 1);
+        if (a.split > 1) {
+            // the entries with a tile of this part move up, in their order
+            mv &= mine;
+            const uint64_t has = sfc_ballot(mv != 0u);
+            if (has == 0) continue;
+            const int rest = __builtin_popcountll(has);
+            const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u));
+            const int to = (mv != 0u ? below : rest + lane - below) << 2;  // a permutation of the lanes
+            mv = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)mv);
+            jv = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)jv);
+            cnt = (uint32_t)rest;
+        }
         if constexpr (CS == 8) {
             entries8(mv, jv, cnt);
             continue;
@@ -251,13 +274,10 @@ __global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_e
     // the lane with j slot k then stores register k
 #pragma unroll
     for (int k = 0; k < kNreg; k++) {
-#pragma unroll
-        for (int d = 1; d < kGroup; d <<= 1) {
-            gx[k] += __shfl_xor(gx[k], d, 64);
-            gy[k] += __shfl_xor(gy[k], d, 64);
-            gz[k] += __shfl_xor(gz[k], d, 64);
-            if (kE) ge[k] += __shfl_xor(ge[k], d, 64);
-        }
+        group_sum<kGroup>(gx[k]);
+        group_sum<kGroup>(gy[k]);
+        group_sum<kGroup>(gz[k]);
+        if (kE) group_sum<kGroup>(ge[k]);
     }
     float rx = gx[0], ry = gy[0], rz = gz[0], re = ge[0];
 #pragma unroll
@@ -268,7 +288,7 @@ __global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_e
         re = jl == k ? ge[k] : re;
     }
     const int64_t io = (int64_t)s * kScSize + ipart<CS>(jl, lane);
-    if (io < n) {
+    if (io < n && ((regs >> jl) & 1u)) {
         a.fx[io] = -rx;
         a.fy[io] = -ry;
         a.fz[io] = -rz;
@@ -279,14 +299,14 @@ __global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_e
 // The batched entries of cluster size 8 need more registers: five waves per
 // SIMD without spills run faster than six with them.
 template <int CS, bool kCompress, bool kQ, bool kE, bool kPbc>
-__global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_eu(CS == 16 ? 1 : (CS == 8 ? 5 : 6)))) void k_pass_lj_half(LjArgs a) {
+__global__ __launch_bounds__(kWave * kPassSplitMax) __attribute__((amdgpu_waves_per_eu(CS == 16 ? 1 : (CS == 8 ? 5 : 6)))) void k_pass_lj_half(LjArgs a) {
     constexpr int kNsub = kScSize / CS;
     constexpr int kNreg = CS == 8 ? 8 : 4;
     constexpr int kNj = CS == 16 ? 4 : 1;
     constexpr int kIL = CS == 8 ? 8 : 16;  // lanes per j-particle (the i side, low bits)
     const int lane = sfc_lane();
-    const int w = threadIdx.x / kWave;
-    const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)(xcd_remap(blockIdx.x, gridDim.x) * kLjWaves + w));
+    const uint32_t part = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const uint32_t s = (uint32_t)xcd_remap(blockIdx.x, gridDim.x);
     if (s >= a.nsc) return;
     const int64_t n = a.n;
     const int jq = CS == 8 ? lane >> 3 : lane >> 4;
@@ -320,12 +340,16 @@ __global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_e
     auto batch_wraps = [&](float4 jp, bool used) __attribute__((always_inline)) {
         return sfc_ballot(used && far_from_box(jp, ib, a.per)) != 0;
     };
-    __shared__ float4 s_jb[kLjWaves][CS == 8 ? kWave : 1];  // x, y, z, charge
-    __shared__ float4 s_jh[kLjWaves][CS == 8 ? kWave : 1];  // j-side force (and energy) sums
-    __shared__ uint32_t s_jhit[kLjWaves][CS == 8 ? kWave : 1];
-    auto entries8 = [&](uint32_t mvl, uint32_t jvl, uint32_t cnt) __attribute__((always_inline)) {
+    extern __shared__ float4 s_lj[];
+    float4 *s_jb = s_lj + (size_t)part * (kLjLdsHalf / 16);  // x, y, z, charge
+    float4 *s_jh = s_jb + kWave;                             // j-side force (and energy) sums
+    uint32_t *s_jhit = reinterpret_cast<uint32_t *>(s_jh + kWave);
+    // (a part of a split super-cluster takes every split-th batch of a segment,
+    // the segment's number shifting the deal)
+    auto entries8 = [&](uint32_t mvl, uint32_t jvl, uint32_t cnt, uint32_t b0) __attribute__((always_inline)) {
         const int il = lane & 7;
-        for (uint32_t q0 = 0; q0 < cnt; q0 += 8) {
+        const uint32_t first = a.split > 1 ? 8u * ((part + b0 / kWave) % a.split) : 0u;
+        for (uint32_t q0 = first; q0 < cnt; q0 += 8u * a.split) {
             const uint32_t e = q0 + (uint32_t)(lane >> 3);
             bool ev = e < cnt;
             const uint32_t cjb = (uint32_t)__shfl((int)jvl, (int)(ev ? e : q0), kWave);
@@ -335,14 +359,14 @@ __global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_e
             const float bx = a.x[pc], by = a.y[pc], bz = a.z[pc];
             const float bq = kQ ? a.q[pc] : 0.0f;
             const float4 jv4 = make_float4(ev ? bx : -kAway, ev ? by : -kAway, ev ? bz : -kAway, ev ? bq : 0.0f);
-            s_jb[w][lane] = jv4;
+            s_jb[lane] = jv4;
             lj_wave_sync();
             const uint32_t bn = cnt - q0 < 8u ? cnt - q0 : 8u;
             const bool wrap = kPbc && batch_wraps(jv4, (uint32_t)(lane >> 3) < bn);
             for (uint32_t q = 0; q < bn; q++) {
                 const uint32_t mk = sfc_readlane(mvl, (int)(q0 + q));
                 const uint32_t cj = sfc_readlane(jvl, (int)(q0 + q));
-                const float4 jb = s_jb[w][q * 8 + jq];
+                const float4 jb = s_jb[q * 8 + jq];
                 float hx = 0.0f, hy = 0.0f, hz = 0.0f, he = 0.0f;
                 uint64_t jm = 0;  // lanes that formed a pair
                 // inside the super-cluster only j > i counts
@@ -385,14 +409,14 @@ __global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_e
                     if (kE) group_sum<kIL>(he);
                 }
                 if (il == 0) {
-                    s_jh[w][q * 8 + jq] = make_float4(hx, hy, hz, he);
-                    s_jhit[w][q * 8 + jq] = ((jm >> (8 * jq)) & 0xFFull) != 0 ? 1u : 0u;
+                    s_jh[q * 8 + jq] = make_float4(hx, hy, hz, he);
+                    s_jhit[q * 8 + jq] = ((jm >> (8 * jq)) & 0xFFull) != 0 ? 1u : 0u;
                 }
             }
             lj_wave_sync();
             // lane (q, r): j-particle r of entry q
-            if (ev && (uint32_t)(lane >> 3) < bn && s_jhit[w][lane]) {
-                const float4 hv = s_jh[w][lane];
+            if (ev && (uint32_t)(lane >> 3) < bn && s_jhit[lane]) {
+                const float4 hv = s_jh[lane];
                 atomicAdd(&a.fx[pq], hv.x);
                 atomicAdd(&a.fy[pq], hv.y);
                 atomicAdd(&a.fz[pq], hv.z);
@@ -415,7 +439,7 @@ __global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_e
         if ((uint32_t)lane < cnt) mv = CS == 4 ? (uint32_t)mshorts[b0 + lane] : (uint32_t)mbytes[b0 + lane];
         prevj = sfc_readlane(jv, (int)cnt - 1);
         if constexpr (CS == 8) {
-            entries8(mv, jv, cnt);
+            entries8(mv, jv, cnt, b0);
             continue;
         }
         float nx[kNj], ny[kNj], nz[kNj], nq[kNj];
@@ -430,8 +454,9 @@ __global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_e
                 nq[t] = kQ ? (vj ? a.q[jp] : 0.0f) : 0.0f;
             }
         };
-        load_j(sfc_readlane(jv, 0));
-        for (uint32_t e = 0; e < cnt; e++) {
+        if (part >= cnt) continue;
+        load_j(sfc_readlane(jv, (int)part));
+        for (uint32_t e = part; e < cnt; e += a.split) {
             const uint32_t mk = sfc_readlane(mv, (int)e);
             const uint32_t cj = sfc_readlane(jv, (int)e);
             float xj[kNj], yj[kNj], zj[kNj], qj[kNj], hx[kNj], hy[kNj], hz[kNj], he[kNj];
@@ -445,7 +470,7 @@ __global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_e
                 qj[t] = nq[t];
                 hx[t] = hy[t] = hz[t] = he[t] = 0.0f;
             }
-            if (e + 1 < cnt) load_j(sfc_readlane(jv, (int)e + 1));
+            if (e + a.split < cnt) load_j(sfc_readlane(jv, (int)(e + a.split)));
             // inside the super-cluster only j > i counts
             const int self_c = (cj >= own_c0 && cj < own_c0 + kNsub) ? (int)(cj - own_c0) : -1;
             auto keep = [&](int ci, int ipos, int jpos) {
@@ -556,9 +581,10 @@ __global__ __launch_bounds__(kWave * kLjWaves) __attribute__((amdgpu_waves_per_e
 }
 
 template <int CS, bool kHalf, bool kPbc>
-void launch_lj(int variant, unsigned g, hipStream_t st, const LjArgs &a) {
+void launch_lj(int variant, hipStream_t st, const LjArgs &a) {
+    const size_t lds = CS == 8 ? (size_t)a.split * (kHalf ? kLjLdsHalf : kLjLds) : 0;
 #define SFCNL_LJ(C, Q, E) \
-    (kHalf ? k_pass_lj_half<CS, C, Q, E, kPbc> : k_pass_lj<CS, C, Q, E, kPbc>)<<<g, kWave * kLjWaves, 0, st>>>(a)
+    (kHalf ? k_pass_lj_half<CS, C, Q, E, kPbc> : k_pass_lj<CS, C, Q, E, kPbc>)<<<a.nsc, kWave * a.split, lds, st>>>(a)
     switch (variant) {
         case 7: SFCNL_LJ(true, true, true); break;
         case 6: SFCNL_LJ(true, true, false); break;
@@ -573,20 +599,20 @@ void launch_lj(int variant, unsigned g, hipStream_t st, const LjArgs &a) {
 }
 
 template <bool kPbc>
-void launch_lj_any(int cs, int half, int variant, unsigned g, hipStream_t st, const LjArgs &a) {
+void launch_lj_any(int cs, int half, int variant, hipStream_t st, const LjArgs &a) {
     if (half) {
         if (cs == 4)
-            launch_lj<4, true, kPbc>(variant, g, st, a);
+            launch_lj<4, true, kPbc>(variant, st, a);
         else if (cs == 16)
-            launch_lj<16, true, kPbc>(variant, g, st, a);
+            launch_lj<16, true, kPbc>(variant, st, a);
         else
-            launch_lj<8, true, kPbc>(variant, g, st, a);
+            launch_lj<8, true, kPbc>(variant, st, a);
     } else if (cs == 4) {
-        launch_lj<4, false, kPbc>(variant, g, st, a);
+        launch_lj<4, false, kPbc>(variant, st, a);
     } else if (cs == 16) {
-        launch_lj<16, false, kPbc>(variant, g, st, a);
+        launch_lj<16, false, kPbc>(variant, st, a);
     } else {
-        launch_lj<8, false, kPbc>(variant, g, st, a);
+        launch_lj<8, false, kPbc>(variant, st, a);
     }
 }
 
@@ -616,8 +642,8 @@ extern "C" int nlist_pass_lj(sfcnl_ctx ctx, int64_t n, int cluster_size, int com
         return set_err(ctx, SFCNL_E_ARG, "nlist_pass_lj: null pointer");
     LjArgs a{n, (uint32_t)((n + kScSize - 1) / kScSize), d_sc_info, d_pool, d_x, d_y, d_z, d_q,
              pr.r_cut * pr.r_cut, pr.sigma * pr.sigma, 24.0f * pr.eps, 4.0f * pr.eps, pr.coulomb,
-             d_fx, d_fy, d_fz, d_epot, make_period(h_period)};
-    const unsigned g = blocks_for(a.nsc, kLjWaves);
+             d_fx, d_fy, d_fz, d_epot, make_period(h_period), 1u};
+    a.split = pass_split(cluster_size, half != 0, a.nsc);
     hipStream_t st = ctx->stream;
     const int variant = (compress ? 4 : 0) | (d_q ? 2 : 0) | (d_epot ? 1 : 0);
     prof_mark(ctx, kStagePass, false);
@@ -629,9 +655,9 @@ extern "C" int nlist_pass_lj(sfcnl_ctx ctx, int64_t n, int cluster_size, int com
         if (rc) return rc;
     }
     if (a.per.on())
-        launch_lj_any<true>(cluster_size, half, variant, g, st, a);
+        launch_lj_any<true>(cluster_size, half, variant, st, a);
     else
-        launch_lj_any<false>(cluster_size, half, variant, g, st, a);
+        launch_lj_any<false>(cluster_size, half, variant, st, a);
     SFCNL_LAUNCHED(ctx);
     prof_mark(ctx, kStagePass, true);
     return SFCNL_OK;

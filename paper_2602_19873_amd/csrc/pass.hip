@@ -22,8 +22,9 @@ using namespace passk;
 // knob of the context (sfcnl_set_pass_waves, 1, 2 or 4). One wave per block
 // lets a block release its slots as soon as its one list is done (7 % faster
 // than four for the half-list pass on the uniform benchmark); the batch
-// autotuner times all three.
-constexpr int kPassWavesMax = 4;
+// autotuner times all three. Small systems split their super-clusters over up
+// to 8 waves instead (pass_split).
+constexpr int kPassWavesMax = kPassSplitMax;
 // LDS per wave of the cluster-size-8 symmetric pass: a batch's 64
 // j-particles (x, y, z, h^2), their 1/h and masses, and every tile lane's
 // j-side partial sum and count for each of the batch's 8 entries
@@ -48,6 +49,7 @@ struct PassArgs {
     const uint8_t *p_active;  // nullable: write only particles with p_active[i] != 0 (full pass)
     const uint32_t *gate;     // nullable: nothing to do when *gate <= gate_max
     uint32_t gate_max;
+    uint32_t split;           // wavefronts that share a super-cluster (a block is then one super-cluster)
 };
 
 // A quarter of the halved M4 shape as two clamped cubes: with
@@ -112,11 +114,18 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
     constexpr int kNj = CS == 16 ? 4 : 1;     // j-particles per lane and entry
     constexpr int kGroup = CS == 8 ? 8 : 4;   // lanes sharing an i-particle
     const int lane = sfc_lane();
-    const int w = threadIdx.x / kWave;
     // wave-uniform: keep the super-cluster index (and all derived from it) scalar
-    const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)(xcd_remap(blockIdx.x, gridDim.x) * (blockDim.x / kWave) + w));
+    uint32_t part;
+    const uint32_t s = wave_sc(a.split, part);
     if (s >= a.nsc || (a.active && !a.active[s]) || (a.gate && *a.gate <= a.gate_max)) return;
     const int64_t n = a.n;
+    // the i-registers of this part: part, part + split, ... (each particle's
+    // sum is formed by one wavefront in list order whatever the split)
+    uint32_t regs = 0, mine = 0;  // registers, and their mask bits in an entry
+    for (uint32_t k = part; k < (uint32_t)kNreg; k += a.split) {
+        regs |= 1u << k;
+        mine |= (CS == 4 ? 0xFu << (4 * k) : 1u << k);
+    }
     const int jl = lane & (kGroup - 1);
 
     // i particles; absent ones get a negative squared radius so that no pair
@@ -174,11 +183,14 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
         jv += jbase;
         // software pipeline: the next entry's j-particles load while the
         // current entry's tiles run
-        uint32_t cj = sfc_readlane(jv, 0);
+        uint64_t todo = sfc_ballot((mv & mine) != 0u);  // entries with a tile of this part
+        if (todo == 0) continue;
+        uint32_t e = (uint32_t)__builtin_ctzll(todo);
+        uint32_t cj = sfc_readlane(jv, (int)e);
         float xj[kNj], yj[kNj], zj[kNj], mj[kNj];
         load_j(cj, xj, yj, zj, mj);
-        for (uint32_t e = 0; e < cnt; e++) {
-            const uint32_t mk = sfc_readlane(mv, (int)e);
+        while (todo) {
+            const uint32_t mk = sfc_readlane(mv, (int)e) & mine;
             const uint32_t ccur = cj;
             float cx[kNj], cy[kNj], cz[kNj], cm[kNj];
 #pragma unroll
@@ -188,8 +200,10 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
                 cz[t] = zj[t];
                 cm[t] = mj[t];
             }
-            if (e + 1 < cnt) {
-                cj = sfc_readlane(jv, (int)e + 1);
+            todo &= todo - 1ull;
+            if (todo) {
+                e = (uint32_t)__builtin_ctzll(todo);
+                cj = sfc_readlane(jv, (int)e);
                 load_j(cj, xj, yj, zj, mj);
             }
             // the j-cluster is one of our own i-clusters: exclude i == j
@@ -224,11 +238,10 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
     // sum the partials of each i-particle (the kGroup lanes sharing it)
 #pragma unroll
     for (int k = 0; k < kNreg; k++) {
-#pragma unroll
-        for (int d = 1; d < kGroup; d <<= 1) {
-            acc[k] += __shfl_xor(acc[k], d, 64);
-            if (kCount) cnt_nb[k] += __shfl_xor(cnt_nb[k], d, 64);
-        }
+        if (kCount)
+            group_sum<kGroup>(acc[k], cnt_nb[k]);
+        else
+            group_sum<kGroup>(acc[k]);
     }
     // lane stores register jl (its group has kGroup lanes, one per register)
     float r = acc[0];
@@ -239,7 +252,7 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
         nb = jl == k ? cnt_nb[k] : nb;
     }
     const int64_t io = (int64_t)s * kScSize + ipart<CS>(jl, lane);
-    if (io < n && (!a.p_active || a.p_active[io])) {
+    if (io < n && ((regs >> jl) & 1u) && (!a.p_active || a.p_active[io])) {
         const float hh = a.h[io];
         const float hinv = 1.0f / hh;
         const float mi = kMass ? a.m[io] : 1.0f;
@@ -290,7 +303,8 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
     const int lane = sfc_lane();
     const int w = threadIdx.x / kWave;
     // wave-uniform: keep the super-cluster index (and all derived from it) scalar
-    const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)(xcd_remap(blockIdx.x, gridDim.x) * (blockDim.x / kWave) + w));
+    uint32_t part;
+    const uint32_t s = wave_sc(a.split, part);
     if (s >= a.nsc) return;
     const int64_t n = a.n;
     const int jq = CS == 8 ? lane >> 3 : lane >> 4;  // j-particle slot of the lane
@@ -363,10 +377,15 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
         f.h = a.h[qc];
         f.m = kMass ? a.m[qc] : 1.0f;
     };
-    auto half_entries8 = [&](uint32_t mvl, uint32_t jvl, uint32_t cnt) {
+    // (a part of a split super-cluster takes every split-th batch of a segment,
+    // the segment's number b0 / 64 shifting the deal)
+    auto half_entries8 = [&](uint32_t mvl, uint32_t jvl, uint32_t cnt, uint32_t b0) {
+        const uint32_t step = 8u * a.split;
+        const uint32_t first = a.split > 1 ? 8u * ((part + b0 / kWave) % a.split) : 0u;
+        if (first >= cnt) return;
         JLoad f;
-        load_batch8(jvl, 0, cnt, f);
-        for (uint32_t q0 = 0; q0 < cnt; q0 += 8) {
+        load_batch8(jvl, first, cnt, f);
+        for (uint32_t q0 = first; q0 < cnt; q0 += step) {
             // the batch's j-particles into LDS (absent ones: far away, radius
             // -1, mass 0; NaN padding never pairs either)
             const float hh = f.v ? f.h : -1.0f;
@@ -414,7 +433,7 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
                 }
             }
             pass_wave_sync();  // the next batch rewrites the LDS arrays
-            if (q0 + 8 < cnt) load_batch8(jvl, q0 + 8, cnt, f);
+            if (q0 + step < cnt) load_batch8(jvl, q0 + step, cnt, f);
         }
     };
 
@@ -433,7 +452,7 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
         prevj = sfc_readlane(jv, (int)cnt - 1);
         jv += jbase;
         if constexpr (CS == 8) {
-            half_entries8(mv, jv, cnt);
+            half_entries8(mv, jv, cnt, b0);
             continue;
         }
         // software pipeline: the next entry's j-particles load while the
@@ -451,8 +470,9 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
                 nm[t] = kMass ? ((vj && nh[t] > 0.0f) ? a.m[q] : 0.0f) : 1.0f;
             }
         };
-        load_j(sfc_readlane(jv, 0));
-        for (uint32_t e = 0; e < cnt; e++) {
+        if (part >= cnt) continue;
+        load_j(sfc_readlane(jv, (int)part));
+        for (uint32_t e = part; e < cnt; e += a.split) {
             const uint32_t mk = sfc_readlane(mv, (int)e);
             const uint32_t cj = sfc_readlane(jv, (int)e);
             float xj[kNj], yj[kNj], zj[kNj], mj[kNj], hj2[kNj], hjinv[kNj], accj[kNj];
@@ -471,7 +491,7 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
                 accj[t] = 0.0f;
                 cntj[t] = 0;
             }
-            if (e + 1 < cnt) load_j(sfc_readlane(jv, (int)e + 1));
+            if (e + a.split < cnt) load_j(sfc_readlane(jv, (int)(e + a.split)));
             // inside the super-cluster only j > i counts
             const int self_c = (cj >= own_c0 && cj < own_c0 + kNsub) ? (int)(cj - own_c0) : -1;
             auto keep = [&](int ci, int ipos, int jpos) {
@@ -644,9 +664,10 @@ int sfcnl::pass_impl(sfcnl_ctx ctx, int64_t n, int cs, int compress, int half, c
     if ((active || p_active || gate) && half)
         return set_err(ctx, SFCNL_E_ARG, "nlist_pass: a restricted pass needs the full list");
     PassArgs a{n, (uint32_t)((n + kScSize - 1) / kScSize), d_sc_info, d_pool, d_x, d_y, d_z, d_h, d_m, d_rho, d_nnb,
-               seg, per, active, p_active, gate, gate_max};
-    const int waves = ctx->pass_waves;
-    const unsigned g = blocks_for(a.nsc, waves);
+               seg, per, active, p_active, gate, gate_max, 1u};
+    a.split = pass_split(cs, half != 0, a.nsc);
+    const int waves = a.split > 1 ? (int)a.split : ctx->pass_waves;
+    const unsigned g = a.split > 1 ? a.nsc : blocks_for(a.nsc, waves);
     const unsigned tpb = (unsigned)(kWave * waves);
     hipStream_t st = ctx->stream;
     const int variant = (compress ? 4 : 0) | (d_m ? 2 : 0) | (d_nnb ? 1 : 0);

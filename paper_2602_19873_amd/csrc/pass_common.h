@@ -60,7 +60,44 @@ __device__ __forceinline__ int ipart(int k, int lane) {
     return CS == 8 ? 8 * k + (lane >> 3) : 16 * k + (lane >> 2);
 }
 
-// Cross-lane sums inside groups of 8 or 16 consecutive lanes with DPP
+constexpr int kPassSplitMax = 8;
+
+// Wavefronts that share a super-cluster's list. With one each, a pass takes
+// as long as its longest list until some thousand super-clusters fill the GPU.
+// A full list is split by i-clusters (every part decodes it and evaluates its
+// own clusters' tiles), so a particle's sum has one order whatever the split;
+// a half list, whose sums meet in atomics in any case, by its entries. Limits
+// where more parts stop paying; us with 1 / 2 / 4 / 8 parts (d density pass,
+// f force pass, uniform systems and lattices):
+//   full, clusters of 8:  d  32768: 117 / 88 / 68 / 58     f  32768: 84 / 63 / 44 / 38
+//                         d  65536: 126 / 101 / 86 / 101   f  97336: 105 / 87 / 77 / 93
+//                         d 131072: 125 / 132 / 136 / 165  f 262144: 126 / 142 / 157 / 196
+//   full, clusters of 4:  d  65536: 152 / 121 / 100        f 125000: 139 / 129 / 122
+//   half, clusters of 8:  d  32768: 108 / 65 / 43 / 35     f  64000: 120 / 73 / 50 / 51
+//                         d 262144: 140 / 114 / 109 / 140  f 262144: 142 / 115 / 114 / 146
+//                         d 800000: 276 / 260 / 281        f 729000: 252 / 236 / 254 / 364
+//                         d 2097152: 581 / 590 / 665       f 4096000: 1144 / 1197 / 1378
+//   half, clusters of 4:  d  65536: 265 / 145 / 86 / 67    f 125000: 223 / 133 / 91 / 91
+//                         d 800000: 501 / 422 / 403        f 262144: 248 / 185 / 153 / 163
+// (clusters of 16 behave as clusters of 4; their full lists have four
+// i-registers to share out)
+inline uint32_t pass_split(int cs, bool half, int64_t nsc) {
+    if (!half) return nsc <= 512 && cs == 8 ? 8u : (nsc <= 1600 ? 4u : 1u);
+    if (nsc <= (cs == 8 ? 800 : 1600)) return 8u;
+    if (nsc <= (cs == 8 ? 4096 : 16384)) return 4u;
+    return cs == 8 && nsc <= 16384 ? 2u : 1u;
+}
+
+// Super-cluster and part of this wavefront: a block holds several
+// super-clusters (split 1) or the parts of one.
+__device__ __forceinline__ uint32_t wave_sc(uint32_t split, uint32_t &part) {
+    const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const uint32_t b = (uint32_t)xcd_remap(blockIdx.x, gridDim.x);
+    part = split > 1 ? w : 0u;
+    return split > 1 ? b : b * (blockDim.x / kWave) + w;
+}
+
+// Cross-lane sums inside groups of 4, 8 or 16 consecutive lanes with DPP
 // (quad swaps, then the mirrored half row, then the mirrored row): every lane
 // of a group ends with the group total.
 template <int CTRL>
@@ -77,8 +114,10 @@ __device__ __forceinline__ void group_sum(float &f, int &c) {
     c += dpp_i<0xB1>(c);
     f += dpp_f<0x4E>(f);  // quad_perm [2, 3, 0, 1]
     c += dpp_i<0x4E>(c);
-    f += dpp_f<0x141>(f);  // row_half_mirror
-    c += dpp_i<0x141>(c);
+    if (kLanes >= 8) {
+        f += dpp_f<0x141>(f);  // row_half_mirror
+        c += dpp_i<0x141>(c);
+    }
     if (kLanes == 16) {
         f += dpp_f<0x140>(f);  // row_mirror
         c += dpp_i<0x140>(c);
@@ -89,7 +128,7 @@ template <int kLanes>
 __device__ __forceinline__ void group_sum(float &f) {
     f += dpp_f<0xB1>(f);
     f += dpp_f<0x4E>(f);
-    f += dpp_f<0x141>(f);
+    if (kLanes >= 8) f += dpp_f<0x141>(f);
     if (kLanes == 16) f += dpp_f<0x140>(f);
 }
 
