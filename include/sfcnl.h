@@ -322,9 +322,9 @@ int nlist_decode(sfcnl_ctx ctx, int64_t n, int cluster_size, int compress, const
  * super-cluster in the requested form. A later round recounts either through
  * full lists of the super-clusters holding a moved particle (each octree walk
  * shared by up to 64 particles) or, when few moved, with one wavefront per
- * moved particle walking the octree with its own sphere and no list;
- * opts->recount chooses: 0 by the number moved (at most n / 4 + 64: per
- * particle), 1 lists, 2 per particle. Counts and radii are the same either
+ * moved particle that walks the octree with its own sphere and takes the
+ * particle through all its remaining rounds; opts->recount chooses: 0 by the
+ * number moved and n, 1 lists, 2 per particle. Counts and radii are the same either
  * way; densities differ in summation order only. The workspace
  * is build_nlist_workspace(n, nl_opts) bytes. If only that closing build does
  * not fit, SFCNL_E_CAPACITY comes back with h_stats->unconverged == 0: radii,
@@ -457,8 +457,9 @@ int sfcnl_mlp_adam(sfcnl_ctx ctx, float *d_params, const float *d_grad, float *d
  *     pbase[s+1]/64)) and offsets are into the one shared pool.
  *   sfcnl_batch_h_iterate: sfcnl_h_iterate on every system at once, with the
  *     same rule per particle; a converged system is left unchanged while
- *     others continue. With use_graph, the launches of one round are captured
- *     once into a HIP graph on the batch's stream and replayed each round
+ *     others continue. With use_graph and recount 1, the launches of a few
+ *     rounds are captured once into a HIP graph on the batch's stream and
+ *     replayed (the other recounts have too few list rounds to repay a capture)
  *     (the host reads the status block between rounds); the batch's stream is
  *     ordered after the context's stream on entry and before it on return.
  *     The seed (nullable) works as in section 5, except that each system's

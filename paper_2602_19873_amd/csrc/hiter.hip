@@ -2,14 +2,13 @@
 // own-radius neighbour count by rebuilding the list (the paper rebuilds its
 // list every step with per-particle radii, Sec. IV; the update rule is this
 // library's, stated in sfcnl.h).
+#include <algorithm>
 #include <vector>
 
 #include "internal.h"
 
 namespace sfcnl {
 namespace {
-
-constexpr float kLn8 = 2.0794415416798357f;
 
 __global__ __launch_bounds__(256) void k_bracket_init(int64_t n, float2 *__restrict__ br) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -56,30 +55,8 @@ __global__ __launch_bounds__(256) void k_h_update(int64_t n, const int32_t *__re
         const int dev = c - target;
         if (dev > tol || dev < -tol) {
             moved = true;
-            const float hc = h[i];
             float2 b = br[i];
-            if (dev < 0)
-                b.x = fmaxf(b.x, hc);  // too few neighbours: h is a lower bound
-            else
-                b.y = fminf(b.y, hc);  // too many: an upper bound
-            float hn;
-            const float d = proposal ? proposal[i] : NAN;
-            if (d >= -kLn8 && d <= kLn8) {  // false for NaN
-                hn = hc * expf(d);
-            } else if (c == 0) {
-                hn = 2.0f * hc;
-            } else {
-                hn = hc * cbrtf((float)target / (float)c);
-                hn = fminf(fmaxf(hn, 0.5f * hc), 2.0f * hc);
-            }
-            if (!(hn > b.x && hn < b.y)) {
-                if (b.y == INFINITY)
-                    hn = 2.0f * b.x;
-                else if (b.x == 0.0f)
-                    hn = 0.5f * b.y;
-                else
-                    hn = 0.5f * (b.x + b.y);
-            }
+            const float hn = h_step(h[i], c, dev, target, proposal ? proposal[i] : NAN, b);
             h[i] = hn;
             br[i] = b;
         }
@@ -99,19 +76,27 @@ __global__ __launch_bounds__(256) void k_h_update(int64_t n, const int32_t *__re
 // clears the status block; the total itself stays in the scan output).
 __global__ void k_publish_total(const uint32_t *total, uint32_t *status) { status[kStUnconverged] = *total; }
 
-// Rounds after the first recount the moved particles one wavefront each
-// (count_moved_impl) when they are at most this many; above it, building the
-// lists of their super-clusters shares each walk among up to 64 particles.
-// Measured on the 1/r sphere and the 64-system batch: the per-particle walk
-// wins up to about a quarter of the particles.
-uint32_t count_path_limit(int64_t n) { return (uint32_t)(n / 4 + 64); }
+// Once at most this many particles moved in a round, each gets a wavefront
+// that takes it through all its remaining rounds (finish_moved_impl); above
+// it, building the lists of their super-clusters shares each walk among up to
+// 64 particles.
+// Whole runs in us with a limit of n / 4, n / 2, n:
+//   spheres, 20,000: 1053 / 927 / 817   200,000: 1931 / 1547 / 1398
+//          1,000,003: 3513 / 3527 / 4192
+//   uniform, 20,000: 1105 / 1067 / 885  200,000: 2066 / 2036 / 1436
+//          1,000,000: 3934 / 4163 / 4675
+//   batch of 4 systems up to 100,000: 9748 / 9193 / 6317
+// Small systems go there right after the first round, as their list rounds
+// are launches (about 20 of them). (Periodic runs keep the lower limit at
+// every size: the list rounds refuse radii that reach half a period.)
+int64_t finish_limit(int64_t n, bool periodic) { return n <= 262144 && !periodic ? n : n / 4 + 64; }
 
-
-
-// Grid of the per-particle recount: up to 8192 wavefronts.
-unsigned count_blocks(uint32_t total) {
-    const uint32_t b = (total + 3u) / 4u;
-    return b < 1u ? 1u : (b > 2048u ? 2048u : b);
+// Adds a finish that started before round `it` to the run's statistics.
+void add_finish(sfcnl_hiter_stats &S, const uint32_t *status, int it, int max_iters) {
+    const int rounds = (int)status[kStFinRounds], left = max_iters - it;
+    S.iters = it + (rounds < left ? rounds + 1 : left);  // (the round that finds all in place counts)
+    S.moved += (int64_t)(status[kStFinMoved] | (uint64_t)status[kStFinMoved + 1] << 32);
+    S.unconverged = status[kStFinLeft];
 }
 
 }  // namespace
@@ -179,8 +164,20 @@ extern "C" int sfcnl_h_iterate(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys,
     bool list_final = false;
     for (int it = 0; it < it_opts->max_iters; it++) {
         const bool first = it == 0;
-        const bool per_particle = !first && (it_opts->recount == 2 ||
-                                             (it_opts->recount == 0 && S.unconverged <= count_path_limit(n)));
+        if (!first && (it_opts->recount == 2 || (it_opts->recount == 0 && S.unconverged <= finish_limit(n, make_period(nl_opts->period).on())))) {
+            // few moved: all their remaining rounds on the last octree
+            int rc = finish_moved_impl(ctx, n, act, d_x, d_y, d_z, d_h, br, d_m, d_rho, d_nnb, it_opts->target,
+                                       it_opts->tol, it_opts->max_iters - it, SegTable{}, make_period(nl_opts->period),
+                                       nullptr, S.unconverged);
+            if (rc) return rc;
+            rc = read_status(ctx);
+            if (rc) return rc;
+            if (ctx->h_status[kStTree])
+                return set_err(ctx, SFCNL_E_HIP, "internal error: octree invariant broken (0x%x)", ctx->h_status[kStTree]);
+            add_finish(S, ctx->h_status, it, it_opts->max_iters);
+            list_final = false;
+            break;
+        }
         // every super-cluster in the requested form: the first round, and with
         // the automatic recount and a half list every round that builds lists.
         // The counting lists are full lists (each pair twice): on the 8M 1/r
@@ -188,30 +185,23 @@ extern "C" int sfcnl_h_iterate(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys,
         // those rounds, they cost more than the half list and its symmetric
         // pass (27.5 against 31.4 ms to converge). Counts, and so rounds and
         // radii, are the same either way (n_i depends on h_i only).
-        const bool full = first || (it_opts->recount == 0 && nl_opts->half && !per_particle);
+        const bool full = first || (it_opts->recount == 0 && nl_opts->half);
         const sfcnl_nlist_opts &o = full ? *nl_opts : it_nl;
         int rc = SFCNL_OK;
         if (full) {
             rc = clusters_impl(ctx, n, d_x, d_y, d_z, d_h, o.cluster_size, d_bbox, SegTable{});
             if (rc) return rc;
         }
-        if (per_particle) {
-            // few moved: one wavefront per moved particle on the last octree
-            rc = count_moved_impl(ctx, n, act, d_x, d_y, d_z, d_h, d_m, d_rho, d_nnb, SegTable{},
-                                  make_period(o.period), nullptr, 0, count_blocks((uint32_t)S.unconverged));
-            if (rc) return rc;
-        } else {
-            // full rounds: every super-cluster in the requested form; the
-            // others: counting lists of the moved particles, same octree
-            rc = nlist_build_impl(ctx, n, d_keys, d_x, d_y, d_z, d_h, d_bbox, o, d_ws, ws_bytes, d_sc_info, d_pool,
-                                  pool_bytes, SegTable{}, true, &S.used_bytes, &S.max_nj, full ? nullptr : act.sc,
-                                  full ? nullptr : act.p, !full);
-            if (rc) return rc;
-            rc = pass_impl(ctx, n, o.cluster_size, o.compress, o.half, d_sc_info, d_pool, d_x, d_y, d_z, d_h, d_m,
-                           d_rho, d_nnb, SegTable{}, make_period(o.period), full ? nullptr : act.sc,
-                           full ? nullptr : act.p);
-            if (rc) return rc;
-        }
+        // full rounds: every super-cluster in the requested form; the
+        // others: counting lists of the moved particles, same octree
+        rc = nlist_build_impl(ctx, n, d_keys, d_x, d_y, d_z, d_h, d_bbox, o, d_ws, ws_bytes, d_sc_info, d_pool,
+                              pool_bytes, SegTable{}, true, &S.used_bytes, &S.max_nj, full ? nullptr : act.sc,
+                              full ? nullptr : act.p, !full);
+        if (rc) return rc;
+        rc = pass_impl(ctx, n, o.cluster_size, o.compress, o.half, d_sc_info, d_pool, d_x, d_y, d_z, d_h, d_m,
+                       d_rho, d_nnb, SegTable{}, make_period(o.period), full ? nullptr : act.sc,
+                       full ? nullptr : act.p);
+        if (rc) return rc;
         list_final = full;
         const float *proposal = nullptr;
         if (seed && seed->mode == SFCNL_SEED_AFTER_FIRST && first) {  // learned step from the first counts
@@ -235,16 +225,17 @@ extern "C" int sfcnl_h_iterate(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys,
         S.iters = it + 1;
         S.unconverged = ctx->h_status[kStUnconverged];
         S.moved += S.unconverged;
-        if (S.unconverged == 0) {
-            if (!list_final) {  // the list of the final radii, every super-cluster, requested form
-                rc = clusters_impl(ctx, n, d_x, d_y, d_z, d_h, nl_opts->cluster_size, d_bbox, SegTable{});
-                if (rc) return rc;
-                rc = nlist_build_impl(ctx, n, d_keys, d_x, d_y, d_z, d_h, d_bbox, *nl_opts, d_ws, ws_bytes,
-                                      d_sc_info, d_pool, pool_bytes, SegTable{}, true, &S.used_bytes, &S.max_nj);
-                if (rc) return rc;
-            }
-            return SFCNL_OK;
+        if (S.unconverged == 0) break;
+    }
+    if (S.unconverged == 0) {
+        if (!list_final) {  // the list of the final radii, every super-cluster, requested form
+            int rc = clusters_impl(ctx, n, d_x, d_y, d_z, d_h, nl_opts->cluster_size, d_bbox, SegTable{});
+            if (rc) return rc;
+            rc = nlist_build_impl(ctx, n, d_keys, d_x, d_y, d_z, d_h, d_bbox, *nl_opts, d_ws, ws_bytes, d_sc_info,
+                                  d_pool, pool_bytes, SegTable{}, true, &S.used_bytes, &S.max_nj);
+            if (rc) return rc;
         }
+        return SFCNL_OK;
     }
     return set_err(ctx, SFCNL_E_NOCONV, "sfcnl_h_iterate: %lld particles unconverged after %d rounds",
                    (long long)S.unconverged, it_opts->max_iters);
@@ -276,6 +267,15 @@ struct RoundArgs {
     int32_t *nnb;
 };
 
+// The status block and the per-system words to host slot `slot`.
+int copy_round_status(sfcnl_ctx ctx, sfcnl_batch b, int slot) {
+    SFCNL_HIP(ctx, hipMemcpyAsync(b->h_rstat + (size_t)slot * kStWords, ctx->d_status, kStWords * sizeof(uint32_t),
+                                  hipMemcpyDeviceToHost, ctx->stream));
+    SFCNL_HIP(ctx, hipMemcpyAsync(b->h_sys_moved + (size_t)slot * b->nsys, b->d_sys_moved,
+                                  b->nsys * sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream));
+    return SFCNL_OK;
+}
+
 // Enqueues one round on ctx->stream with list options `o`; `seed` adds the
 // learned first step; `restricted` limits the list build and the pass to the
 // super-clusters flagged in `act` (which receives the next round's flags);
@@ -290,25 +290,16 @@ int enqueue_round(sfcnl_ctx ctx, const RoundArgs &r, const sfcnl_nlist_opts &o, 
         rc = clusters_impl(ctx, n, r.x, r.y, r.z, r.h, o.cluster_size, r.bbox, seg);
         if (rc) return rc;
     }
-    // restricted rounds hold both recounts; the moved total (left in the scan
-    // output by the previous round) selects one on the device: the lists of
-    // the moved particles' super-clusters, or one wavefront per moved particle
+    // in a replay, a restricted round after convergence (the moved total left
+    // by the previous round is zero) does nothing
     const uint32_t *gate = restricted ? act.scan + n / kScSize : nullptr;
-    // recount 1: lists only (the per-particle path runs for a zero total,
-    // where it has nothing to do); 2: per particle only
-    const uint32_t limit = r.it->recount == 1 ? 0u : (r.it->recount == 2 ? 0xFFFFFFFFu : count_path_limit(n));
     rc = nlist_build_impl(ctx, n, r.keys, r.x, r.y, r.z, r.h, r.bbox, o, r.ws, r.ws_bytes, r.sc_info, r.pool,
                           r.pool_bytes, seg, false, nullptr, nullptr, restricted ? act.sc : nullptr,
-                          restricted ? act.p : nullptr, restricted, gate, limit);
+                          restricted ? act.p : nullptr, restricted, gate, 0u);
     if (rc) return rc;
     rc = pass_impl(ctx, n, o.cluster_size, o.compress, o.half, r.sc_info, r.pool, r.x, r.y, r.z, r.h, r.m, r.rho,
-                   r.nnb, seg, Period{}, restricted ? act.sc : nullptr, restricted ? act.p : nullptr, gate, limit);
+                   r.nnb, seg, Period{}, restricted ? act.sc : nullptr, restricted ? act.p : nullptr, gate, 0u);
     if (rc) return rc;
-    if (restricted) {
-        rc = count_moved_impl(ctx, n, act, r.x, r.y, r.z, r.h, r.m, r.rho, r.nnb, seg, Period{}, gate, limit,
-                              count_blocks(r.it->recount == 2 ? 8192u : limit));
-        if (rc) return rc;
-    }
     const float *proposal = nullptr;
     if (seed) {
         rc = features_impl(ctx, n, r.keys, r.x, r.y, r.z, r.h, r.nnb, 1.0f, r.it->target, seed->d_feat, seg);
@@ -326,11 +317,7 @@ int enqueue_round(sfcnl_ctx ctx, const RoundArgs &r, const sfcnl_nlist_opts &o, 
     if (rc) return rc;
     k_publish_total<<<1, 1, 0, ctx->stream>>>(act.scan + n / kScSize, ctx->d_status);
     SFCNL_LAUNCHED(ctx);
-    SFCNL_HIP(ctx, hipMemcpyAsync(r.b->h_rstat + (size_t)slot * kStWords, ctx->d_status, kStWords * sizeof(uint32_t),
-                                  hipMemcpyDeviceToHost, ctx->stream));
-    SFCNL_HIP(ctx, hipMemcpyAsync(r.b->h_sys_moved + (size_t)slot * r.b->nsys, r.b->d_sys_moved,
-                                  r.b->nsys * sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream));
-    return SFCNL_OK;
+    return copy_round_status(ctx, r.b, slot);
 }
 
 // Runs the batch's work on its own stream, ordered after the caller's stream
@@ -428,20 +415,43 @@ extern "C" int sfcnl_batch_h_iterate(sfcnl_ctx ctx, sfcnl_batch b, const uint64_
     it_nl.half = 0;
     const ActiveWs act = nlist_ws_active(d_ws, b->n_pad, it_nl, b->nsys);
     bool list_final = false;
-    // restricted rounds replay a graph of kGraphRounds rounds (one of a single
-    // round when fewer are left): rounds after convergence in a replay find
-    // nothing flagged and change nothing, so the host reads the status
-    // blocks of a replay in order and stops at the first converged one
+    // With recount 1, where every round builds lists, restricted rounds replay
+    // a graph of kGraphRounds rounds (one of a single round when fewer are
+    // left): rounds after convergence in a replay find nothing flagged and
+    // change nothing, so the host reads the status blocks of a replay in order
+    // and stops at the first converged one. Otherwise only the few rounds
+    // before the finish build lists, which is less than a capture takes
+    // (0.3 ms for four rounds).
     GraphHolder gh_many, gh_one;
     std::vector<char> active((size_t)b->nsys, 1);
     int it = 0;
-    while (it < it_opts->max_iters) {
+    while (it < it_opts->max_iters && S.unconverged > 0) {
         int nr = 1;
+        if (it > 0 && (it_opts->recount == 2 || (it_opts->recount == 0 && S.unconverged <= finish_limit(b->n_pad, false)))) {
+            // few moved: all their remaining rounds on the last octree
+            int rc = fill_u32(ctx, b->d_sys_moved, b->nsys, 0);
+            if (rc) return rc;
+            rc = finish_moved_impl(ctx, b->n_pad, act, d_x, d_y, d_z, d_h, r.br, d_m, d_rho, d_nnb, it_opts->target,
+                                   it_opts->tol, it_opts->max_iters - it, seg_of(b), Period{}, b->d_sys_moved,
+                                   S.unconverged);
+            if (rc) return rc;
+            rc = copy_round_status(ctx, b, 0);
+            if (rc) return rc;
+            SFCNL_HIP(ctx, hipStreamSynchronize(st));
+            if (b->h_rstat[kStTree])
+                return set_err(ctx, SFCNL_E_HIP, "internal error: octree invariant broken (0x%x)", b->h_rstat[kStTree]);
+            add_finish(S, b->h_rstat, it, it_opts->max_iters);
+            if (h_sys_rounds)
+                for (int s = 0; s < b->nsys; s++)
+                    if (active[s]) h_sys_rounds[s] = std::min(it + (int)b->h_sys_moved[s] + 1, it_opts->max_iters);
+            list_final = false;
+            break;
+        }
         if (it == 0) {
             const sfcnl_hseed *sd = (seed && seed->mode == SFCNL_SEED_AFTER_FIRST) ? seed : nullptr;
             int rc = enqueue_round(ctx, r, *nl_opts, sd, false, act, 0);
             if (rc) return rc;
-        } else if (use_graph) {
+        } else if (use_graph && it_opts->recount == 1) {
             nr = it + kGraphRounds <= it_opts->max_iters ? kGraphRounds : 1;
             GraphHolder &gh = nr > 1 ? gh_many : gh_one;
             if (!gh.e) {
@@ -493,18 +503,19 @@ extern "C" int sfcnl_batch_h_iterate(sfcnl_ctx ctx, sfcnl_batch b, const uint64_
                 for (int s = 0; s < b->nsys; s++)
                     if (it == 0 || active[s]) h_sys_rounds[s] = it + 1;
             for (int s = 0; s < b->nsys; s++) active[s] = hm[s] != 0;
-            if (S.unconverged == 0) {
-                if (!list_final) {  // the list of the final radii, every super-cluster, requested form
-                    const SegTable seg = seg_of(b);
-                    int rc = clusters_impl(ctx, b->n_pad, d_x, d_y, d_z, d_h, nl_opts->cluster_size, d_bbox, seg);
-                    if (rc) return rc;
-                    rc = nlist_build_impl(ctx, b->n_pad, d_keys, d_x, d_y, d_z, d_h, d_bbox, *nl_opts, d_ws, ws_bytes,
-                                          d_sc_info, d_pool, pool_bytes, seg, true, &S.used_bytes, &S.max_nj);
-                    if (rc) return rc;
-                }
-                return SFCNL_OK;
-            }
+            if (S.unconverged == 0) break;
         }
+    }
+    if (S.unconverged == 0) {
+        if (!list_final) {  // the list of the final radii, every super-cluster, requested form
+            const SegTable seg = seg_of(b);
+            int rc = clusters_impl(ctx, b->n_pad, d_x, d_y, d_z, d_h, nl_opts->cluster_size, d_bbox, seg);
+            if (rc) return rc;
+            rc = nlist_build_impl(ctx, b->n_pad, d_keys, d_x, d_y, d_z, d_h, d_bbox, *nl_opts, d_ws, ws_bytes,
+                                  d_sc_info, d_pool, pool_bytes, seg, true, &S.used_bytes, &S.max_nj);
+            if (rc) return rc;
+        }
+        return SFCNL_OK;
     }
     return set_err(ctx, SFCNL_E_NOCONV, "sfcnl_batch_h_iterate: %lld particles unconverged after %d rounds",
                    (long long)S.unconverged, it_opts->max_iters);

@@ -26,6 +26,10 @@ enum StatusWord : int {
     kStTree = 5,         // octree invariant broken (internal error)
     kStUnconverged = 6,  // h iteration: particles that moved this round
     kStChunks = 7,       // shared staging chunks the lists asked for (taken, plus requests left unserved)
+    kStFinMoved = 8,     // finish_moved: moves over its rounds (64 bits)
+    kStFinRounds = 10,   // its rounds in which a particle moved
+    kStFinLeft = 11,     // particles still moving in its last allowed round
+    kStFinNext = 12,     // its next unclaimed list position
     kStWords = 16
 };
 
@@ -269,7 +273,7 @@ size_t nlist_ws_bytes(int64_t n, const sfcnl_nlist_opts &o, int nsys);
 // `reuse_tree` keeps the octree of the previous build (same keys, bucket and
 // cluster size: its positions and ranges are still exact).
 // `gate` (device word, nullable): when *gate <= gate_max every super-cluster
-// gets an empty list (the moved particles are recounted by count_moved_impl).
+// gets an empty list.
 int nlist_build_impl(sfcnl_ctx ctx, int64_t n, const uint64_t *keys, const float *x, const float *y, const float *z,
                      const float *h, const float *bbox, const sfcnl_nlist_opts &o, void *ws, size_t ws_bytes,
                      uint32_t *sc_info, uint32_t *pool, size_t pool_bytes, const SegTable &seg, bool readback,
@@ -287,15 +291,16 @@ struct ActiveWs {
     const uint4 *cs_rec;
     uint32_t nslots;
 };
-// Recount of the moved particles without a list (h-iteration rounds after the
-// first): compacts act.p into act.plist, then one wavefront per listed
-// particle walks the octree of the last full build with the particle's own
-// sphere and writes rho and nnb as the restricted pass would. With `gate`
-// (device word, nullable) both kernels run only if *gate <= gate_max; the
-// per-particle kernel grid is `blocks` workgroups of 4 waves.
-int count_moved_impl(sfcnl_ctx ctx, int64_t n, const ActiveWs &act, const float *x, const float *y, const float *z,
-                     const float *h, const float *m, float *rho, int32_t *nnb, const SegTable &seg, const Period &per,
-                     const uint32_t *gate, uint32_t gate_max, unsigned blocks);
+// All remaining rounds of the moved particles (act.p, their number in
+// act.scan[nsc]) of an h-iteration without a list: compacts act.p into
+// act.plist, then every listed particle is counted and updated until it is
+// within tol of the target or `rounds` rounds are over, and gets its rho and
+// nnb. kStFin* of the status block then hold the outcome; sys_rounds (nullable,
+// one word per system, zeroed by the caller) the rounds in which a particle of
+// the system moved. moved: the number of moved particles (host).
+int finish_moved_impl(sfcnl_ctx ctx, int64_t n, const ActiveWs &act, const float *x, const float *y, const float *z,
+                      float *h, float2 *br, const float *m, float *rho, int32_t *nnb, int target, int tol, int rounds,
+                      const SegTable &seg, const Period &per, uint32_t *sys_rounds, int64_t moved);
 ActiveWs nlist_ws_active(void *ws, int64_t n, const sfcnl_nlist_opts &o, int nsys);
 int clusters_impl(sfcnl_ctx ctx, int64_t n, const float *x, const float *y, const float *z, const float *h, int cs,
                   float *bbox, const SegTable &seg);
@@ -392,6 +397,44 @@ __device__ __forceinline__ float sfc_wave_max(float v) {
 }
 __device__ __forceinline__ float sfc_wave_min(float v) {
     return sfc_wave_reduce(v, [](float a, float b) { return fminf(a, b); });
+}
+
+// The h-iteration's update of a radius hc that holds c particles, dev =
+// c - target beyond the tolerance: the bracket b takes hc, and the new radius
+// is the learned step d = log(h_new / hc) where it is within a factor 8, else
+// the cube-root step, and the bracket's middle where that leaves the bracket.
+constexpr float kLn8 = 2.0794415416798357f;
+__device__ __forceinline__ float h_step(float hc, int c, int dev, int target, float d, float2 &b) {
+    if (dev < 0)
+        b.x = fmaxf(b.x, hc);  // too few neighbours: h is a lower bound
+    else
+        b.y = fminf(b.y, hc);  // too many: an upper bound
+    float hn;
+    if (d >= -kLn8 && d <= kLn8) {  // false for NaN
+        hn = hc * expf(d);
+    } else if (c == 0) {
+        hn = 2.0f * hc;
+    } else {
+        hn = hc * cbrtf((float)target / (float)c);
+        hn = fminf(fmaxf(hn, 0.5f * hc), 2.0f * hc);
+    }
+    if (!(hn > b.x && hn < b.y)) {
+        if (b.y == INFINITY)
+            hn = 2.0f * b.x;
+        else if (b.x == 0.0f)
+            hn = 0.5f * b.y;
+        else
+            hn = 0.5f * (b.x + b.y);
+    }
+    return hn;
+}
+
+// From this count on h_step without a learned step gives the same radius for
+// every count (the cube-root step is clamped at a half from 8 targets on, the
+// bracket takes the radius alone).
+inline uint32_t h_plenty(int target, int tol) {
+    const int64_t p = std::max<int64_t>(9 * (int64_t)target, (int64_t)target + tol + 1);
+    return p < 0x7FFFFFFF ? (uint32_t)p : 0xFFFFFFFFu;
 }
 
 // Gap along one axis between two boxes (or a point and a box), from

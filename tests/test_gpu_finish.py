@@ -1,0 +1,84 @@
+"""An h-iteration whose particles finish one by one (recount 2) against one
+that builds lists in every round (recount 1): the same radii, counts, brackets,
+rounds and moves, densities within 1e-5 of the oracle's, at targets that fit
+into the kept pairs, just do not, and far exceed them, with masses, periodic
+axes, round limits inside the finish, and batches."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2602_19873_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    import paper_2602_19873_amd as sf
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    torch.cuda.set_device(0)
+    ctx = sf.Context(0)
+    yield sf, ctx, torch
+    ctx.close()
+
+
+def _sorted(env, s, masses):
+    sf, ctx, torch = env
+    m = np.random.default_rng(s.n).uniform(0.5, 2.0, s.n).astype(np.float32) if masses else np.ones(s.n, np.float32)
+    f = [torch.from_numpy(np.ascontiguousarray(v)).cuda() for v in (s.x, s.y, s.z, s.h, m)]
+    keys, perm = sf.sfc_sort(ctx, *f[:3], s.box)
+    return keys, sf.sfc_gather(ctx, perm, f)
+
+
+@pytest.mark.parametrize("kind,n,target,masses,period,max_iters", [
+    ("uniform", 9001, 50, False, False, 64), ("uniform", 9001, 430, True, False, 64),
+    ("uniform", 9001, 470, False, False, 64), ("uniform", 6000, 1500, True, False, 64),
+    ("uniform", 9001, 50, True, True, 64), ("uniform", 9001, 450, False, True, 64),
+    ("plummer", 20000, 100, False, False, 64), ("plummer", 20000, 100, True, False, 4),
+    ("plummer", 20000, 100, False, False, 9), ("uniform", 65, 10, False, False, 64), ("uniform", 40, 64, False, False, 8)])
+def test_finish_matches_lists(env, kind, n, target, masses, period, max_iters):
+    sf, ctx, torch = env
+    print("finish %s n=%d T=%d m=%d per=%d max=%d" % (kind, n, target, masses, period, max_iters), flush=True)
+    s = (workloads.uniform_global(n, 5, target=min(0.7 * target, 0.5 * n)) if kind == "uniform"
+         else workloads.plummer(n, 6, target=target))
+    keys, (xs, ys, zs, h0, ms) = _sorted(env, s, masses)
+    per = (1.0, 1.0, 1.0) if period else None
+    out = {}
+    for mode in (1, 2):
+        h, br = h0.clone(), torch.empty(2 * n, dtype=torch.float32, device="cuda")
+        r = sf.h_iterate(ctx, keys, xs, ys, zs, h, target=target, tol=1, max_iters=max_iters, m=ms if masses else None,
+                         bracket=br, period=per, recount=mode)
+        rho = r.rho.cpu().numpy()[:n].astype(np.float64)
+        out[mode] = (h.cpu().numpy(), r.nnb.cpu().numpy()[:n], br.cpu().numpy(),
+                     (r.iters, r.moved, r.unconverged, r.converged), rho)
+    for k in range(3):
+        np.testing.assert_array_equal(out[1][k], out[2][k])
+    assert out[1][3] == out[2][3]
+    assert (np.abs(out[2][4] - out[1][4]) / out[1][4]).max() <= 2e-5
+    if out[2][3][3]:
+        host = [v.cpu().numpy() for v in (xs, ys, zs)]
+        ref, cnt = oracle.density(*host, out[2][0], ms.cpu().numpy() if masses else None, period=per)
+        np.testing.assert_array_equal(out[2][1], cnt)
+        assert (np.abs(out[2][4] - ref) / ref).max() <= 1e-5
+
+
+@pytest.mark.parametrize("max_iters", [3, 6, 64])
+def test_finish_batch(env, max_iters):
+    sf, ctx, torch = env
+    sys_ = [workloads.plummer(3000, 1, target=60), workloads.uniform_global(700, 2, target=60),
+            workloads.plummer(12001, 3, target=60), workloads.uniform_global(64, 4, target=30)]
+    out = {}
+    for mode in (1, 2, 0):
+        b = sf.Batch(ctx, [t.n for t in sys_], [t.box for t in sys_])
+        f = [torch.from_numpy(np.concatenate([getattr(t, c) for t in sys_])).cuda() for c in "xyzh"]
+        keys, perm = sf.batch_sort(ctx, b, *f[:3])
+        srt = sf.batch_gather(ctx, b, perm, f)
+        r = sf.batch_h_iterate(ctx, b, keys, *srt, target=60, tol=1, max_iters=max_iters, recount=mode)
+        out[mode] = (srt[3].cpu().numpy(), r.nnb.cpu().numpy(), r.sys_rounds.tolist(),
+                     (r.iters, r.moved, r.unconverged, r.converged))
+    for mode in (2, 0):
+        np.testing.assert_array_equal(out[mode][0], out[1][0])
+        np.testing.assert_array_equal(out[mode][1], out[1][1])
+        assert out[mode][2:] == out[1][2:]
