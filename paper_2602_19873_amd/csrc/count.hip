@@ -207,8 +207,8 @@ __global__ __launch_bounds__(256) void k_finish_moved(FinishArgs a) {
                 // no later radius reaches the bracket's upper end
                 const float reach = fmaxf(fminf(kReach * hc, b.y), hc);
                 kept_r2 = reach * reach;
-                // (a count from 9 times the target on halves the radius whatever
-                // it is, so only the last round needs it)
+                // (a count of `plenty` halves the radius whatever it is, so only
+                // the last round needs it)
                 cnt = walk(h2, 0.0f, r + 1 < (uint32_t)a.rounds ? a.plenty : 0xFFFFFFFFu, std::false_type{});
             }
             const int dev = (int)cnt - a.target;

@@ -76,6 +76,8 @@ __global__ __launch_bounds__(256) void k_h_update(int64_t n, const int32_t *__re
 // clears the status block; the total itself stays in the scan output).
 __global__ void k_publish_total(const uint32_t *total, uint32_t *status) { status[kStUnconverged] = *total; }
 
+constexpr uint32_t kAllCounts = 0xFFFFFFFFu;  // (pass_impl's plenty)
+
 // Once at most this many particles moved in a round, each gets a wavefront
 // that takes it through all its remaining rounds (finish_moved_impl); above
 // it, building the lists of their super-clusters shares each walk among up to
@@ -162,8 +164,11 @@ extern "C" int sfcnl_h_iterate(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys,
     const ActiveWs act = nlist_ws_active(d_ws, n, it_nl, 1);
     const int64_t nsc = (n + kScSize - 1) / kScSize;
     bool list_final = false;
+    // particles that move are counted again unless the rounds are over
+    const uint32_t plenty = h_plenty(it_opts->target, it_opts->tol);
     for (int it = 0; it < it_opts->max_iters; it++) {
         const bool first = it == 0;
+        const bool learned = first && seed && seed->mode == SFCNL_SEED_AFTER_FIRST;  // features take the counts
         if (!first && (it_opts->recount == 2 || (it_opts->recount == 0 && S.unconverged <= finish_limit(n, make_period(nl_opts->period).on())))) {
             // few moved: all their remaining rounds on the last octree
             int rc = finish_moved_impl(ctx, n, act, d_x, d_y, d_z, d_h, br, d_m, d_rho, d_nnb, it_opts->target,
@@ -200,11 +205,11 @@ extern "C" int sfcnl_h_iterate(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys,
         if (rc) return rc;
         rc = pass_impl(ctx, n, o.cluster_size, o.compress, o.half, d_sc_info, d_pool, d_x, d_y, d_z, d_h, d_m,
                        d_rho, d_nnb, SegTable{}, make_period(o.period), full ? nullptr : act.sc,
-                       full ? nullptr : act.p);
+                       full ? nullptr : act.p, nullptr, 0, learned || it + 1 == it_opts->max_iters ? kAllCounts : plenty);
         if (rc) return rc;
         list_final = full;
         const float *proposal = nullptr;
-        if (seed && seed->mode == SFCNL_SEED_AFTER_FIRST && first) {  // learned step from the first counts
+        if (learned) {  // learned step from the first counts
             rc = sfcnl_hseed_features(ctx, n, d_keys, d_x, d_y, d_z, d_h, d_nnb, seed->box_edge, it_opts->target,
                                       seed->d_feat);
             if (rc) return rc;
@@ -279,10 +284,11 @@ int copy_round_status(sfcnl_ctx ctx, sfcnl_batch b, int slot) {
 // Enqueues one round on ctx->stream with list options `o`; `seed` adds the
 // learned first step; `restricted` limits the list build and the pass to the
 // super-clusters flagged in `act` (which receives the next round's flags);
-// the round's status block and per-system moved flags are copied to host
+// particles from `plenty` pairs on may be counted short (they move, and a later
+// round counts them again); the round's status block and per-system moved flags are copied to host
 // slot `slot`.
 int enqueue_round(sfcnl_ctx ctx, const RoundArgs &r, const sfcnl_nlist_opts &o, const sfcnl_hseed *seed,
-                  bool restricted, const ActiveWs &act, int slot) {
+                  bool restricted, const ActiveWs &act, int slot, uint32_t plenty) {
     const SegTable seg = seg_of(r.b);
     const int64_t n = r.b->n_pad;
     int rc = SFCNL_OK;
@@ -298,7 +304,7 @@ int enqueue_round(sfcnl_ctx ctx, const RoundArgs &r, const sfcnl_nlist_opts &o, 
                           restricted ? act.p : nullptr, restricted, gate, 0u);
     if (rc) return rc;
     rc = pass_impl(ctx, n, o.cluster_size, o.compress, o.half, r.sc_info, r.pool, r.x, r.y, r.z, r.h, r.m, r.rho,
-                   r.nnb, seg, Period{}, restricted ? act.sc : nullptr, restricted ? act.p : nullptr, gate, 0u);
+                   r.nnb, seg, Period{}, restricted ? act.sc : nullptr, restricted ? act.p : nullptr, gate, 0u, plenty);
     if (rc) return rc;
     const float *proposal = nullptr;
     if (seed) {
@@ -415,6 +421,7 @@ extern "C" int sfcnl_batch_h_iterate(sfcnl_ctx ctx, sfcnl_batch b, const uint64_
     it_nl.half = 0;
     const ActiveWs act = nlist_ws_active(d_ws, b->n_pad, it_nl, b->nsys);
     bool list_final = false;
+    const uint32_t plenty = h_plenty(it_opts->target, it_opts->tol);
     // With recount 1, where every round builds lists, restricted rounds replay
     // a graph of kGraphRounds rounds (one of a single round when fewer are
     // left): rounds after convergence in a replay find nothing flagged and
@@ -449,7 +456,7 @@ extern "C" int sfcnl_batch_h_iterate(sfcnl_ctx ctx, sfcnl_batch b, const uint64_
         }
         if (it == 0) {
             const sfcnl_hseed *sd = (seed && seed->mode == SFCNL_SEED_AFTER_FIRST) ? seed : nullptr;
-            int rc = enqueue_round(ctx, r, *nl_opts, sd, false, act, 0);
+            int rc = enqueue_round(ctx, r, *nl_opts, sd, false, act, 0, sd || it + 1 == it_opts->max_iters ? kAllCounts : plenty);
             if (rc) return rc;
         } else if (use_graph && it_opts->recount == 1) {
             nr = it + kGraphRounds <= it_opts->max_iters ? kGraphRounds : 1;
@@ -458,7 +465,7 @@ extern "C" int sfcnl_batch_h_iterate(sfcnl_ctx ctx, sfcnl_batch b, const uint64_
                 ctx->prof_slots = 0;  // no event records inside the graph
                 SFCNL_HIP(ctx, hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
                 int rc = SFCNL_OK;
-                for (int k = 0; k < nr && rc == SFCNL_OK; k++) rc = enqueue_round(ctx, r, it_nl, nullptr, true, act, k);
+                for (int k = 0; k < nr && rc == SFCNL_OK; k++) rc = enqueue_round(ctx, r, it_nl, nullptr, true, act, k, kAllCounts);
                 hipGraph_t g = nullptr;
                 hipError_t e = hipStreamEndCapture(st, &g);
                 gh.g = g;
@@ -469,7 +476,7 @@ extern "C" int sfcnl_batch_h_iterate(sfcnl_ctx ctx, sfcnl_batch b, const uint64_
             }
             SFCNL_HIP(ctx, hipGraphLaunch(gh.e, st));
         } else {
-            int rc = enqueue_round(ctx, r, it_nl, nullptr, true, act, 0);
+            int rc = enqueue_round(ctx, r, it_nl, nullptr, true, act, 0, it + 1 == it_opts->max_iters ? kAllCounts : plenty);
             if (rc) return rc;
         }
         SFCNL_HIP(ctx, hipStreamSynchronize(st));

@@ -305,11 +305,13 @@ ActiveWs nlist_ws_active(void *ws, int64_t n, const sfcnl_nlist_opts &o, int nsy
 int clusters_impl(sfcnl_ctx ctx, int64_t n, const float *x, const float *y, const float *z, const float *h, int cs,
                   float *bbox, const SegTable &seg);
 // `active` as for nlist_build_impl: the pass leaves rho and nnb of inactive
-// super-clusters unchanged (full lists only).
+// super-clusters unchanged (full lists only). plenty: particles whose count
+// reaches it may get any count from it on, and any rho.
 int pass_impl(sfcnl_ctx ctx, int64_t n, int cs, int compress, int half, const uint32_t *sc_info, const uint32_t *pool,
               const float *x, const float *y, const float *z, const float *h, const float *m, float *rho, int32_t *nnb,
               const SegTable &seg, const Period &per, const uint32_t *active = nullptr,
-              const uint8_t *p_active = nullptr, const uint32_t *gate = nullptr, uint32_t gate_max = 0);
+              const uint8_t *p_active = nullptr, const uint32_t *gate = nullptr, uint32_t gate_max = 0,
+              uint32_t plenty = 0xFFFFFFFFu);
 int features_impl(sfcnl_ctx ctx, int64_t n, const uint64_t *keys, const float *x, const float *y, const float *z,
                   const float *h, const int32_t *nnb, float box_edge, int target, uint16_t *feat,
                   const SegTable &seg);
@@ -430,10 +432,10 @@ __device__ __forceinline__ float h_step(float hc, int c, int dev, int target, fl
 }
 
 // From this count on h_step without a learned step gives the same radius for
-// every count (the cube-root step is clamped at a half from 8 targets on, the
-// bracket takes the radius alone).
+// every count (the cube-root step is clamped at a half from 8 targets on, with
+// room for the root's rounding; the bracket takes the radius alone).
 inline uint32_t h_plenty(int target, int tol) {
-    const int64_t p = std::max<int64_t>(9 * (int64_t)target, (int64_t)target + tol + 1);
+    const int64_t p = std::max<int64_t>(8 * (int64_t)target + target / 64 + 2, (int64_t)target + tol + 1);
     return p < 0x7FFFFFFF ? (uint32_t)p : 0xFFFFFFFFu;
 }
 

@@ -210,14 +210,8 @@ __global__ __launch_bounds__(kWave * kPassSplitMax) __attribute__((amdgpu_waves_
         if (a.split > 1) {
             // the entries with a tile of this part move up, in their order
             mv &= mine;
-            const uint64_t has = sfc_ballot(mv != 0u);
-            if (has == 0) continue;
-            const int rest = __builtin_popcountll(has);
-            const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u));
-            const int to = (mv != 0u ? below : rest + lane - below) << 2;  // a permutation of the lanes
-            mv = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)mv);
-            jv = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)jv);
-            cnt = (uint32_t)rest;
+            sfc_compact(mv != 0u, mv, jv, cnt);
+            if (cnt == 0) continue;
         }
         if constexpr (CS == 8) {
             entries8(mv, jv, cnt);

@@ -50,7 +50,25 @@ struct PassArgs {
     const uint32_t *gate;     // nullable: nothing to do when *gate <= gate_max
     uint32_t gate_max;
     uint32_t split;           // wavefronts that share a super-cluster (a block is then one super-cluster)
+    uint32_t plenty;          // counts from here on need not be complete (0xFFFFFFFF: all are)
 };
+
+// Bit k set: byte k of b is all ones.
+__device__ __forceinline__ uint32_t full_bytes(uint64_t b) {
+    b &= b >> 4;
+    b &= b >> 2;
+    b &= b >> 1;
+    return (uint32_t)(((b & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56);
+}
+
+// Sum over the lanes with the same low three bits.
+__device__ __forceinline__ int sum_high_lanes(int v) {
+    v += dpp_i<0x128>(v);  // row_ror 8
+    const auto r = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    v = (int)(r[0] + r[1]);
+    const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    return (int)(h[0] + h[1]);
+}
 
 // A quarter of the halved M4 shape as two clamped cubes: with
 // a = sat(c (1 - q)), c = 4^(-1/3), and u = sat(1/2 - q) (sat clamps to
@@ -107,7 +125,7 @@ __device__ __forceinline__ void tile_pair(float xj, float yj, float zj, float mj
 // with compression; six waves spilled more and ran 2 % slower). Cluster size
 // 16 holds four j-particles per lane; under the same cap it spills heavily,
 // so it keeps its own register count.
-template <int CS, bool kCompress, bool kMass, bool kCount, bool kPbc>
+template <int CS, bool kCompress, bool kMass, bool kCount, bool kPbc, bool kSome>
 __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_per_eu(CS == 16 ? 1 : 6))) void k_pass(PassArgs a) {
     constexpr int kNsub = kScSize / CS;
     constexpr int kNreg = CS == 8 ? 8 : 4;
@@ -116,20 +134,20 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
     const int lane = sfc_lane();
     // wave-uniform: keep the super-cluster index (and all derived from it) scalar
     uint32_t part;
-    const uint32_t s = wave_sc(a.split, part);
-    if (s >= a.nsc || (a.active && !a.active[s]) || (a.gate && *a.gate <= a.gate_max)) return;
+    const uint32_t s = wave_sc(kSome ? a.split : 1u, part);
+    if (s >= a.nsc || (kSome && a.active && !a.active[s]) || (kSome && a.gate && *a.gate <= a.gate_max)) return;
     const int64_t n = a.n;
     // the i-registers of this part: part, part + split, ... (each particle's
     // sum is formed by one wavefront in list order whatever the split)
     uint32_t regs = 0, mine = 0;  // registers, and their mask bits in an entry
-    for (uint32_t k = part; k < (uint32_t)kNreg; k += a.split) {
+    for (uint32_t k = part; kSome && k < (uint32_t)kNreg; k += a.split) {
         regs |= 1u << k;
         mine |= (CS == 4 ? 0xFu << (4 * k) : 1u << k);
     }
     const int jl = lane & (kGroup - 1);
 
-    // i particles; absent ones get a negative squared radius so that no pair
-    // is accepted
+    // i particles; absent ones, and in a restricted pass those that are not to
+    // be written, get a negative squared radius so that no pair is accepted
     float ix[kNreg], iy[kNreg], iz[kNreg], ih2[kNreg], ihinv[kNreg];
 #pragma unroll
     for (int k = 0; k < kNreg; k++) {
@@ -139,7 +157,7 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
         iy[k] = v ? a.y[i] : 0.0f;
         iz[k] = v ? a.z[i] : 0.0f;
         const float hh = v ? a.h[i] : 1.0f;
-        ih2[k] = v ? hh * hh : -1.0f;
+        ih2[k] = v && (!kSome || !a.p_active || a.p_active[i]) ? hh * hh : -1.0f;
         ihinv[k] = 1.0f / hh;
     }
     // acc[k] sums m_j f(q)/8 with f the spline shape (f(0) = 1)
@@ -169,7 +187,7 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
             mj[t] = kMass ? (vj ? a.m[jp] : 0.0f) : 1.0f;
         }
     };
-    for (uint32_t b0 = 0; b0 < nj; b0 += kWave) {
+    for (uint32_t b0 = 0; b0 < nj && (!kSome || mine); b0 += kWave) {
         const uint32_t cnt = nj - b0 < (uint32_t)kWave ? nj - b0 : (uint32_t)kWave;
         uint32_t jv;
         if (kCompress) {
@@ -183,14 +201,14 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
         jv += jbase;
         // software pipeline: the next entry's j-particles load while the
         // current entry's tiles run
-        uint64_t todo = sfc_ballot((mv & mine) != 0u);  // entries with a tile of this part
+        uint64_t todo = sfc_ballot(kSome ? (mv & mine) != 0u : (uint32_t)lane < cnt);  // entries with a tile to do
         if (todo == 0) continue;
         uint32_t e = (uint32_t)__builtin_ctzll(todo);
         uint32_t cj = sfc_readlane(jv, (int)e);
         float xj[kNj], yj[kNj], zj[kNj], mj[kNj];
         load_j(cj, xj, yj, zj, mj);
         while (todo) {
-            const uint32_t mk = sfc_readlane(mv, (int)e) & mine;
+            const uint32_t mk = sfc_readlane(mv, (int)e) & (kSome ? mine : 0xFFFFFFFFu);
             const uint32_t ccur = cj;
             float cx[kNj], cy[kNj], cz[kNj], cm[kNj];
 #pragma unroll
@@ -234,6 +252,16 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
                     }
             }
         }
+        if (kSome && kCount && a.plenty != 0xFFFFFFFFu) {
+            // i-clusters whose particles all have plenty need no more tiles
+#pragma unroll
+            for (int k = 0; k < kNreg; k++) {
+                float none = 0.0f;
+                int c = cnt_nb[k];
+                group_sum<kGroup>(none, c);
+                if (!sfc_ballot(!((uint32_t)c >= a.plenty || !(ih2[k] > 0.0f)))) mine &= ~(CS == 4 ? 0xFu << (4 * k) : 1u << k);
+            }
+        }
     }
     // sum the partials of each i-particle (the kGroup lanes sharing it)
 #pragma unroll
@@ -252,7 +280,7 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
         nb = jl == k ? cnt_nb[k] : nb;
     }
     const int64_t io = (int64_t)s * kScSize + ipart<CS>(jl, lane);
-    if (io < n && ((regs >> jl) & 1u) && (!a.p_active || a.p_active[io])) {
+    if (io < n && (!kSome || (((regs >> jl) & 1u) && (!a.p_active || a.p_active[io])))) {
         const float hh = a.h[io];
         const float hinv = 1.0f / hh;
         const float mi = kMass ? a.m[io] : 1.0f;
@@ -294,7 +322,7 @@ __device__ __forceinline__ void half_pair(float xj, float yj, float zj, float mj
     acc_j = add_shape<kMass>(acc_j, mi, r, rc, hjinv);
 }
 
-template <int CS, bool kCompress, bool kMass, bool kCount, bool kPbc>
+template <int CS, bool kCompress, bool kMass, bool kCount, bool kPbc, bool kPlenty>
 __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_per_eu(CS == 16 ? 1 : (CS == 8 ? 5 : 6)))) void k_pass_half(PassArgs a) {
     constexpr int kNsub = kScSize / CS;
     constexpr int kNreg = CS == 8 ? 8 : 4;
@@ -380,8 +408,8 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
     // (a part of a split super-cluster takes every split-th batch of a segment,
     // the segment's number b0 / 64 shifting the deal)
     auto half_entries8 = [&](uint32_t mvl, uint32_t jvl, uint32_t cnt, uint32_t b0) {
-        const uint32_t step = 8u * a.split;
-        const uint32_t first = a.split > 1 ? 8u * ((part + b0 / kWave) % a.split) : 0u;
+        const uint32_t step = kPlenty ? 8u : 8u * a.split;  // (kPlenty: dealt by drop_full)
+        const uint32_t first = !kPlenty && a.split > 1 ? 8u * ((part + b0 / kWave) % a.split) : 0u;
         if (first >= cnt) return;
         JLoad f;
         load_batch8(jvl, first, cnt, f);
@@ -437,10 +465,44 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
         }
     };
 
+    // kPlenty (cluster size 8): a tile is left out once all its i- and all its
+    // j-particles have plenty. i_full: the i-clusters that have, from this
+    // wave's sums and what the others have added; both only grow, so a count
+    // read late is a lower bound. (Counts reach plenty after a few segments of
+    // lists of thousands of entries: 16 condensed systems at a uniform guess,
+    // 14,387 pairs per particle on average at a target of 150: 11.2 -> 3.5 ms.)
+    uint32_t i_full = 0;
+    auto seen = [&](int64_t q) { return (uint32_t)__hip_atomic_load(&a.nnb[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    auto drop_full = [&](uint32_t &mvl, uint32_t &jvl, uint32_t &cnt, uint32_t b0) {
+        // the deal of half_entries8 here, by the entries' places before any is
+        // dropped (the parts see different counts)
+        if (a.split > 1 && (uint32_t)(lane >> 3) % a.split != (part + b0 / kWave) % a.split) mvl = 0u;
+        int own = 0;
+#pragma unroll
+        for (int k = 0; k < kNreg; k++) {
+            const int c = sum_high_lanes(cnt_nb[k]);
+            own = jq == k ? c : own;
+        }
+        const int64_t i = (int64_t)s * kScSize + lane;  // (= ipart_sym of register jq)
+        i_full = full_bytes(sfc_ballot(i >= n || (uint32_t)own + seen(i) >= a.plenty));
+        if (i_full == 0 && a.split == 1) return;
+        bool j_full = i_full != 0 && mvl != 0u;
+        uint32_t c[8];
+#pragma unroll
+        for (int r = 0; r < 8; r++) {
+            const int64_t q = (int64_t)jvl * 8 + r;
+            c[r] = seen(j_full && q < n ? q : n - 1);
+        }
+#pragma unroll
+        for (int r = 0; r < 8; r++) j_full = j_full && ((int64_t)jvl * 8 + r >= n || c[r] >= a.plenty);
+        if (j_full) mvl &= ~i_full;
+        sfc_compact(mvl != 0u, mvl, jvl, cnt);
+    };
+
     uint32_t p = off + (nj * (CS == 4 ? 2u : 1u) + 3u) / 4u;
     uint32_t prevj = 0xFFFFFFFFu;
     for (uint32_t b0 = 0; b0 < nj; b0 += kWave) {
-        const uint32_t cnt = nj - b0 < (uint32_t)kWave ? nj - b0 : (uint32_t)kWave;
+        uint32_t cnt = nj - b0 < (uint32_t)kWave ? nj - b0 : (uint32_t)kWave;
         uint32_t jv;
         if (kCompress) {
             jv = decode_segment(a.pool, p, cnt, prevj);
@@ -452,6 +514,7 @@ __global__ __launch_bounds__(kWave * kPassWavesMax) __attribute__((amdgpu_waves_
         prevj = sfc_readlane(jv, (int)cnt - 1);
         jv += jbase;
         if constexpr (CS == 8) {
+            if (kPlenty) drop_full(mv, jv, cnt, b0);
             half_entries8(mv, jv, cnt, b0);
             continue;
         }
@@ -605,32 +668,53 @@ __global__ __launch_bounds__(256) void k_decode(DecodeArgs a) {
     }
 }
 
+template <int CS, bool kPbc, bool kSome>
+void launch_pass_full(int variant, unsigned g, unsigned tpb, hipStream_t st, const PassArgs &a) {
+    switch (variant) {
+        case 7: k_pass<CS, true, true, true, kPbc, kSome><<<g, tpb, 0, st>>>(a); break;
+        case 6: k_pass<CS, true, true, false, kPbc, kSome><<<g, tpb, 0, st>>>(a); break;
+        case 5: k_pass<CS, true, false, true, kPbc, kSome><<<g, tpb, 0, st>>>(a); break;
+        case 4: k_pass<CS, true, false, false, kPbc, kSome><<<g, tpb, 0, st>>>(a); break;
+        case 3: k_pass<CS, false, true, true, kPbc, kSome><<<g, tpb, 0, st>>>(a); break;
+        case 2: k_pass<CS, false, true, false, kPbc, kSome><<<g, tpb, 0, st>>>(a); break;
+        case 1: k_pass<CS, false, false, true, kPbc, kSome><<<g, tpb, 0, st>>>(a); break;
+        default: k_pass<CS, false, false, false, kPbc, kSome><<<g, tpb, 0, st>>>(a); break;
+    }
+}
+
 template <int CS, bool kPbc>
 void launch_pass(int variant, unsigned g, unsigned tpb, hipStream_t st, const PassArgs &a) {
-    switch (variant) {
-        case 7: k_pass<CS, true, true, true, kPbc><<<g, tpb, 0, st>>>(a); break;
-        case 6: k_pass<CS, true, true, false, kPbc><<<g, tpb, 0, st>>>(a); break;
-        case 5: k_pass<CS, true, false, true, kPbc><<<g, tpb, 0, st>>>(a); break;
-        case 4: k_pass<CS, true, false, false, kPbc><<<g, tpb, 0, st>>>(a); break;
-        case 3: k_pass<CS, false, true, true, kPbc><<<g, tpb, 0, st>>>(a); break;
-        case 2: k_pass<CS, false, true, false, kPbc><<<g, tpb, 0, st>>>(a); break;
-        case 1: k_pass<CS, false, false, true, kPbc><<<g, tpb, 0, st>>>(a); break;
-        default: k_pass<CS, false, false, false, kPbc><<<g, tpb, 0, st>>>(a); break;
-    }
+    // shared, restricted or abridged lists (their checks cost 5 % where there is
+    // none of it: 4,000,037 particles 955 against 904 us)
+    if (a.split > 1 || a.active || a.p_active || a.gate || a.plenty != 0xFFFFFFFFu)
+        launch_pass_full<CS, kPbc, true>(variant, g, tpb, st, a);
+    else
+        launch_pass_full<CS, kPbc, false>(variant, g, tpb, st, a);
 }
 
 template <int CS, bool kPbc>
 void launch_pass_half(int variant, unsigned g, unsigned tpb, hipStream_t st, const PassArgs &a) {
     const size_t lds = CS == 8 ? (size_t)(tpb / kWave) * kPassLds8 : 0;
+    if constexpr (CS == 8) {
+        if (a.plenty != 0xFFFFFFFFu && (variant & 1)) {
+            switch (variant) {
+                case 7: k_pass_half<CS, true, true, true, kPbc, true><<<g, tpb, lds, st>>>(a); break;
+                case 5: k_pass_half<CS, true, false, true, kPbc, true><<<g, tpb, lds, st>>>(a); break;
+                case 3: k_pass_half<CS, false, true, true, kPbc, true><<<g, tpb, lds, st>>>(a); break;
+                default: k_pass_half<CS, false, false, true, kPbc, true><<<g, tpb, lds, st>>>(a); break;
+            }
+            return;
+        }
+    }
     switch (variant) {
-        case 7: k_pass_half<CS, true, true, true, kPbc><<<g, tpb, lds, st>>>(a); break;
-        case 6: k_pass_half<CS, true, true, false, kPbc><<<g, tpb, lds, st>>>(a); break;
-        case 5: k_pass_half<CS, true, false, true, kPbc><<<g, tpb, lds, st>>>(a); break;
-        case 4: k_pass_half<CS, true, false, false, kPbc><<<g, tpb, lds, st>>>(a); break;
-        case 3: k_pass_half<CS, false, true, true, kPbc><<<g, tpb, lds, st>>>(a); break;
-        case 2: k_pass_half<CS, false, true, false, kPbc><<<g, tpb, lds, st>>>(a); break;
-        case 1: k_pass_half<CS, false, false, true, kPbc><<<g, tpb, lds, st>>>(a); break;
-        default: k_pass_half<CS, false, false, false, kPbc><<<g, tpb, lds, st>>>(a); break;
+        case 7: k_pass_half<CS, true, true, true, kPbc, false><<<g, tpb, lds, st>>>(a); break;
+        case 6: k_pass_half<CS, true, true, false, kPbc, false><<<g, tpb, lds, st>>>(a); break;
+        case 5: k_pass_half<CS, true, false, true, kPbc, false><<<g, tpb, lds, st>>>(a); break;
+        case 4: k_pass_half<CS, true, false, false, kPbc, false><<<g, tpb, lds, st>>>(a); break;
+        case 3: k_pass_half<CS, false, true, true, kPbc, false><<<g, tpb, lds, st>>>(a); break;
+        case 2: k_pass_half<CS, false, true, false, kPbc, false><<<g, tpb, lds, st>>>(a); break;
+        case 1: k_pass_half<CS, false, false, true, kPbc, false><<<g, tpb, lds, st>>>(a); break;
+        default: k_pass_half<CS, false, false, false, kPbc, false><<<g, tpb, lds, st>>>(a); break;
     }
 }
 
@@ -660,11 +744,12 @@ using namespace sfcnl;
 int sfcnl::pass_impl(sfcnl_ctx ctx, int64_t n, int cs, int compress, int half, const uint32_t *d_sc_info,
                      const uint32_t *d_pool, const float *d_x, const float *d_y, const float *d_z, const float *d_h,
                      const float *d_m, float *d_rho, int32_t *d_nnb, const SegTable &seg, const Period &per,
-                     const uint32_t *active, const uint8_t *p_active, const uint32_t *gate, uint32_t gate_max) {
+                     const uint32_t *active, const uint8_t *p_active, const uint32_t *gate, uint32_t gate_max,
+                     uint32_t plenty) {
     if ((active || p_active || gate) && half)
         return set_err(ctx, SFCNL_E_ARG, "nlist_pass: a restricted pass needs the full list");
     PassArgs a{n, (uint32_t)((n + kScSize - 1) / kScSize), d_sc_info, d_pool, d_x, d_y, d_z, d_h, d_m, d_rho, d_nnb,
-               seg, per, active, p_active, gate, gate_max, 1u};
+               seg, per, active, p_active, gate, gate_max, 1u, plenty};
     a.split = pass_split(cs, half != 0, a.nsc);
     const int waves = a.split > 1 ? (int)a.split : ctx->pass_waves;
     const unsigned g = a.split > 1 ? a.nsc : blocks_for(a.nsc, waves);

@@ -62,6 +62,18 @@ __device__ __forceinline__ int ipart(int k, int lane) {
 
 constexpr int kPassSplitMax = 8;
 
+// Moves the list entries (mask, j-cluster) of the lanes with `keep` up, in
+// their order; cnt becomes their number.
+__device__ __forceinline__ void sfc_compact(bool keep, uint32_t &mv, uint32_t &jv, uint32_t &cnt) {
+    const uint64_t has = sfc_ballot(keep);
+    const int rest = sfc_popc(has);
+    const int below = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u));
+    const int to = (keep ? below : rest + sfc_lane() - below) << 2;  // a permutation of the lanes
+    mv = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)mv);
+    jv = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)jv);
+    cnt = (uint32_t)rest;
+}
+
 // Wavefronts that share a super-cluster's list. With one each, a pass takes
 // as long as its longest list until some thousand super-clusters fill the GPU.
 // A full list is split by i-clusters (every part decodes it and evaluates its

@@ -82,3 +82,31 @@ def test_finish_batch(env, max_iters):
         np.testing.assert_array_equal(out[mode][0], out[1][0])
         np.testing.assert_array_equal(out[mode][1], out[1][1])
         assert out[mode][2:] == out[1][2:]
+
+
+@pytest.mark.parametrize("cs,half,masses,period,n", [
+    (cs, half, masses, period, n) for n in (20011, 70000) for cs, half, masses, period in
+    [(8, True, False, False), (8, True, True, True), (8, False, True, False), (4, False, False, False),
+     (16, False, False, True), (4, True, False, False), (16, True, True, False)]] + [(8, True, False, False, 64 * 16384 + 1)])
+def test_plentiful_counts(env, cs, half, masses, period, n):
+    # rounds that may leave counts far above the target short, against rounds of one call each, which may not
+    sf, ctx, torch = env
+    print("plenty cs=%d half=%d m=%d per=%d n=%d" % (cs, half, masses, period, n), flush=True)
+    s = workloads.uniform_global(n, 8, target=20.0) if period else workloads.plummer(n, 9, target=20)
+    s.h = (s.h * np.exp(np.random.default_rng(3).uniform(0.0, np.log(8.0 if n < 100000 else 4.0), n))).astype(np.float32)
+    s.h = np.minimum(s.h, np.float32(0.4)) if period else s.h
+    keys, (xs, ys, zs, h0, ms) = _sorted(env, s, masses)
+    kw = dict(target=20, tol=1, m=ms if masses else None, cluster_size=cs, half=half, max_j_per_sc=4096,
+              period=(1.0, 1.0, 1.0) if period else None, recount=1)
+    out = []
+    for calls, rounds in ((1, 4), (4, 1)):
+        h, br = h0.clone(), torch.empty(2 * n, dtype=torch.float32, device="cuda")
+        for k in range(calls):
+            r = sf.h_iterate(ctx, keys, xs, ys, zs, h, max_iters=rounds, bracket=br, resume=k > 0, **kw)
+            if k == 0 and calls > 1:
+                print("  at or above nine targets: %.3f" % (r.nnb[:n] >= 180).float().mean().item(), flush=True)
+                assert (r.nnb[:n] >= 180).float().mean().item() > 0.1
+        out.append((h.cpu().numpy(), br.cpu().numpy(), r.nnb.cpu().numpy()[:n], r.rho.cpu().numpy()[:n].astype(np.float64)))
+    for k in range(3):
+        np.testing.assert_array_equal(out[0][k], out[1][k])
+    assert (np.abs(out[0][3] - out[1][3]) / out[1][3]).max() <= 2e-5
