@@ -49,6 +49,7 @@ namespace {
 // encoder: a block's resources are released only when its slowest wave ends,
 // and super-clusters differ in work; measured 10 % faster than four.
 constexpr int kWavesPerBlock = 1;
+constexpr uint32_t kStrictFrom = 128;  // tested clusters after which few listed ones matter (k_traverse's strict tests)
 constexpr int kStackCap = 148;  // 1 + 7 * 21 records at most
 constexpr int kSegCap = 80;     // words of one 64-value segment: 2 + (64 + 512 + 7) / 8
 constexpr int kQueueCap = 128;  // queued candidates (a ring): fewer than 16 left over, one box step adds at most 64
@@ -922,6 +923,28 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
     // tested.
     const uint64_t lt = sfc_lt_mask();
     uint32_t cand = 0, cn = 0, pos = 0, pos_end = 0;
+    // Eight particles in the outskirts of a condensed system have a box that
+    // holds its core, and the boxes let thousands of clusters through that no
+    // particle's own sphere comes near. Where few of the tested clusters joined
+    // the list, nodes and clusters are also tested against the particles one by
+    // one. (16 systems, half of them Plummer spheres: a traversal at converged
+    // radii 1.12 -> 0.39 ms, as its outermost super-clusters walked for 1 ms;
+    // the 1/r sphere of 4,000,037 particles 1439 -> 1143 us. From 128 clusters
+    // on with one in four listed: 512 and 2048 clusters 1209 and 1440 us for
+    // the sphere; one in two costs uniform systems 5 %.)
+    bool strict = false;
+    // does one of the `count` particles from p0 on come near the box?
+    auto any_near = [&](uint32_t p0, uint32_t count, const float4 &lo, const float4 &hi) SFC_INLINE {
+        bool near = false;
+#pragma unroll 1
+        for (uint32_t k = 0; k < count; k++) {
+            const uint32_t pc = p0 + k < n_last ? p0 + k : n_last;
+            float4 q = make_float4(a.x[pc], a.y[pc], a.z[pc], a.h[pc]);
+            if (gather && !a.p_active[pc]) q.w = 0.0f;
+            near = near || (q.w >= 0.0f && boxes_near<kPbc>(q, q, lo, hi, per));  // (NaN: a batch's padding)
+        }
+        return near;
+    };
     for (bool more = true; more;) {
         if (pos < pos_end) {
             const uint32_t room = kWave - cn, left = pos_end - pos;
@@ -963,8 +986,9 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
             const float4 lo = make_float4(l.x, l.y, l.z, gather ? 0.0f : l.w);  // own radius only when counting
             // a half list never needs a node that ends before the super-cluster
             const int gb = CS == 16 ? (lane & 7) >> 1 : lane & 7;
-            const bool hit = act && boxes_near<kPbc>(s_box[w][2 * gb], s_box[w][2 * gb + 1], lo, hi, per) &&
-                             (!half || crec.y > own_p0);
+            bool hit = act && boxes_near<kPbc>(s_box[w][2 * gb], s_box[w][2 * gb + 1], lo, hi, per) &&
+                       (!half || crec.y > own_p0);
+            if (strict) hit = hit && any_near(own_p0 + 8u * (uint32_t)(lane & 7), 8u, lo, hi);
             const uint32_t keep = nonzero_bytes(sfc_ballot(hit));
             const int cnt = __popc(keep);
             if (sp + cnt > kStackCap) {  // cannot happen in a valid octree (depth <= 21)
@@ -990,6 +1014,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
             for (int k = 0; k < kBoxes; k++)
                 hit = hit | boxes_near<kPbc>(s_box[w][2 * k], s_box[w][2 * k + 1], blo, u, per);
             hit = hit && (uint32_t)lane < cn;
+            if (strict && sfc_ballot(hit)) hit = hit && any_near(own_p0, kWave, blo, u);
             cn = 0;
             const uint64_t sv = sfc_ballot(hit);
             if (hit) queue[(qt + (uint32_t)sfc_popc(sv & lt)) % kQueueCap] = cand;
@@ -1009,6 +1034,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
             test_batch(c, cnt);
             qh += cnt;
         }
+        strict = qh > kStrictFrom && nj < qh / 4;
     }
     if (nj & (kWave - 1)) flush(nj & (kWave - 1));
     if (lane == 0) {

@@ -103,3 +103,17 @@ def test_counting_lists(env, cs):
     conv = np.abs(res.nnb.cpu().numpy() - 50) <= 1
     _, cnt = oracle.density(x, y, z, hs.cpu().numpy(), None, "grid")
     np.testing.assert_array_equal(cnt[conv], res.nnb.cpu().numpy()[conv])
+
+
+@pytest.mark.parametrize("cs", [4, 8, 16])
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("n,period", [(20011, None), (20011, (1.0, 1.0, 1.0)), (2500, (0.0, 1.0, 0.0))])
+def test_condensed_with_outskirts(env, cs, half, n, period):
+    """A dense core inside a thin halo: super-clusters whose boxes hold the core and whose spheres do not reach it (the
+    particle by particle tests), halo radii both far from and into the core."""
+    rng = np.random.default_rng(n + cs)
+    core = rng.random(n) < 0.9
+    p = np.where(core, 0.47 + 0.01 * rng.standard_normal((3, n)), rng.random((3, n)))
+    r = np.sqrt(((p - 0.47) ** 2).sum(0))
+    h = np.where(core, 0.002 + 0.1 * np.abs(r), rng.uniform(0.3, 1.05, n) * np.maximum(r, 0.02))
+    _check(env, p, np.minimum(h, 0.45), (0.0, 1.0, 0.0, 1.0, 0.0, 1.0), cs, half, period)
