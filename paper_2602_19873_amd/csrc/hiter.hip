@@ -72,10 +72,6 @@ __global__ __launch_bounds__(256) void k_h_update(int64_t n, const int32_t *__re
     }
 }
 
-// The moved total for the host's status read (the next round's list build
-// clears the status block; the total itself stays in the scan output).
-__global__ void k_publish_total(const uint32_t *total, uint32_t *status) { status[kStUnconverged] = *total; }
-
 constexpr uint32_t kAllCounts = 0xFFFFFFFFu;  // (pass_impl's plenty)
 
 // Once at most this many particles moved in a round, each gets a wavefront
@@ -201,7 +197,7 @@ extern "C" int sfcnl_h_iterate(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys,
         // others: counting lists of the moved particles, same octree
         rc = nlist_build_impl(ctx, n, d_keys, d_x, d_y, d_z, d_h, d_bbox, o, d_ws, ws_bytes, d_sc_info, d_pool,
                               pool_bytes, SegTable{}, true, &S.used_bytes, &S.max_nj, full ? nullptr : act.sc,
-                              full ? nullptr : act.p, !full);
+                              full ? nullptr : act.p, first ? kTreeNew : (full ? kTreeBoxes : kTreeKeep));
         if (rc) return rc;
         rc = pass_impl(ctx, n, o.cluster_size, o.compress, o.half, d_sc_info, d_pool, d_x, d_y, d_z, d_h, d_m,
                        d_rho, d_nnb, SegTable{}, make_period(o.period), full ? nullptr : act.sc,
@@ -220,10 +216,10 @@ extern "C" int sfcnl_h_iterate(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys,
         k_h_update<<<blocks_for(n, 256), 256, 0, strm>>>(n, d_nnb, d_h, br, it_opts->target, it_opts->tol, proposal,
                                                         ctx->d_status, SegTable{}, nullptr, act.sc, act.p);
         SFCNL_LAUNCHED(ctx);
-        rc = scan_u32(ctx, act.sc, act.scan, nsc, act.scan + nsc, act.scan_tmp);
+        // the moved total also for the host's status read (the next round's list
+        // build clears the status block)
+        rc = scan_u32(ctx, act.sc, act.scan, nsc, act.scan + nsc, act.scan_tmp, ctx->d_status + kStUnconverged);
         if (rc) return rc;
-        k_publish_total<<<1, 1, 0, strm>>>(act.scan + nsc, ctx->d_status);
-        SFCNL_LAUNCHED(ctx);
         SFCNL_HIP(ctx, hipMemcpyAsync(ctx->h_status + kStUnconverged, ctx->d_status + kStUnconverged,
                                       sizeof(uint32_t), hipMemcpyDeviceToHost, strm));
         SFCNL_HIP(ctx, hipStreamSynchronize(strm));
@@ -237,7 +233,8 @@ extern "C" int sfcnl_h_iterate(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys,
             int rc = clusters_impl(ctx, n, d_x, d_y, d_z, d_h, nl_opts->cluster_size, d_bbox, SegTable{});
             if (rc) return rc;
             rc = nlist_build_impl(ctx, n, d_keys, d_x, d_y, d_z, d_h, d_bbox, *nl_opts, d_ws, ws_bytes, d_sc_info,
-                                  d_pool, pool_bytes, SegTable{}, true, &S.used_bytes, &S.max_nj);
+                                  d_pool, pool_bytes, SegTable{}, true, &S.used_bytes, &S.max_nj, nullptr, nullptr,
+                                  kTreeBoxes);
             if (rc) return rc;
         }
         return SFCNL_OK;
@@ -301,7 +298,7 @@ int enqueue_round(sfcnl_ctx ctx, const RoundArgs &r, const sfcnl_nlist_opts &o, 
     const uint32_t *gate = restricted ? act.scan + n / kScSize : nullptr;
     rc = nlist_build_impl(ctx, n, r.keys, r.x, r.y, r.z, r.h, r.bbox, o, r.ws, r.ws_bytes, r.sc_info, r.pool,
                           r.pool_bytes, seg, false, nullptr, nullptr, restricted ? act.sc : nullptr,
-                          restricted ? act.p : nullptr, restricted, gate, 0u);
+                          restricted ? act.p : nullptr, restricted ? kTreeKeep : kTreeNew, gate, 0u);
     if (rc) return rc;
     rc = pass_impl(ctx, n, o.cluster_size, o.compress, o.half, r.sc_info, r.pool, r.x, r.y, r.z, r.h, r.m, r.rho,
                    r.nnb, seg, Period{}, restricted ? act.sc : nullptr, restricted ? act.p : nullptr, gate, 0u, plenty);
@@ -319,10 +316,9 @@ int enqueue_round(sfcnl_ctx ctx, const RoundArgs &r, const sfcnl_nlist_opts &o, 
     k_h_update<<<blocks_for(n, 256), 256, 0, ctx->stream>>>(n, r.nnb, r.h, r.br, r.it->target, r.it->tol, proposal,
                                                            ctx->d_status, seg, r.b->d_sys_moved, act.sc, act.p);
     SFCNL_LAUNCHED(ctx);
-    rc = scan_u32(ctx, act.sc, act.scan, n / kScSize, act.scan + n / kScSize, act.scan_tmp);
+    rc = scan_u32(ctx, act.sc, act.scan, n / kScSize, act.scan + n / kScSize, act.scan_tmp,
+                  ctx->d_status + kStUnconverged);
     if (rc) return rc;
-    k_publish_total<<<1, 1, 0, ctx->stream>>>(act.scan + n / kScSize, ctx->d_status);
-    SFCNL_LAUNCHED(ctx);
     return copy_round_status(ctx, r.b, slot);
 }
 
@@ -519,7 +515,8 @@ extern "C" int sfcnl_batch_h_iterate(sfcnl_ctx ctx, sfcnl_batch b, const uint64_
             int rc = clusters_impl(ctx, b->n_pad, d_x, d_y, d_z, d_h, nl_opts->cluster_size, d_bbox, seg);
             if (rc) return rc;
             rc = nlist_build_impl(ctx, b->n_pad, d_keys, d_x, d_y, d_z, d_h, d_bbox, *nl_opts, d_ws, ws_bytes,
-                                  d_sc_info, d_pool, pool_bytes, seg, true, &S.used_bytes, &S.max_nj);
+                                  d_sc_info, d_pool, pool_bytes, seg, true, &S.used_bytes, &S.max_nj, nullptr, nullptr,
+                                  kTreeBoxes);
             if (rc) return rc;
         }
         return SFCNL_OK;

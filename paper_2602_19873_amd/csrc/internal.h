@@ -118,10 +118,8 @@ struct Carver {
 // ---- device-wide exclusive scan of u32 (scan.hip) ----
 size_t scan_tmp_bytes(int64_t n);
 // out[i] = sum_{k<i} in[i]; *d_total = sum (may be null). in and out may alias.
-int scan_u32(sfcnl_ctx ctx, const uint32_t *in, uint32_t *out, int64_t n, uint32_t *d_total, void *tmp);
-// The same over the first min(*d_count, cap) words, the count known only on
-// the device (one block; the scan ends at that count, later words untouched).
-int scan_u32_dyn(sfcnl_ctx ctx, const uint32_t *in, uint32_t *out, const uint32_t *d_count, int64_t cap);
+int scan_u32(sfcnl_ctx ctx, const uint32_t *in, uint32_t *out, int64_t n, uint32_t *d_total, void *tmp,
+             uint32_t *d_total2 = nullptr);
 // Fills n u32 words with a value (a kernel, so it can sit inside a captured graph).
 int fill_u32(sfcnl_ctx ctx, uint32_t *p, int64_t n, uint32_t v);
 // The same over two arrays of n words in one launch (q may be null).
@@ -263,6 +261,8 @@ int octree_topology(sfcnl_ctx ctx, Octree &t, const uint64_t *keys, const SegTab
 int octree_geometry(sfcnl_ctx ctx, Octree &t, const float *x, const float *y, const float *z, const float *h,
                     const float4 *cluster_box, const SegTable &seg);
 
+enum TreeUse { kTreeNew, kTreeBoxes, kTreeKeep };
+
 // build_nlist without argument checks; `readback` waits for the stream and
 // reports capacity and input errors (otherwise the flags stay on the device).
 size_t nlist_ws_bytes(int64_t n, const sfcnl_nlist_opts &o, int nsys);
@@ -270,15 +270,17 @@ size_t nlist_ws_bytes(int64_t n, const sfcnl_nlist_opts &o, int nsys);
 // nonzero flag get a list (full lists only); the others get an empty one.
 // `p_active` (nullable, one flag per particle): the lists count only the
 // flagged particles' own-radius pairs (d2 < h_i^2), so boxes need no radii;
-// `reuse_tree` keeps the octree of the previous build (same keys, bucket and
-// cluster size: its positions and ranges are still exact).
+// `tree`: after a build in the same workspace with the same keys, positions,
+// bucket and cluster size, kTreeKeep takes that octree as it is (its ranges and
+// boxes are still exact, its radii need not be) and kTreeBoxes its nodes with
+// new boxes and radii.
 // `gate` (device word, nullable): when *gate <= gate_max every super-cluster
 // gets an empty list.
 int nlist_build_impl(sfcnl_ctx ctx, int64_t n, const uint64_t *keys, const float *x, const float *y, const float *z,
                      const float *h, const float *bbox, const sfcnl_nlist_opts &o, void *ws, size_t ws_bytes,
                      uint32_t *sc_info, uint32_t *pool, size_t pool_bytes, const SegTable &seg, bool readback,
                      size_t *used_bytes, int64_t *max_nj, const uint32_t *active = nullptr,
-                     const uint8_t *p_active = nullptr, bool reuse_tree = false, const uint32_t *gate = nullptr,
+                     const uint8_t *p_active = nullptr, TreeUse tree = kTreeNew, const uint32_t *gate = nullptr,
                      uint32_t gate_max = 0);
 // arrays for restricted rebuilds inside a build_nlist workspace
 struct ActiveWs {

@@ -63,13 +63,16 @@ __device__ __forceinline__ void seg_range(const SegTable &seg, int64_t p, int64_
 // for the levels (cdig, leaf level]). Block 0 also zeroes the nclear words at
 // clear (the caller's counters that must start at zero; this saves their own
 // launch).
-constexpr int kLeafPer = 4;
-constexpr int kLeafSpan = 256 * kLeafPer;
+// (kLeafPer 4 shares the window's ends; up to kLeafFew particles, where its
+// blocks leave most of the GPU idle, 1: 32,768 particles 8.6 -> 5.4 us.)
+constexpr int64_t kLeafFew = 262144;
 
+template <int kLeafPer>
 __global__ __launch_bounds__(256) void k_leaf_level(const uint64_t *__restrict__ keys, int64_t n, int bucket,
                                                     SegTable seg, int8_t *__restrict__ cdig,
                                                     int8_t *__restrict__ lleaf, uint32_t *__restrict__ blk,
                                                     uint32_t *__restrict__ clear, int nclear) {
+    constexpr int kLeafSpan = 256 * kLeafPer;
     __shared__ uint64_t s_key[kLeafSpan + 2 * kMaxBucket];  // keys b0 - bucket .. b0 + span + bucket - 1
     __shared__ int8_t s_tab[2][kLeafSpan + kMaxBucket];  // bytes (measured faster than words)
     __shared__ uint32_t s_w[kLeafPer][256 / kWave];
@@ -151,14 +154,21 @@ __global__ __launch_bounds__(256) void k_leaf_level(const uint64_t *__restrict__
 }
 
 // Node numbers in depth-first pre-order: the prefix of the node counts over
-// the particles (the block's offset from the scanned block totals, plus an
-// exclusive scan inside the block). node_at[p] is the first node starting at
-// p or after it; the nodes starting at p are written.
+// the particles (the block's offset, plus an exclusive scan inside the block).
+// node_at[p] is the first node starting at p or after it; the nodes starting
+// at p are written. kSum: blk holds the block totals and every block adds those
+// before its own (up to kSumBlocks of them, no slower; a scan launch takes 3 to
+// 7 us), the last writing the node count; else their prefix sums. Block 0
+// also clears the child slot counter.
+constexpr unsigned kSumBlocks = 1024;
+
+template <bool kSum>
 __global__ __launch_bounds__(256) void k_emit_nodes(const int8_t *__restrict__ cdig, const int8_t *__restrict__ lleaf,
                                                     const uint32_t *__restrict__ blk_off, int64_t n, uint32_t cap,
                                                     uint32_t *__restrict__ node_at, uint32_t *__restrict__ nfirst,
-                                                    uint8_t *__restrict__ nlevel, uint8_t *__restrict__ nleaf) {
-    __shared__ uint32_t s_w[256 / kWave];
+                                                    uint8_t *__restrict__ nlevel, uint8_t *__restrict__ nleaf,
+                                                    uint32_t *__restrict__ nnodes, uint32_t *__restrict__ nslots) {
+    __shared__ uint32_t s_w[256 / kWave], s_b[256 / kWave];
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int c = 0, L = 0;
     if (p < n) {
@@ -167,10 +177,19 @@ __global__ __launch_bounds__(256) void k_emit_nodes(const int8_t *__restrict__ c
     }
     const uint32_t cnt = c < L ? (uint32_t)(L - c) : 0u;
     const int lane = sfc_lane(), w = threadIdx.x / kWave;
+    uint32_t earlier = 0;  // (this thread's share of the blocks before)
+    if (kSum) {
+        for (uint32_t b = threadIdx.x; b < blockIdx.x; b += 256) earlier += blk_off[b];
+        earlier = sfc_incl_scan(earlier);
+        if (lane == kWave - 1) s_b[w] = earlier;
+    }
     const uint32_t inc = sfc_incl_scan(cnt);
     if (lane == kWave - 1) s_w[w] = inc;
     __syncthreads();
-    uint32_t before = blk_off[blockIdx.x];
+    uint32_t before = kSum ? (s_b[0] + s_b[1]) + (s_b[2] + s_b[3]) : blk_off[blockIdx.x];
+    if (kSum && blockIdx.x + 1 == gridDim.x && threadIdx.x == 0)
+        *nnodes = before + ((s_w[0] + s_w[1]) + (s_w[2] + s_w[3]));
+    if (blockIdx.x == 0 && threadIdx.x == 0) *nslots = 0u;
     for (int k = 0; k < w; k++) before += s_w[k];
     uint32_t k = before + inc - cnt;
     if (p >= n) return;
@@ -186,6 +205,12 @@ __global__ __launch_bounds__(256) void k_emit_nodes(const int8_t *__restrict__ c
 // grid strides over it.
 constexpr unsigned kNodeGrid = 2048;
 
+// kRangeLanes lanes find a node's end together: each step they probe as many
+// evenly spaced keys of what is left, a dependent load for every factor of
+// kRangeLanes + 1. 16 lanes up to kLeafFew particles (32,768: 7.2 us with one
+// lane, 5.1 with 16), 2 above, where more lanes fetch more lines than they
+// save steps (1,000,003: 10.0 with one, 13.2 with 16 lanes).
+template <int kRangeLanes>
 __global__ __launch_bounds__(256) void k_node_range(const uint64_t *__restrict__ keys, int64_t n,
                                                     const uint32_t *__restrict__ node_at,
                                                     const uint32_t *__restrict__ d_nnodes, uint32_t cap,
@@ -193,60 +218,76 @@ __global__ __launch_bounds__(256) void k_node_range(const uint64_t *__restrict__
                                                     const uint8_t *__restrict__ nlevel, uint32_t *__restrict__ nend,
                                                     uint32_t *__restrict__ nesc, uint32_t *status, SegTable seg) {
     const uint32_t nn = node_count(d_nnodes, cap);
-    const uint32_t k0 = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k0 == 0 && *d_nnodes > cap) atomicOr(&status[kStTree], 1u);
-    for (uint32_t k = k0; k < nn; k += gridDim.x * blockDim.x) {
-        uint32_t f = nfirst[k];
-        int L = nlevel[k];
+    if (blockIdx.x == 0 && threadIdx.x == 0 && *d_nnodes > cap) atomicOr(&status[kStTree], 1u);
+    const uint32_t q = threadIdx.x % kRangeLanes;
+    const uint32_t first = (uint32_t)sfc_lane() & ~(uint32_t)(kRangeLanes - 1);
+    // a node's lanes share k and so every branch below
+    for (uint32_t k = (blockIdx.x * blockDim.x + threadIdx.x) / kRangeLanes; k < nn;
+         k += gridDim.x * (blockDim.x / kRangeLanes)) {
+        const uint32_t f = nfirst[k];
+        const int L = nlevel[k];
         int64_t slo, shi;
         seg_range(seg, f, n, slo, shi);
         uint32_t end = (uint32_t)shi;  // a root spans its whole system
         if (L > 0) {
             const int shift = 3 * (kMaxLevel - L);
             const uint64_t pre = keys[f] >> shift;
+            // keys before lo are inside, those from hi on outside
             uint32_t lo = f + 1, hi = (uint32_t)shi;
             while (lo < hi) {
-                uint32_t mid = lo + (hi - lo) / 2;
-                if ((keys[mid] >> shift) == pre)
-                    lo = mid + 1;
-                else
-                    hi = mid;
+                const uint32_t step = (hi - lo) / (kRangeLanes + 1) + 1u;  // (at most hi - lo)
+                const uint32_t at = lo + (q + 1u) * step - 1u;  // (probe q, past the end: outside)
+                const bool in = at < hi && (keys[at] >> shift) == pre;
+                const uint32_t c = (uint32_t)__builtin_popcount((uint32_t)(sfc_ballot(in) >> first) & ((1u << kRangeLanes) - 1u));
+                // probes 0 .. c - 1 are inside, probe c is not
+                hi = c < (uint32_t)kRangeLanes && lo + (c + 1u) * step - 1u < hi ? lo + (c + 1u) * step - 1u : hi;
+                lo += c * step;
             }
             end = lo;
         }
-        nend[k] = end;
-        const uint32_t e = end == (uint32_t)n ? nn : node_at[end];
-        nesc[k] = e < nn ? e : nn;
+        if (q == 0) {
+            nend[k] = end;
+            const uint32_t e = end == (uint32_t)n ? nn : node_at[end];
+            nesc[k] = e < nn ? e : nn;
+        }
     }
 }
 
 // Children of every node (up to 8, in key order, by following escape indices
 // from the next node): each child learns its parent and its index among the
-// siblings; the parent's count goes to cbase for the prefix sum that places
-// the children in child slots.
+// siblings; cbase is the first of the node's child slots. A wave takes the
+// slots of its nodes' children together from the counter nslots, so 64 nodes
+// in a row have theirs in a row; the order of the waves' shares does not
+// matter to anyone (a prefix sum over the nodes took a launch of 6 to 7 us).
 __global__ __launch_bounds__(256) void k_children(const uint32_t *__restrict__ d_nnodes, uint32_t cap,
                                                   const uint8_t *__restrict__ nleaf, const uint32_t *__restrict__ nesc,
                                                   uint32_t *__restrict__ parent, uint8_t *__restrict__ pidx,
                                                   uint8_t *__restrict__ nnchild, uint32_t *__restrict__ cbase,
-                                                  uint32_t *status) {
+                                                  uint32_t *__restrict__ nslots, uint32_t *status) {
     const uint32_t nn = node_count(d_nnodes, cap);
-    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < nn; k += gridDim.x * blockDim.x) {
-        if (nleaf[k]) {
-            nnchild[k] = 0;
-            cbase[k] = 0;
-            continue;
+    const int lane = sfc_lane();
+    for (uint32_t k0 = blockIdx.x * blockDim.x + threadIdx.x - (uint32_t)lane; k0 < nn; k0 += gridDim.x * blockDim.x) {
+        const uint32_t k = k0 + (uint32_t)lane;
+        uint32_t i = 0;
+        if (k < nn && !nleaf[k]) {
+            uint32_t e = nesc[k], c = k + 1;
+            while (c < e && i < 8) {
+                parent[c] = k;
+                pidx[c] = (uint8_t)i;
+                i++;
+                c = nesc[c];
+            }
+            if (c < e || i == 0) atomicOr(&status[kStTree], 2u);  // an octree node has 1..8 children
         }
-        uint32_t e = nesc[k], c = k + 1;
-        int i = 0;
-        while (c < e && i < 8) {
-            parent[c] = k;
-            pidx[c] = (uint8_t)i;
-            i++;
-            c = nesc[c];
+        const uint32_t inc = sfc_incl_scan(i);
+        const uint32_t all = sfc_readlane(inc, kWave - 1);
+        uint32_t base = 0;
+        if (lane == 0 && all) base = atomicAdd(nslots, all);
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+        if (k < nn) {
+            nnchild[k] = (uint8_t)i;
+            cbase[k] = base + inc - i;
         }
-        if (c < e || i == 0) atomicOr(&status[kStTree], 2u);  // an octree node has 1..8 children
-        nnchild[k] = (uint8_t)i;
-        cbase[k] = (uint32_t)i;
     }
 }
 
@@ -515,24 +556,38 @@ int octree_topology(sfcnl_ctx ctx, Octree &t, const uint64_t *keys, const SegTab
     const unsigned gp = blocks_for(n, 256);
     // leaf levels and per-block node counts, their prefix sum (the total is
     // the node count), then the nodes in depth-first pre-order
-    k_leaf_level<<<blocks_for(n, kLeafSpan), 256, 0, st>>>(keys, n, B, seg, t.cdig, t.lleaf, t.blk, clear,
-                                                          clear ? nclear : 0);
+    if (n <= kLeafFew)
+        k_leaf_level<1><<<blocks_for(n, 256), 256, 0, st>>>(keys, n, B, seg, t.cdig, t.lleaf, t.blk, clear,
+                                                            clear ? nclear : 0);
+    else
+        k_leaf_level<4><<<blocks_for(n, 1024), 256, 0, st>>>(keys, n, B, seg, t.cdig, t.lleaf, t.blk, clear,
+                                                             clear ? nclear : 0);
     SFCNL_LAUNCHED(ctx);
-    int rc = scan_u32(ctx, t.blk, t.blk, (int64_t)gp, t.d_nnodes, t.scan_tmp);
-    if (rc) return rc;
     const uint32_t cap = t.node_cap;
-    k_emit_nodes<<<gp, 256, 0, st>>>(t.cdig, t.lleaf, t.blk, n, cap, t.node_at, t.nfirst, t.nlevel, t.nleaf);
+    uint32_t *const nslots = t.d_nnodes + 1;
+    if (gp <= kSumBlocks) {
+        k_emit_nodes<true><<<gp, 256, 0, st>>>(t.cdig, t.lleaf, t.blk, n, cap, t.node_at, t.nfirst, t.nlevel, t.nleaf,
+                                               t.d_nnodes, nslots);
+    } else {
+        const int rc = scan_u32(ctx, t.blk, t.blk, (int64_t)gp, t.d_nnodes, t.scan_tmp);
+        if (rc) return rc;
+        k_emit_nodes<false><<<gp, 256, 0, st>>>(t.cdig, t.lleaf, t.blk, n, cap, t.node_at, t.nfirst, t.nlevel, t.nleaf,
+                                                t.d_nnodes, nslots);
+    }
     SFCNL_LAUNCHED(ctx);
     // the node count is only known on the device: a fixed grid strides over it
     const unsigned gn = node_grid(t);
-    k_node_range<<<gn, 256, 0, st>>>(keys, n, t.node_at, t.d_nnodes, cap, t.nfirst, t.nlevel, t.nend, t.nesc,
+    if (n <= kLeafFew)
+        k_node_range<16><<<4 * gn, 256, 0, st>>>(keys, n, t.node_at, t.d_nnodes, cap, t.nfirst, t.nlevel, t.nend, t.nesc,
+                                     ctx->d_status, seg);
+    else
+        k_node_range<2><<<gn, 256, 0, st>>>(keys, n, t.node_at, t.d_nnodes, cap, t.nfirst, t.nlevel, t.nend, t.nesc,
                                      ctx->d_status, seg);
     SFCNL_LAUNCHED(ctx);
     k_children<<<gn, 256, 0, st>>>(t.d_nnodes, cap, t.nleaf, t.nesc, t.parent, t.pidx, t.nnchild, t.cbase,
-                                   ctx->d_status);
+                                   nslots, ctx->d_status);
     SFCNL_LAUNCHED(ctx);
-    // contiguous child slots: prefix sum of the child counts over the nodes
-    return scan_u32_dyn(ctx, t.cbase, t.cbase, t.d_nnodes, (int64_t)cap);
+    return SFCNL_OK;
 }
 
 int octree_geometry(sfcnl_ctx ctx, Octree &t, const float *x, const float *y, const float *z, const float *h,

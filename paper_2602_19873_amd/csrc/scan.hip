@@ -43,7 +43,8 @@ __global__ __launch_bounds__(kThreads) void k_reduce(const uint32_t *__restrict_
     if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
-__global__ __launch_bounds__(1024) void k_top(uint32_t *__restrict__ sums, int64_t nb, uint32_t *total) {
+__global__ __launch_bounds__(1024) void k_top(uint32_t *__restrict__ sums, int64_t nb, uint32_t *total,
+                                            uint32_t *total2) {
     __shared__ uint32_t s_w[1024 / kWave];
     const int t = threadIdx.x;
     int64_t per = (nb + 1023) / 1024;
@@ -67,7 +68,10 @@ __global__ __launch_bounds__(1024) void k_top(uint32_t *__restrict__ sums, int64
         sums[b] = run;
         run += v;
     }
-    if (t == 0 && total) *total = all;
+    if (t == 0) {
+        if (total) *total = all;
+        if (total2) *total2 = all;
+    }
 }
 
 __global__ __launch_bounds__(kThreads) void k_down(const uint32_t *in, uint32_t *out, int64_t n,
@@ -93,7 +97,7 @@ __global__ __launch_bounds__(kThreads) void k_down(const uint32_t *in, uint32_t 
 // staged through LDS: a coalesced load of the chunk, then thread t scans the
 // contiguous run [32 t, 32 t + 32) (one padding word after every 32 keeps
 // those runs on distinct banks), then a coalesced store; a carry joins the
-// chunks (in == out works). With d_count the length is min(*d_count, n).
+// chunks (in == out works).
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallPer = 32;
 constexpr int64_t kSmallChunk = (int64_t)kSmallThreads * kSmallPer;
@@ -101,15 +105,51 @@ constexpr int64_t kSmallScan = 4 * kSmallChunk;  // longest static scan done by 
 
 __device__ __forceinline__ int small_slot(int i) { return i + (i >> 5); }
 
+// Scan of at most kTinyScan words by one block, four consecutive ones a
+// thread: one load, one barrier. The chunk loop below takes 5.6 to 6 us even
+// for a few words (it walks all 32 words a thread has room for); this takes 3.
+constexpr int kTinyScan = 4 * kSmallThreads;
+
+__device__ __forceinline__ void scan_tiny(const uint32_t *in, uint32_t *out, int n, uint32_t *total, uint32_t *total2,
+                                          uint32_t *s_w) {
+    const int t = threadIdx.x, lane = sfc_lane(), w = t / kWave;
+    uint32_t v[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) v[k] = 4 * t + k < n ? in[4 * t + k] : 0u;
+    const uint32_t acc = (v[0] + v[1]) + (v[2] + v[3]);
+    const uint32_t inc = sfc_incl_scan(acc);
+    if (lane == kWave - 1) s_w[w] = inc;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int k = 0; k < kSmallThreads / kWave; k++) {
+        const uint32_t u = s_w[k];
+        if (k < w) before += u;
+        all += u;
+    }
+    uint32_t run = before + inc - acc;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        if (4 * t + k < n) out[4 * t + k] = run;
+        run += v[k];
+    }
+    if (t == 0) {
+        if (total) *total = all;
+        if (total2) *total2 = all;
+    }
+}
+
+__global__ __launch_bounds__(kSmallThreads) void k_scan_tiny(const uint32_t *in, uint32_t *out, int n, uint32_t *total,
+                                                             uint32_t *total2) {
+    __shared__ uint32_t s_w[kSmallThreads / kWave];
+    scan_tiny(in, out, n, total, total2, s_w);
+}
+
 __global__ __launch_bounds__(kSmallThreads) void k_scan_small(const uint32_t *in, uint32_t *out, int64_t n,
-                                                              const uint32_t *d_count, uint32_t *total) {
+                                                              uint32_t *total, uint32_t *total2) {
     __shared__ uint32_t s_v[kSmallChunk + kSmallChunk / kSmallPer];
     __shared__ uint32_t s_w[kSmallThreads / kWave];
     const int t = threadIdx.x;
-    if (d_count) {
-        const int64_t c = *d_count;
-        n = c < n ? c : n;
-    }
     const int lane = sfc_lane(), w = t / kWave;
     uint32_t carry = 0;
     for (int64_t c0 = 0; c0 < n; c0 += kSmallChunk) {
@@ -168,7 +208,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_scan_small(const uint32_t *in
         carry += all;
         __syncthreads();  // the next chunk overwrites s_v and s_w
     }
-    if (t == 0 && total) *total = carry;
+    if (t == 0) {
+        if (total) *total = carry;
+        if (total2) *total2 = carry;
+    }
 }
 
 // Fills of n words, four per thread: 16-byte stores where the array is
@@ -199,13 +242,23 @@ __global__ void k_fill2(uint32_t *p, uint32_t *q, int64_t n, uint32_t v, bool ve
 
 size_t scan_tmp_bytes(int64_t n) { return align_up((size_t)(blocks_for(n, kTile) + 1) * 4, 256); }
 
-int scan_u32(sfcnl_ctx ctx, const uint32_t *in, uint32_t *out, int64_t n, uint32_t *d_total, void *tmp) {
+int scan_u32(sfcnl_ctx ctx, const uint32_t *in, uint32_t *out, int64_t n, uint32_t *d_total, void *tmp,
+             uint32_t *d_total2) {
     if (n <= 0) {
+        if (d_total2) {
+            const int rc = fill_u32(ctx, d_total2, 1, 0);
+            if (rc) return rc;
+        }
         if (d_total) return fill_u32(ctx, d_total, 1, 0);
         return SFCNL_OK;
     }
+    if (n <= kTinyScan) {
+        k_scan_tiny<<<1, kSmallThreads, 0, ctx->stream>>>(in, out, (int)n, d_total, d_total2);
+        SFCNL_LAUNCHED(ctx);
+        return SFCNL_OK;
+    }
     if (n <= kSmallScan) {
-        k_scan_small<<<1, kSmallThreads, 0, ctx->stream>>>(in, out, n, nullptr, d_total);
+        k_scan_small<<<1, kSmallThreads, 0, ctx->stream>>>(in, out, n, d_total, d_total2);
         SFCNL_LAUNCHED(ctx);
         return SFCNL_OK;
     }
@@ -214,16 +267,9 @@ int scan_u32(sfcnl_ctx ctx, const uint32_t *in, uint32_t *out, int64_t n, uint32
     // k_down reads its tile before writing, so in == out is allowed
     k_reduce<<<nb, kThreads, 0, ctx->stream>>>(in, n, sums);
     SFCNL_LAUNCHED(ctx);
-    k_top<<<1, 1024, 0, ctx->stream>>>(sums, nb, d_total);
+    k_top<<<1, 1024, 0, ctx->stream>>>(sums, nb, d_total, d_total2);
     SFCNL_LAUNCHED(ctx);
     k_down<<<nb, kThreads, 0, ctx->stream>>>(in, out, n, sums);
-    SFCNL_LAUNCHED(ctx);
-    return SFCNL_OK;
-}
-
-int scan_u32_dyn(sfcnl_ctx ctx, const uint32_t *in, uint32_t *out, const uint32_t *d_count, int64_t cap) {
-    if (cap <= 0) return SFCNL_OK;
-    k_scan_small<<<1, kSmallThreads, 0, ctx->stream>>>(in, out, cap, d_count, nullptr);
     SFCNL_LAUNCHED(ctx);
     return SFCNL_OK;
 }

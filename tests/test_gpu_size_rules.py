@@ -1,0 +1,69 @@
+"""Sizes at which the build changes its launches: blocks of node counts and
+lists that add up their own offsets or take prefix sums, leaf levels in blocks
+of one or four groups, node ends by 16 or 2 lanes, and short scans. Lists bit
+for bit and counts exactly as the oracle's; h-iterations against its counts."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2602_19873_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    import paper_2602_19873_amd as sf
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    torch.cuda.set_device(0)
+    ctx = sf.Context(0)
+    yield sf, ctx, torch
+    ctx.close()
+
+
+@pytest.mark.parametrize("bucket", [8, 128, 256])
+@pytest.mark.parametrize("n", [1, 256, 257, 65536, 65537, 262144, 262145])
+def test_lists_at_size_rules(env, n, bucket):
+    sf, ctx, torch = env
+    print("size rules n=%d bucket=%d" % (n, bucket), flush=True)
+    s = workloads.uniform_varied(n, 40 + bucket, target=min(8.0, 0.5 * n)) if n > 1 else workloads.uniform_varied(1, 1, target=0.5)
+    pipe = sf.Pipeline(ctx, n, s.box, leaf_bucket=bucket, half=True)
+    nl = pipe.step(*(torch.from_numpy(np.ascontiguousarray(v)).cuda() for v in (s.x, s.y, s.z, s.h)))
+    host = [t.cpu().numpy() for t in pipe.sorted[:4]]
+    offs, jj, mm = oracle.cluster_list(*host, 8, "grid", half=True)
+    info, pool = oracle.encode_all(offs, jj, mm, 8, True)
+    np.testing.assert_array_equal(nl.sc_info.cpu().numpy().view(np.uint32), info)
+    assert nl.used_bytes == 4 * len(pool)
+    np.testing.assert_array_equal(nl.pool.cpu().numpy().view(np.uint32)[:len(pool)], pool)
+    _, cnt = oracle.density(*host)
+    np.testing.assert_array_equal(pipe.nnb.cpu().numpy()[:n], cnt)
+
+
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("n", [65537, 262144, 262145])
+def test_iteration_at_size_rules(env, n, half):
+    # radii of every round and the closing list (new boxes on the first round's nodes)
+    sf, ctx, torch = env
+    print("size rules iteration n=%d half=%d" % (n, half), flush=True)
+    s = workloads.uniform_global(n, 50, target=25.0)
+    f = [torch.from_numpy(np.ascontiguousarray(v)).cuda() for v in (s.x, s.y, s.z, s.h)]
+    keys, perm = sf.sfc_sort(ctx, *f[:3], s.box)
+    xs, ys, zs, h0 = sf.sfc_gather(ctx, perm, f)
+    out = []
+    for recount in (0, 1):
+        h = h0.clone()
+        r = sf.h_iterate(ctx, keys, xs, ys, zs, h, target=16, tol=1, half=half, recount=recount)
+        assert r.converged
+        out.append((h.cpu().numpy(), r.nnb.cpu().numpy()[:n], r.iters, r.moved, r.nl.sc_info.cpu().numpy(),
+                    r.nl.pool.cpu().numpy()[:r.nl.used_bytes // 4]))
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
+    host = [v.cpu().numpy() for v in (xs, ys, zs)]
+    _, cnt = oracle.density(*host, out[0][0])
+    np.testing.assert_array_equal(out[0][1], cnt)
+    offs, jj, mm = oracle.cluster_list(*host, out[0][0], 8, "grid", half=half)
+    info, pool = oracle.encode_all(offs, jj, mm, 8, True)
+    np.testing.assert_array_equal(out[0][4].view(np.uint32), info)
+    np.testing.assert_array_equal(out[0][5].view(np.uint32), pool)
