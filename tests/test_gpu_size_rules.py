@@ -67,3 +67,42 @@ def test_iteration_at_size_rules(env, n, half):
     info, pool = oracle.encode_all(offs, jj, mm, 8, True)
     np.testing.assert_array_equal(out[0][4].view(np.uint32), info)
     np.testing.assert_array_equal(out[0][5].view(np.uint32), pool)
+
+
+@pytest.mark.parametrize("kind", ["uniform", "equal", "ties"])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1023, 1025, 4097, 8191, 8192, 8193])
+def test_small_sort(env, n, kind):
+    # one launch up to 8192 particles, the radix passes above; equal keys keep their order
+    sf, ctx, torch = env
+    rng = np.random.default_rng(n)
+    p = rng.random((3, n))
+    if kind == "equal":
+        p[:] = 0.3
+    elif kind == "ties":
+        p = np.floor(p * 4.0) / 4.0 + rng.random((3, n)) * 1e-9
+    p = p.astype(np.float32)
+    print("small sort n=%d %s" % (n, kind), flush=True)
+    keys, perm = sf.sfc_sort(ctx, *(torch.from_numpy(np.ascontiguousarray(v)).cuda() for v in p), workloads.UNIT_BOX)
+    ref = oracle.hilbert_keys(*p, workloads.UNIT_BOX)
+    order = np.argsort(ref, kind="stable")
+    np.testing.assert_array_equal(keys.cpu().numpy().view(np.uint64)[:n], ref[order])
+    np.testing.assert_array_equal(perm.cpu().numpy().view(np.uint32)[:n], order)
+
+
+@pytest.mark.parametrize("nf", [1, 4, 5, 8])
+@pytest.mark.parametrize("n", [1, 262144, 262145])
+def test_gather_at_size_rules(env, n, nf):
+    sf, ctx, torch = env
+    g = torch.Generator(device="cuda").manual_seed(n + nf)
+    perm = torch.randperm(n, generator=g, device="cuda")
+    f = [torch.rand(n, generator=g, device="cuda") for _ in range(nf)]
+    ws = torch.empty(sf.sfc_gather_workspace(n), dtype=torch.uint8, device="cuda")
+    out = sf.sfc_gather(ctx, perm.to(torch.int32), f, ws=ws)
+    for a, b in zip(out, f):
+        assert torch.equal(a[:n], b[perm])
+    # in place, four fields at a time
+    ref = [v.clone() for v in f[:4]]
+    if nf > 1:
+        sf.sfc_gather(ctx, perm.to(torch.int32), f[:4], outs=f[:4], ws=ws)
+        for a, b in zip(f, ref):
+            assert torch.equal(a, b[perm])
