@@ -258,10 +258,11 @@ int octree_build(sfcnl_ctx ctx, Octree &t, const uint64_t *keys, const float *x,
 // sorted keys alone, then the node boxes from the cluster boxes and particles.
 int octree_topology(sfcnl_ctx ctx, Octree &t, const uint64_t *keys, const SegTable &seg, uint32_t *clear = nullptr,
                     int nclear = 0);
+int box_levels_build(sfcnl_ctx ctx, Octree &t, const float4 *cluster_box, const float4 **lvl);
 int octree_geometry(sfcnl_ctx ctx, Octree &t, const float *x, const float *y, const float *z, const float *h,
                     const float4 *cluster_box, const SegTable &seg);
 
-enum TreeUse { kTreeNew, kTreeBoxes, kTreeKeep };
+enum TreeUse { kTreeNew, kTreeBoxes, kTreeKeep, kTreeNone };
 
 // build_nlist without argument checks; `readback` waits for the stream and
 // reports capacity and input errors (otherwise the flags stay on the device).
@@ -273,7 +274,7 @@ size_t nlist_ws_bytes(int64_t n, const sfcnl_nlist_opts &o, int nsys);
 // `tree`: after a build in the same workspace with the same keys, positions,
 // bucket and cluster size, kTreeKeep takes that octree as it is (its ranges and
 // boxes are still exact, its radii need not be) and kTreeBoxes its nodes with
-// new boxes and radii.
+// new boxes and radii. kTreeNone: nobody reads the tree after the build.
 // `gate` (device word, nullable): when *gate <= gate_max every super-cluster
 // gets an empty list.
 int nlist_build_impl(sfcnl_ctx ctx, int64_t n, const uint64_t *keys, const float *x, const float *y, const float *z,

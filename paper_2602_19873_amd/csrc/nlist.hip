@@ -172,6 +172,7 @@ struct TravArgs {
     const float4 *bbox;
     const float4 *cs_box;  // octree child slots (slot 0 = root)
     const uint4 *cs_rec;
+    const float4 *lvl1;    // kDirect: boxes of 8 clusters (nullable; cs_box is then the root box alone)
     uint32_t nslots;       // capacity of the slot arrays
     SegTable seg;          // batched systems (empty for one system)
     Period per;            // periodic axes (used by the kPbc kernels)
@@ -414,26 +415,52 @@ __device__ __forceinline__ uint32_t candidate_mask(uint32_t seen, int lane) {
     }
 }
 
+// kDirect: a small system without its octree, kDirect waves of a block sharing
+// a super-cluster. Each takes its share of all groups of 8 clusters, tests the
+// groups' boxes (lvl1, nullable: every group passes), the clusters' boxes and
+// the pairs of what comes near, and leaves the masks in LDS, from which the
+// first wave makes the list. The octree's ten dependent launches and the walk's
+// chain of node reads by one wave take longer than testing every group, whose
+// work grows with n^2. Whole steps, octree against this, clusters of 8 in us:
+// 1,000 particles 111 / 52, 32,768 201 / 123, 65,536 245 / 161, 131,072
+// 285 / 236, 200,000 312 / 395, periodic 50,000 246 / 176, 200,000 378 / 485;
+// clusters of 4: 65,536 278 / 220, 131,072 342 / 678; of 16: 131,072 344 / 255,
+// 262,144 416 / 412. Group boxes (a launch) and 4 instead of 8 waves pay from
+// kDirectFew on: 24,000 123 without, 125 with; 65,536 183 without, 162 with.
+constexpr int kDirectWavesFew = 8, kDirectWavesMany = 4;
+constexpr int64_t kDirectFew = 32768;  // particles: above, 4 waves and group boxes
+constexpr int64_t direct_max(int cs) { return cs == 4 ? 65536 : (cs == 8 ? 131072 : 196608); }
+
 // Five waves per SIMD: at most 96 VGPRs, and at most 7,680 bytes of LDS (four
 // waves: 0.56 against 0.53 ms on the 2M box).
-template <int CS, bool kHalf, bool kPbc>
-__global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(5, 5))) void k_traverse(TravArgs a) {
+template <int CS, bool kHalf, bool kPbc, int kDirect>
+__global__ __launch_bounds__(kWave * (kDirect ? kDirect : kWavesPerBlock)) __attribute__((amdgpu_waves_per_eu(5, 5))) void k_traverse(TravArgs a) {
     using S = Shape<CS>;
     constexpr int kNsub = S::kNsub;
     constexpr int kBatch = kWave / CS;               // candidates per batch of 64 j-particles
     constexpr int kBoxes = kNsub < 8 ? kNsub : 8;    // i-boxes of the box tests (CS = 4: of two clusters each)
     constexpr bool kLaneTiles = CS == 8;
-    __shared__ uint4 s_stack[kWavesPerBlock][kStackCap];
-    __shared__ uint32_t s_queue[kWavesPerBlock][kQueueCap];
-    __shared__ float4 s_box[kWavesPerBlock][2 * kBoxes];
-    __shared__ uint2 s_ent[kWavesPerBlock][kBatch];
-    __shared__ uint4_t s_a[kWavesPerBlock][4][kWave];  // the filter's i-operands: less[0], less[1], plain[0], plain[1]
+    constexpr int kW = kDirect ? kDirect : kWavesPerBlock;
+    __shared__ uint4 s_stack[kDirect ? 1 : kW][kDirect ? 1 : kStackCap];
+    __shared__ uint32_t s_queue[kW][kQueueCap];
+    __shared__ float4 s_box[kW][2 * kBoxes];
+    __shared__ uint2 s_ent[kDirect ? 1 : kW][kBatch];
+    using Mask = typename std::conditional<CS == 4, uint16_t, uint8_t>::type;
+    __shared__ uint32_t s_grp[kDirect ? kW : 1][kDirect ? kWave : 1];
+    extern __shared__ uint32_t s_dyn[];  // kDirect: every cluster's mask
+    Mask *const s_mask = reinterpret_cast<Mask *>(s_dyn);
+    __shared__ uint4_t s_a[kW][4][kWave];  // the filter's i-operands: less[0], less[1], plain[0], plain[1]
     const int lane = sfc_lane();
     const int w = threadIdx.x / kWave;
     // wave-uniform: keep the super-cluster index (and all derived from it) scalar
-    const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)(xcd_remap(blockIdx.x, gridDim.x) * kWavesPerBlock + w));
+    const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane(
+        (int)(kDirect ? xcd_remap(blockIdx.x, gridDim.x) : xcd_remap(blockIdx.x, gridDim.x) * kWavesPerBlock + w));
     if (s >= a.nsc) return;
-    if ((a.active && !a.active[s]) || (a.gate && *a.gate <= a.gate_max)) {  // no list for this super-cluster
+    if (kDirect) {
+        const uint32_t words = (a.nclu * (uint32_t)sizeof(Mask) + 3u) / 4u;
+        for (uint32_t k = threadIdx.x; k < words; k += kW * kWave) s_dyn[k] = 0u;
+        __syncthreads();
+    } else if ((a.active && !a.active[s]) || (a.gate && *a.gate <= a.gate_max)) {  // no list for this super-cluster
         if (sfc_lane() == 0) {
             a.sc_nj[s] = 0;
             a.sc_words[s] = 0;
@@ -441,7 +468,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
         return;
     }
     const int64_t n = a.n;
-    const bool gather = a.p_active != nullptr;
+    const bool gather = !kDirect && a.p_active != nullptr;
     const uint32_t own_c0 = s * kNsub;   // first i-cluster of this super-cluster
     const uint32_t own_p0 = s * kScSize; // and its first particle
     // i-particle `lane`; absent ones are put far away so that no test accepts them
@@ -596,13 +623,15 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
 
     // stack of node records {first, end, child count (0 = leaf), first child
     // slot}; a node is pushed only after its box passed the test
-    uint4 *stack = s_stack[w];
+    uint4 *stack = s_stack[kDirect ? 0 : w];
     uint32_t *queue = s_queue[w];
     int sp = 0;
     // the tree of this super-cluster's system; list entries are cluster
     // indices relative to the system's first cluster
     uint32_t jbase = 0;
-    if (a.seg.on()) {
+    if (kDirect) {
+        // no tree
+    } else if (a.seg.on()) {
         const int sy = a.seg.sc_sys[s];
         jbase = a.seg.pbase[sy] / CS;
         if (lane == 0) stack[0] = a.seg.roots[sy];
@@ -679,8 +708,8 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
     // (g, l) takes i-particle l of its tile and steps through the 8
     // j-particles of its candidate, two of which it holds while the quad's
     // other lanes supply the rest (DPP operands).
-    __shared__ uint32_t s_tile[kWavesPerBlock][kLaneTiles ? 64 : 1];
-    __shared__ uint64_t s_hits[kWavesPerBlock][kLaneTiles ? 8 : 1];
+    __shared__ uint32_t s_tile[kW][kLaneTiles ? 64 : 1];
+    __shared__ uint64_t s_hits[kW][kLaneTiles ? 8 : 1];
     if constexpr (kLaneTiles) s_tile[w][lane] = 0u;  // entries past a batch's tiles: some valid tile
     auto particle = [&](uint32_t p, bool i_side) SFC_INLINE {
         const bool v = p < (uint64_t)n;
@@ -889,16 +918,20 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
         // the candidates with a nonempty mask join the list in queue order
         // (lane (nj + rank) % 64 of ej / em)
         if (!used) mq = 0u;
+        if constexpr (kDirect) {
+            if (mq) s_mask[cj] = (Mask)mq;
+            return;
+        }
         const uint64_t ne = sfc_ballot(mq != 0u);
         if (ne) {
             const uint32_t c = (uint32_t)sfc_popc(ne);
-            if (mq) s_ent[w][__builtin_amdgcn_mbcnt_lo((uint32_t)ne, 0u)] = make_uint2(cj - jbase, mq);
+            if (mq) s_ent[kDirect ? 0 : w][__builtin_amdgcn_mbcnt_lo((uint32_t)ne, 0u)] = make_uint2(cj - jbase, mq);
             wave_sync();
             const uint32_t base = nj & (kWave - 1);
             const uint32_t first = c < kWave - base ? c : kWave - base;
             const uint32_t d = (uint32_t)lane - base;
             if (d < first) {
-                const uint2 e = s_ent[w][d];
+                const uint2 e = s_ent[kDirect ? 0 : w][d];
                 ej = e.x;
                 em = e.y;
             }
@@ -906,7 +939,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
             if ((nj & (kWave - 1)) == 0) flush(kWave);
             if (c > first) {
                 if ((uint32_t)lane < c - first) {
-                    const uint2 e = s_ent[w][first + lane];
+                    const uint2 e = s_ent[kDirect ? 0 : w][first + lane];
                     ej = e.x;
                     em = e.y;
                 }
@@ -922,6 +955,81 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
     // LDS), the survivors join the queue in order and its whole batches are
     // tested.
     const uint64_t lt = sfc_lt_mask();
+    if constexpr (kDirect) {
+        // the waves take the groups of 8 clusters by turns, 64 at a time
+        const uint32_t c_first = half ? own_c0 : 0u;  // (j-clusters wholly before i: no j > i)
+        const uint32_t g_first = c_first / 8u, ngrp = (a.nclu + 7u) / 8u;
+        for (uint32_t k0 = 0; g_first + k0 * kW + (uint32_t)w < ngrp; k0 += kWave) {
+            const uint32_t g = g_first + (k0 + (uint32_t)lane) * kW + (uint32_t)w;
+            bool gin = g < ngrp;
+            if (a.lvl1) {
+                const float4 l = a.lvl1[2 * (size_t)(gin ? g : 0u)], u = a.lvl1[2 * (size_t)(gin ? g : 0u) + 1];
+                bool hit = false;
+#pragma unroll
+                for (int k = 0; k < kBoxes; k++)
+                    hit = hit | boxes_near<kPbc>(s_box[w][2 * k], s_box[w][2 * k + 1], l, u, per);
+                gin = gin && hit;
+            }
+            const uint64_t gs = sfc_ballot(gin);
+            const uint32_t ng = (uint32_t)sfc_popc(gs);
+            if (gin) s_grp[w][sfc_popc(gs & lt)] = g;
+            wave_sync();
+            for (uint32_t e0 = 0; e0 < ng; e0 += 8) {
+                const uint32_t e = e0 + (uint32_t)(lane >> 3);
+                const uint32_t c = 8u * s_grp[w][e < ng ? e : 0u] + (uint32_t)(lane & 7);
+                const bool in = e < ng && c < a.nclu && c >= c_first;
+                const float4 l = a.bbox[2 * (size_t)(in ? c : 0u)], u = a.bbox[2 * (size_t)(in ? c : 0u) + 1];
+                bool hit = false;
+#pragma unroll
+                for (int k = 0; k < kBoxes; k++)
+                    hit = hit | boxes_near<kPbc>(s_box[w][2 * k], s_box[w][2 * k + 1], l, u, per);
+                const uint64_t sv = sfc_ballot(hit && in);
+                if (hit && in) queue[(qt + (uint32_t)sfc_popc(sv & lt)) % kQueueCap] = c;
+                qt += (uint32_t)sfc_popc(sv);
+                wave_sync();
+                for (; qt - qh >= (uint32_t)kBatch; qh += kBatch) {
+                    JLoad f;
+                    load_batch(qh, kBatch, f);
+                    test_batch(f, kBatch);
+                }
+            }
+            wave_sync();  // the next groups overwrite s_grp
+        }
+        if (qt != qh) {
+            JLoad f;
+            load_batch(qh, qt - qh, f);
+            test_batch(f, qt - qh);
+        }
+        __syncthreads();
+        if (w != 0) return;
+        // the list: 64 clusters at a time, those with a mask to the lanes that
+        // follow the entries so far (lane e % 64 for entry e)
+        for (uint32_t c0 = c_first; c0 < a.nclu; c0 += kWave) {
+            const uint32_t c = c0 + (uint32_t)lane;
+            const uint32_t m = c < a.nclu ? s_mask[c] : 0u;
+            const uint64_t ne = sfc_ballot(m != 0u);
+            if (ne == 0) continue;
+            const uint32_t cnt = (uint32_t)sfc_popc(ne), base = nj & (kWave - 1), below = (uint32_t)sfc_popc(ne & lt);
+            const uint32_t to = (base + (m ? below : cnt + (uint32_t)lane - below)) & (kWave - 1);  // a permutation
+            const uint32_t pj = (uint32_t)__builtin_amdgcn_ds_permute((int)(to << 2), (int)c);
+            const uint32_t pm = (uint32_t)__builtin_amdgcn_ds_permute((int)(to << 2), (int)m);
+            const uint32_t first = cnt < kWave - base ? cnt : kWave - base;
+            const uint32_t d = (uint32_t)lane - base;
+            if (d < first) {
+                ej = pj;
+                em = pm;
+            }
+            nj += first;
+            if ((nj & (kWave - 1)) == 0) flush(kWave);
+            if (cnt > first) {
+                if ((uint32_t)lane < cnt - first) {
+                    ej = pj;
+                    em = pm;
+                }
+                nj += cnt - first;
+            }
+        }
+    } else {
     uint32_t cand = 0, cn = 0, pos = 0, pos_end = 0;
     // Eight particles in the outskirts of a condensed system have a box that
     // holds its core, and the boxes let thousands of clusters through that no
@@ -1035,6 +1143,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock) __attribute__((amdgpu_waves
             qh += cnt;
         }
         strict = qh > kStrictFrom && nj < qh / 4;
+    }
     }
     if (nj & (kWave - 1)) flush(nj & (kWave - 1));
     if (lane == 0) {
@@ -1224,15 +1333,39 @@ void carve_nlist(Carver &cv, NlistWs &ws, int64_t n, const sfcnl_nlist_opts &o, 
     ws.plist = cv.take<uint32_t>((size_t)n);
 }
 
-template <bool kPbc>
-void launch_traverse(int cs, int half, unsigned gb, hipStream_t st, const TravArgs &ta) {
-    if (cs == 4) {
-        if (half) k_traverse<4, true, kPbc><<<gb, kWave * kWavesPerBlock, 0, st>>>(ta); else k_traverse<4, false, kPbc><<<gb, kWave * kWavesPerBlock, 0, st>>>(ta);
-    } else if (cs == 16) {
-        if (half) k_traverse<16, true, kPbc><<<gb, kWave * kWavesPerBlock, 0, st>>>(ta); else k_traverse<16, false, kPbc><<<gb, kWave * kWavesPerBlock, 0, st>>>(ta);
-    } else {
-        if (half) k_traverse<8, true, kPbc><<<gb, kWave * kWavesPerBlock, 0, st>>>(ta); else k_traverse<8, false, kPbc><<<gb, kWave * kWavesPerBlock, 0, st>>>(ta);
+template <int CS, bool kPbc, int kDirect>
+void launch_direct(int half, unsigned nsc, hipStream_t st, const TravArgs &ta) {
+    const size_t lds = align_up((size_t)ta.nclu * (CS == 4 ? 2 : 1), 16);
+    if (half)
+        k_traverse<CS, true, kPbc, kDirect><<<nsc, kWave * kDirect, lds, st>>>(ta);
+    else
+        k_traverse<CS, false, kPbc, kDirect><<<nsc, kWave * kDirect, lds, st>>>(ta);
+}
+
+template <int CS, bool kPbc>
+void launch_traverse_cs(int half, bool direct, unsigned nsc, hipStream_t st, const TravArgs &ta) {
+    if (direct) {
+        if (ta.n <= kDirectFew)
+            launch_direct<CS, kPbc, kDirectWavesFew>(half, nsc, st, ta);
+        else
+            launch_direct<CS, kPbc, kDirectWavesMany>(half, nsc, st, ta);
+        return;
     }
+    const unsigned gb = blocks_for(nsc, kWavesPerBlock);
+    if (half)
+        k_traverse<CS, true, kPbc, 0><<<gb, kWave * kWavesPerBlock, 0, st>>>(ta);
+    else
+        k_traverse<CS, false, kPbc, 0><<<gb, kWave * kWavesPerBlock, 0, st>>>(ta);
+}
+
+template <bool kPbc>
+void launch_traverse(int cs, int half, bool direct, unsigned nsc, hipStream_t st, const TravArgs &ta) {
+    if (cs == 4)
+        launch_traverse_cs<4, kPbc>(half, direct, nsc, st, ta);
+    else if (cs == 16)
+        launch_traverse_cs<16, kPbc>(half, direct, nsc, st, ta);
+    else
+        launch_traverse_cs<8, kPbc>(half, direct, nsc, st, ta);
 }
 
 // Periodic axes: the particles must span less than one period (the root box
@@ -1350,23 +1483,35 @@ int sfcnl::nlist_build_impl(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys, co
     uint32_t *const st_clear = ctx->d_status + kStPoolOverflow;
     const int st_nclear = kStatusAlloc - kStPoolOverflow;
     int rc = SFCNL_OK;
+    // small systems need no octree for their lists
+    const bool direct = n <= direct_max(cs) && !seg.on() && !active && !p_active && !gate;
+    const bool kept = tree == kTreeKeep;
+    if (tree == kTreeNone && !direct) tree = kTreeNew;
+    if (tree == kTreeBoxes && direct) tree = kTreeNone;  // (its radii are read by walks of whole lists only)
     if (tree != kTreeNew) {
         rc = fill_u32(ctx, st_clear, st_nclear, 0);
         if (rc) return rc;
     }
-    if (tree != kTreeKeep) {
-        const float4 *const boxes = reinterpret_cast<const float4 *>(d_bbox);
-        prof_mark(ctx, kStageOctree, false);
+    const float4 *const boxes = reinterpret_cast<const float4 *>(d_bbox);
+    const float4 *lvl1 = nullptr, *root = ws.tree.cs_box;
+    if (!kept) prof_mark(ctx, kStageOctree, false);
+    if (direct && (n > kDirectFew || per.on())) {
+        rc = box_levels_build(ctx, ws.tree, boxes, nullptr);
+        if (rc) return rc;
+        if (ws.tree.nboxlvl > 0) lvl1 = ws.tree.boxlvl[0];
+        root = ws.tree.nboxlvl > 0 ? ws.tree.boxlvl[ws.tree.nboxlvl - 1] : boxes;
+    }
+    if (tree == kTreeNew || tree == kTreeBoxes) {
         rc = tree == kTreeNew
                  ? octree_build(ctx, ws.tree, d_keys, d_x, d_y, d_z, d_h, boxes, seg, st_clear, st_nclear)
                  : octree_geometry(ctx, ws.tree, d_x, d_y, d_z, d_h, boxes, seg);
         if (rc) return rc;
-        if (per.on()) {
-            k_check_span<<<1, 1, 0, st>>>(ws.tree.cs_box, per, ctx->d_status);
-            SFCNL_LAUNCHED(ctx);
-        }
-        prof_mark(ctx, kStageOctree, true);
     }
+    if (per.on() && !kept) {
+        k_check_span<<<1, 1, 0, st>>>(root, per, ctx->d_status);
+        SFCNL_LAUNCHED(ctx);
+    }
+    if (!kept) prof_mark(ctx, kStageOctree, true);
 
     TravArgs ta;
     ta.n = n;
@@ -1378,7 +1523,8 @@ int sfcnl::nlist_build_impl(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys, co
     ta.z = d_z;
     ta.h = d_h;
     ta.bbox = reinterpret_cast<const float4 *>(d_bbox);
-    ta.cs_box = ws.tree.cs_box;
+    ta.cs_box = direct ? root : ws.tree.cs_box;
+    ta.lvl1 = lvl1;
     ta.cs_rec = ws.tree.cs_rec;
     ta.nslots = ws.tree.node_cap;
     ta.seg = seg;
@@ -1398,9 +1544,9 @@ int sfcnl::nlist_build_impl(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys, co
     const unsigned gb = blocks_for(nsc, kWavesPerBlock);
     prof_mark(ctx, kStageTraverse, false);
     if (per.on())
-        launch_traverse<true>(cs, o.half, gb, st, ta);
+        launch_traverse<true>(cs, o.half, direct, nsc, st, ta);
     else
-        launch_traverse<false>(cs, o.half, gb, st, ta);
+        launch_traverse<false>(cs, o.half, direct, nsc, st, ta);
     SFCNL_LAUNCHED(ctx);
     prof_mark(ctx, kStageTraverse, true);
     prof_mark(ctx, kStageEncode, false);
@@ -1478,7 +1624,7 @@ extern "C" int build_nlist(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys, con
     if (!d_keys || !d_x || !d_y || !d_z || !d_h || !d_bbox || !d_ws || !d_sc_info || (!d_pool && pool_bytes))
         return set_err(ctx, SFCNL_E_ARG, "build_nlist: null pointer");
     return nlist_build_impl(ctx, n, d_keys, d_x, d_y, d_z, d_h, d_bbox, *opts, d_ws, ws_bytes, d_sc_info, d_pool,
-                            pool_bytes, SegTable{}, true, h_used_bytes, h_max_nj);
+                            pool_bytes, SegTable{}, true, h_used_bytes, h_max_nj, nullptr, nullptr, kTreeNone);
 }
 
 // The async build's status to the host: word k (zero when `zero`) with the
@@ -1522,7 +1668,7 @@ extern "C" int build_nlist_async(sfcnl_ctx ctx, int64_t n, const uint64_t *d_key
         size_t used;
         int64_t maxnj;
         rc = nlist_build_impl(ctx, n, d_keys, d_x, d_y, d_z, d_h, d_bbox, *opts, d_ws, ws_bytes, d_sc_info, d_pool,
-                              pool_bytes, SegTable{}, false, &used, &maxnj);
+                              pool_bytes, SegTable{}, false, &used, &maxnj, nullptr, nullptr, kTreeNone);
         if (rc) return rc;
     }
     return mark_pending(ctx, n, opts, pool_bytes);

@@ -590,31 +590,38 @@ int octree_topology(sfcnl_ctx ctx, Octree &t, const uint64_t *keys, const SegTab
     return SFCNL_OK;
 }
 
-int octree_geometry(sfcnl_ctx ctx, Octree &t, const float *x, const float *y, const float *z, const float *h,
-                    const float4 *cluster_box, const SegTable &seg) {
-    const int64_t n = t.n;
-    hipStream_t st = ctx->stream;
-    const uint32_t cap = t.node_cap;
-    const unsigned gn = node_grid(t);
-    // box hierarchy over the cluster boxes (three levels per launch), then the
-    // exact node boxes and records in their slots
+// The box hierarchy over the cluster boxes, three levels per launch.
+int box_levels_build(sfcnl_ctx ctx, Octree &t, const float4 *cluster_box, const float4 **lvl) {
     int64_t sizes[kMaxBoxLevels];
-    const int nl = box_levels(n, t.cs, sizes);
-    BoxLevels L;
-    L.lvl[0] = cluster_box;
-    L.nlvl = nl + 1;
-    L.cshift = t.cs == 4 ? 2 : (t.cs == 16 ? 4 : 3);
-    int64_t below = (n + t.cs - 1) / t.cs;
+    const int nl = box_levels(t.n, t.cs, sizes);
+    const float4 *at[kMaxBoxLevels + 1];
+    at[0] = cluster_box;
+    int64_t below = (t.n + t.cs - 1) / t.cs;
     for (int l = 0; l < nl;) {
         const int nlev = nl - l < 3 ? nl - l : 3;
-        k_box_levels<<<blocks_for(sizes[l], 256), 256, 0, st>>>(
-            L.lvl[l], below, nlev, t.boxlvl[l], sizes[l], nlev > 1 ? t.boxlvl[l + 1] : nullptr,
+        k_box_levels<<<blocks_for(sizes[l], 256), 256, 0, ctx->stream>>>(
+            at[l], below, nlev, t.boxlvl[l], sizes[l], nlev > 1 ? t.boxlvl[l + 1] : nullptr,
             nlev > 1 ? sizes[l + 1] : 0, nlev > 2 ? t.boxlvl[l + 2] : nullptr, nlev > 2 ? sizes[l + 2] : 0);
         SFCNL_LAUNCHED(ctx);
-        for (int k = 0; k < nlev; k++) L.lvl[l + 1 + k] = t.boxlvl[l + k];
+        for (int k = 0; k < nlev; k++) at[l + 1 + k] = t.boxlvl[l + k];
         below = sizes[l + nlev - 1];
         l += nlev;
     }
+    for (int l = 0; lvl && l <= nl; l++) lvl[l] = at[l];
+    return SFCNL_OK;
+}
+
+int octree_geometry(sfcnl_ctx ctx, Octree &t, const float *x, const float *y, const float *z, const float *h,
+                    const float4 *cluster_box, const SegTable &seg) {
+    hipStream_t st = ctx->stream;
+    const uint32_t cap = t.node_cap;
+    const unsigned gn = node_grid(t);
+    // the box hierarchy, then the exact node boxes and records in their slots
+    BoxLevels L;
+    const int rc = box_levels_build(ctx, t, cluster_box, L.lvl);
+    if (rc) return rc;
+    L.nlvl = t.nboxlvl + 1;
+    L.cshift = t.cs == 4 ? 2 : (t.cs == 16 ? 4 : 3);
     // kSlotLanes lanes per node: a grid of twice the node kernels' blocks
     k_node_slots<<<2 * gn, 256, 0, st>>>(t.d_nnodes, cap, t.nfirst, t.nend, t.nlevel, t.nnchild, t.parent, t.pidx,
                                      t.cbase, x, y, z, h, L, t.cs_box, t.cs_rec);
