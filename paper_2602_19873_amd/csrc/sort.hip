@@ -339,32 +339,43 @@ __global__ __launch_bounds__(kKeysThreads) void k_keys_hist(int64_t n, const flo
 // sixteenth of the keys each; equal keys by index, so the order is the stable
 // one. The work grows with n^2, but for a few thousand particles it is less
 // than the ten launches of the radix passes: up to kSmallSort particles.
-// Keys and sort, radix passes against this: 1,000 particles 43 -> 9.5 us,
-// 4,000 49 -> 20, 6,900 49 -> 29, 13,000 51 -> 50.
-constexpr int64_t kSmallSort = 8192;
+// Up to kMergeSort particles the same orders tiles of kMergeTile, and a second
+// launch ranks every particle among the other tiles (k_merge_rank). Keys and
+// sort in us, radix passes / one launch / tiles: 1,000 particles 43 / 9.5 / -,
+// 3,000 49 / 17 / 17, 6,000 49 / 27 / 18, 12,000 50 / 46 / 19, 32,768
+// 51 / - / 29, 50,000 51 / - / 47, 65,536 51 / - / 52 (tiles of 2048: 22 at
+// 12,000, 30 at 32,768).
+constexpr int64_t kSmallSort = 3072;
+constexpr int64_t kMergeSort = 49152;
+constexpr int kMergeTile = 1024;
 constexpr int kSmallThreads = 1024;
 
-__global__ __launch_bounds__(kSmallThreads) void k_sort_small(int n, const float *__restrict__ x,
+// Orders each tile of `tile` particles (the last may be shorter).
+__global__ __launch_bounds__(kSmallThreads) void k_sort_small(int n_all, int tile, const float *__restrict__ x,
                                                               const float *__restrict__ y, const float *__restrict__ z,
                                                               float lox, float sx, float loy, float sy, float loz,
                                                               float sz, uint64_t *__restrict__ keys,
                                                               uint32_t *__restrict__ perm, uint32_t *status) {
-    extern __shared__ uint64_t s_all[];  // n keys
+    extern __shared__ uint64_t s_all[];  // the tile's keys
     __shared__ uint32_t s_tab[kHilbertWords];
     __shared__ uint32_t s_part[kSmallThreads / kWave][kWave];
     const int t = threadIdx.x, lane = sfc_lane();
     const int w = __builtin_amdgcn_readfirstlane(t / kWave);
+    const int per = (tile + kWave - 1) / kWave;  // blocks a tile
+    const int t0 = (int)blockIdx.x / per * tile, first = (int)blockIdx.x % per * kWave;
+    const int n = n_all - t0 < tile ? n_all - t0 : tile;
+    if (first >= n) return;  // (past a short last tile)
     hilbert_tables_to_lds(s_tab);
     __syncthreads();
     bool bad = false;
     for (int i = t; i < n; i += kSmallThreads) {
-        const float px = x[i], py = y[i], pz = z[i];
+        const float px = x[t0 + i], py = y[t0 + i], pz = z[t0 + i];
         bad = bad || !(isfinite(px) && isfinite(py) && isfinite(pz));
         s_all[i] = hilbert_key(quantise(px, lox, sx), quantise(py, loy, sy), quantise(pz, loz, sz), s_tab);
     }
-    if (bad && blockIdx.x == 0) atomicOr(&status[kStInputErr], 1u);
+    if (bad && first == 0) atomicOr(&status[kStInputErr], 1u);
     __syncthreads();
-    const int i0 = (int)blockIdx.x * kWave, i = i0 + lane;
+    const int i0 = first, i = i0 + lane;
     const uint64_t mine = s_all[i < n ? i : n - 1];
     const int share = (n + kSmallThreads / kWave - 1) / (kSmallThreads / kWave);
     const int j0 = w * share < n ? w * share : n, j1 = j0 + share < n ? j0 + share : n;
@@ -383,8 +394,59 @@ __global__ __launch_bounds__(kSmallThreads) void k_sort_small(int n, const float
         uint32_t r = 0;
 #pragma unroll
         for (int k = 0; k < kSmallThreads / kWave; k++) r += s_part[k][lane];
-        keys[r] = mine;
-        perm[r] = (uint32_t)i;
+        keys[t0 + (int)r] = mine;
+        perm[t0 + (int)r] = (uint32_t)(t0 + i);
+    }
+}
+
+// Places the particles of ordered tiles: a block takes 64 of a tile, its four
+// waves every fourth tile each, four searches in flight together (a chain of
+// 11 loads from the L2 cache whatever the keys' distribution). Tiles
+// before come first among equal keys.
+constexpr int kMergeWaves = 4, kMergeFlight = 4;
+
+__global__ __launch_bounds__(kWave * kMergeWaves) void k_merge_rank(int n, const uint64_t *__restrict__ kin,
+                                                                   const uint32_t *__restrict__ vin,
+                                                                   uint64_t *__restrict__ kout,
+                                                                   uint32_t *__restrict__ vout) {
+    __shared__ uint32_t s_part[kMergeWaves][kWave];
+    const int lane = sfc_lane();
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int i = (int)blockIdx.x * kWave + lane, own = (int)blockIdx.x * kWave / kMergeTile;
+    const uint64_t mine = kin[i < n ? i : n - 1];
+    const int ntile = (n + kMergeTile - 1) / kMergeTile;
+    uint32_t rank = w == 0 ? (uint32_t)(i - own * kMergeTile) : 0u;
+    for (int b0 = w; b0 < ntile; b0 += kMergeWaves * kMergeFlight) {
+        int pos[kMergeFlight];
+#pragma unroll
+        for (int k = 0; k < kMergeFlight; k++) pos[k] = 0;
+#pragma unroll 1
+        for (int step = kMergeTile; step > 0; step >>= 1) {
+            uint64_t v[kMergeFlight];
+#pragma unroll
+            for (int k = 0; k < kMergeFlight; k++) {
+                const int at = (b0 + k * kMergeWaves) * kMergeTile + pos[k] + step - 1;
+                v[k] = kin[at < n ? at : n - 1];
+            }
+#pragma unroll
+            for (int k = 0; k < kMergeFlight; k++) {
+                const int b = b0 + k * kMergeWaves;
+                const bool in = pos[k] + step <= kMergeTile && b * kMergeTile + pos[k] + step <= n;
+                if (in && (b < own ? v[k] <= mine : v[k] < mine)) pos[k] += step;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kMergeFlight; k++)
+            if (b0 + k * kMergeWaves != own) rank += (uint32_t)pos[k];  // (a tile past the end: none)
+    }
+    s_part[w][lane] = rank;
+    __syncthreads();
+    if (w == 0 && i < n) {
+        uint32_t r = 0;
+#pragma unroll
+        for (int k = 0; k < kMergeWaves; k++) r += s_part[k][lane];
+        kout[r] = mine;
+        vout[r] = vin[i];
     }
 }
 
@@ -921,14 +983,22 @@ int sort_impl(sfcnl_ctx ctx, int64_t n, const float *d_x, const float *d_y, cons
     for (const float *in : {d_x, d_y, d_z})
         apart = apart && !overlap(in, (size_t)n * 4, d_keys_out, (size_t)n * 8) &&
                 !overlap(in, (size_t)n * 4, d_perm_out, (size_t)n * 4);
-    if (apart) {
+    if (apart || (n > kSmallSort && n <= kMergeSort)) {
+        const int tile = apart ? (int)n : kMergeTile;
         prof_mark(ctx, kStageKeys, false);
         prof_mark(ctx, kStageKeys, true);
         prof_mark(ctx, kStageSort, false);
-        k_sort_small<<<blocks_for(n, kWave), kSmallThreads, (size_t)n * 8, st>>>(
-            (int)n, d_x, d_y, d_z, h_box[0], box_scale(h_box[0], h_box[1]), h_box[2], box_scale(h_box[2], h_box[3]),
-            h_box[4], box_scale(h_box[4], h_box[5]), d_keys_out, d_perm_out, ctx->d_status);
+        k_sort_small<<<(unsigned)(((n + tile - 1) / tile) * ((tile + kWave - 1) / kWave)), kSmallThreads,
+                       (size_t)tile * 8, st>>>(
+            (int)n, tile, d_x, d_y, d_z, h_box[0], box_scale(h_box[0], h_box[1]), h_box[2],
+            box_scale(h_box[2], h_box[3]), h_box[4], box_scale(h_box[4], h_box[5]), apart ? d_keys_out : s.ktmp,
+            apart ? d_perm_out : s.vtmp, ctx->d_status);
         SFCNL_LAUNCHED(ctx);
+        if (!apart) {
+            k_merge_rank<<<blocks_for(n, kWave), kWave * kMergeWaves, 0, st>>>((int)n, s.ktmp, s.vtmp, d_keys_out,
+                                                                               d_perm_out);
+            SFCNL_LAUNCHED(ctx);
+        }
         prof_mark(ctx, kStageSort, true);
         return SFCNL_OK;
     }

@@ -70,9 +70,9 @@ def test_iteration_at_size_rules(env, n, half):
 
 
 @pytest.mark.parametrize("kind", ["uniform", "equal", "ties"])
-@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1023, 1025, 4097, 8191, 8192, 8193])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1023, 1025, 3071, 3072, 3073, 4095, 4096, 4097, 20479, 49151, 49152, 49153])
 def test_small_sort(env, n, kind):
-    # one launch up to 8192 particles, the radix passes above; equal keys keep their order
+    # one launch up to 3072 particles, ordered tiles up to 49152, the radix passes above; equal keys keep their order
     sf, ctx, torch = env
     rng = np.random.default_rng(n)
     p = rng.random((3, n))
