@@ -14,9 +14,10 @@
 // loads). A list round or a recount of all moved particles per round walks
 // again for each of some 10 (one sphere) to 40 rounds (16 systems), and from
 // the tenth round on a round was 90 to 120 us of launches around a few us of
-// work: 1,000,003 particles of a 1/r sphere 4.74 -> 3.51 ms, 20,000 1.68 ->
-// 0.82 ms, four systems of up to 100,000 17.2 -> 6.3 ms for the whole
-// iteration.
+// work: for the whole iteration 1,000,003 particles of a 1/r sphere 4.74 ->
+// 3.51 ms, 20,000 1.68 -> 0.82 ms, four systems of up to 100,000 17.2 -> 6.3 ms
+// (3.18, 0.44 and 3.3 ms with what came after: shared counters by stripes,
+// incomplete counts and lists without an octree).
 #include <algorithm>
 #include <type_traits>
 
@@ -54,7 +55,8 @@ __global__ __launch_bounds__(256) void k_compact_moved(int64_t n, const uint32_t
     const int lane = sfc_lane();
     const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * kWavesPerBlock + threadIdx.x / kWave));
     const uint32_t nsc = (uint32_t)((n + kScSize - 1) / kScSize);
-    if (s == 0 && lane >= kStFinMoved && lane <= kStFinNext) status[lane] = 0u;
+    if (s == 0 && lane >= kStFinMoved && lane <= kStFinLeft) status[lane] = 0u;
+    if (s == 0 && lane < kChunkStripes) status[kStWords + lane * kStripeWords + kStripeFin] = 0u;
     if (s >= nsc || cnt[s] == 0) return;
     const int64_t i = (int64_t)s * kScSize + lane;
     const bool f = i < n && moved[i] != 0;
@@ -81,8 +83,11 @@ struct FinishArgs {
     uint32_t *status, *sys_rounds;
 };
 
-// One wavefront per listed particle, taken from the list kTake at a time as
-// waves become free (some particles need two rounds, some forty).
+// One wavefront per listed particle, taken from the list as waves become free
+// (some particles need two rounds, some forty): list position k 64 + s belongs
+// to stripe s, whose waves share a counter (one counter for all, an atomic that
+// returns a value per particle, cost 0.5 ms: iteration of 65,536 particles, all
+// of them here, 1290 -> 714 us).
 template <bool kMass, bool kPbc>
 __global__ __launch_bounds__(256) void k_finish_moved(FinishArgs a) {
     __shared__ uint4 s_stack[kWavesPerBlock][kStackCap];
@@ -95,8 +100,8 @@ __global__ __launch_bounds__(256) void k_finish_moved(FinishArgs a) {
     uint4 *stack = s_stack[w];
     float *d2s = s_d2[w];
     uint32_t *js = s_j[w];
-    const uint32_t take = total > 8u * nw ? 4u : 1u;
-    uint32_t t = (blockIdx.x * kWavesPerBlock + (uint32_t)w) * take, t_end = t + take;
+    uint32_t t = blockIdx.x * kWavesPerBlock + (uint32_t)w;
+    const uint32_t stripe = t % kChunkStripes, members = (nw - stripe + kChunkStripes - 1) / kChunkStripes;
     uint32_t moves = 0, most = 0, left = 0;
     while (t < total) {
         const uint32_t i = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.plist[t]);
@@ -241,13 +246,9 @@ __global__ __launch_bounds__(256) void k_finish_moved(FinishArgs a) {
         }
         moves += my_moves;
         most = r > most ? r : most;
-        t++;
-        if (t >= t_end) {
-            uint32_t next = 0;
-            if (lane == 0) next = atomicAdd(&a.status[kStFinNext], take);
-            t = nw * take + (uint32_t)__builtin_amdgcn_readfirstlane((int)next);
-            t_end = t + take;
-        }
+        uint32_t next = 0;
+        if (lane == 0) next = atomicAdd(&a.status[kStWords + stripe * kStripeWords + kStripeFin], 1u);
+        t = (members + (uint32_t)__builtin_amdgcn_readfirstlane((int)next)) * kChunkStripes + stripe;
     }
     if (lane == 0 && most) {
         atomicAdd(reinterpret_cast<unsigned long long *>(&a.status[kStFinMoved]), (unsigned long long)moves);

@@ -79,11 +79,13 @@ constexpr uint32_t kAllCounts = 0xFFFFFFFFu;  // (pass_impl's plenty)
 // it, building the lists of their super-clusters shares each walk among up to
 // 64 particles.
 // Whole runs in us with a limit of n / 4, n / 2, n:
-//   spheres, 20,000: 1053 / 927 / 817   200,000: 1931 / 1547 / 1398
-//          1,000,003: 3513 / 3527 / 4192
-//   uniform, 20,000: 1105 / 1067 / 885  200,000: 2066 / 2036 / 1436
-//          1,000,000: 3934 / 4163 / 4675
-//   batch of 4 systems up to 100,000: 9748 / 9193 / 6317
+//   spheres, 5,000: 433 / 374 / 297     20,000: 525 / 488 / 438
+//          200,000: 1474 / 1332 / 1197  400,000: 2174 / 2034 / 2120
+//        1,000,003: 3182 / 3154 / 3829
+//   uniform, 20,000: 541 / 545 / 470    200,000: 1448 / 1444 / 1240
+//          1,000,000: 3693 / 3963 / 4726
+//   batches: 4 systems up to 100,000: 4915 / 4678 / 3304
+//            16 up to 200,000 (1.0M): 16819 / 17924 / 19701
 // Small systems go there right after the first round, as their list rounds
 // are launches (about 20 of them). (Periodic runs keep the lower limit at
 // every size: the list rounds refuse radii that reach half a period.)

@@ -29,7 +29,6 @@ enum StatusWord : int {
     kStFinMoved = 8,     // finish_moved: moves over its rounds (64 bits)
     kStFinRounds = 10,   // its rounds in which a particle moved
     kStFinLeft = 11,     // particles still moving in its last allowed round
-    kStFinNext = 12,     // its next unclaimed list position
     kStWords = 16
 };
 
@@ -38,8 +37,10 @@ enum StatusWord : int {
 // stripe k gives out ids k, k + kChunkStripes, k + 2 kChunkStripes, ..., so
 // that the super-clusters' requests spread over many addresses instead of
 // queueing on one. Word 1 of a stripe's line holds the longest list among
-// the super-clusters s with s % kChunkStripes = k.
+// the super-clusters s with s % kChunkStripes = k, word kStripeFin its share of
+// finish_moved's list handed out.
 constexpr int kChunkStripes = 64;
+constexpr int kStripeFin = 2;
 constexpr int kStripeWords = 32;
 constexpr int kStatusAlloc = kStWords + kChunkStripes * kStripeWords;  // words of the device status allocation
 

@@ -422,10 +422,10 @@ __device__ __forceinline__ uint32_t candidate_mask(uint32_t seen, int lane) {
 // first wave makes the list. The octree's ten dependent launches and the walk's
 // chain of node reads by one wave take longer than testing every group, whose
 // work grows with n^2. Whole steps, octree against this, clusters of 8 in us:
-// 1,000 particles 111 / 52, 32,768 201 / 123, 65,536 245 / 161, 131,072
-// 285 / 236, 200,000 312 / 395, periodic 50,000 246 / 176, 200,000 378 / 485;
-// clusters of 4: 65,536 278 / 220, 131,072 342 / 678; of 16: 131,072 344 / 255,
-// 262,144 416 / 412. Group boxes (a launch) and 4 instead of 8 waves pay from
+// 1,000 particles 95 / 52, 32,768 180 / 103, 65,536 243 / 159, 131,072
+// 283 / 235, 200,000 310 / 394, periodic 50,000 243 / 172, 200,000 373 / 483;
+// clusters of 4: 65,536 276 / 219, 131,072 338 / 672; of 16: 131,072 344 / 255,
+// 262,144 412 / 410. Group boxes (a launch) and 4 instead of 8 waves pay from
 // kDirectFew on: 24,000 123 without, 125 with; 65,536 183 without, 162 with.
 constexpr int kDirectWavesFew = 8, kDirectWavesMany = 4;
 constexpr int64_t kDirectFew = 32768;  // particles: above, 4 waves and group boxes
