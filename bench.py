@@ -762,9 +762,9 @@ def run_step(args, sf, torch, ctx):
     dom = prof["_live"][0]  # the dominant stage, timed live in the timed steps
     dd = stages[dom]
     hb = "true" if args.half else "false"
-    kernel_of = {"traverse": "k_traverse<%d,%s,false>" % (args.cluster_size, hb),
-                 "pass": ("k_pass_half<%d,true,false,true,false>" % args.cluster_size if args.half
-                          else "k_pass<%d,true,false,true,false>" % args.cluster_size)}
+    kernel_of = {"traverse": "k_traverse<%d,%s,false,0>" % (args.cluster_size, hb),
+                 "pass": ("k_pass_half<%d,true,false,true,false,false>" % args.cluster_size if args.half
+                          else "k_pass<%d,true,false,true,false,false>" % args.cluster_size)}
     kern = kernel_of.get(dom, dom)
     traffic = counters[kern][0] if kern in counters else None
     roofline = {"kernel": kern, "bound": dd["bound"], "achieved": dd["achieved"],
