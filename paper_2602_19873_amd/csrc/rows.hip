@@ -26,6 +26,7 @@
 // -> 292 us for 500,009 particles; 8 rows per wavefront from one staging: 314.)
 #include "internal.h"
 #include "pass_common.h"
+#include "row_stage.h"
 
 namespace sfcnl {
 namespace {
@@ -280,8 +281,6 @@ struct RowPassArgs {
     int32_t *nnb;
 };
 
-constexpr int kStageWords = 256;  // words of a row in LDS (longer rows are read from memory)
-
 // As decode_segment, from the words at w[p..] (LDS or memory); the last word
 // read is the segment's last.
 template <typename W>
@@ -326,8 +325,8 @@ __global__ __launch_bounds__(kWave) void k_pass_rows(RowPassArgs a) {
     const float hinv = 1.0f / hi;
     bool staged = false;
     if (kCompress && i + 1 < n) {  // the next row begins where this one ends
-        const uint32_t len = a.row_info[2 * (size_t)i + 2] - off;
-        staged = len <= (uint32_t)kStageWords;
+        const uint32_t len = row_stage_words(off, cnt, a.row_info[2 * (size_t)i + 2]);
+        staged = len != 0u;
         if (staged) {
             for (uint32_t q = (uint32_t)lane; q < len; q += kWave) s_words[q] = a.pool[off + q];
             wave_sync();
