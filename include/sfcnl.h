@@ -65,8 +65,10 @@ void sfcnl_destroy(sfcnl_ctx ctx);
 int sfcnl_set_stream(sfcnl_ctx ctx, void *stream);
 /* Launch shape of the density passes (nlist_pass and the batched passes) of
  * this context: 1, 2 or 4 wavefronts (super-clusters) per workgroup (default
- * 1). Results do not depend on it; the batch autotuner times the choices.
- * Other values return SFCNL_E_ARG. */
+ * 1; with 1, several wavefronts share a super-cluster of a small system).
+ * Results do not depend on it (but for the order of a half list's atomic
+ * sums); the batch autotuner times the choices. Other values return
+ * SFCNL_E_ARG. */
 int sfcnl_set_pass_waves(sfcnl_ctx ctx, int waves);
 const char *sfcnl_last_error(sfcnl_ctx ctx);
 /* Waits for the stream and returns the latched device-side error, if any

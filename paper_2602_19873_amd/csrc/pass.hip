@@ -22,8 +22,8 @@ using namespace passk;
 // knob of the context (sfcnl_set_pass_waves, 1, 2 or 4). One wave per block
 // lets a block release its slots as soon as its one list is done (7 % faster
 // than four for the half-list pass on the uniform benchmark); the batch
-// autotuner times all three. Small systems split their super-clusters over up
-// to 8 waves instead (pass_split).
+// autotuner times all three. At one, small systems split their super-clusters
+// over up to 8 waves (pass_split).
 constexpr int kPassWavesMax = kPassSplitMax;
 // LDS per wave of the cluster-size-8 symmetric pass: a batch's 64
 // j-particles (x, y, z, h^2), their 1/h and masses, and every tile lane's
@@ -756,7 +756,8 @@ int sfcnl::pass_impl(sfcnl_ctx ctx, int64_t n, int cs, int compress, int half, c
         return set_err(ctx, SFCNL_E_ARG, "nlist_pass: a restricted pass needs the full list");
     PassArgs a{n, (uint32_t)((n + kScSize - 1) / kScSize), d_sc_info, d_pool, d_x, d_y, d_z, d_h, d_m, d_rho, d_nnb,
                seg, per, active, p_active, gate, gate_max, 1u, plenty};
-    a.split = pass_split(cs, half != 0, a.nsc);
+    // (a shape chosen with sfcnl_set_pass_waves is taken as it is)
+    a.split = ctx->pass_waves == 1 ? pass_split(cs, half != 0, a.nsc) : 1u;
     const int waves = a.split > 1 ? (int)a.split : ctx->pass_waves;
     const unsigned g = a.split > 1 ? a.nsc : blocks_for(a.nsc, waves);
     const unsigned tpb = (unsigned)(kWave * waves);
