@@ -28,8 +28,6 @@ namespace {
 
 constexpr int kWavesPerBlock = 4;
 constexpr int kStackCap = 160;  // 1 + 7 * 21 pushes at most
-constexpr int kKept = 512;      // pairs kept per wavefront; more: every round walks
-constexpr float kReach = 1.08f; // radius of the walk over the particle's radius
 
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");

@@ -89,7 +89,16 @@ constexpr uint32_t kAllCounts = 0xFFFFFFFFu;  // (pass_impl's plenty)
 // Small systems go there right after the first round, as their list rounds
 // are launches (about 20 of them). (Periodic runs keep the lower limit at
 // every size: the list rounds refuse radii that reach half a period.)
-int64_t finish_limit(int64_t n, bool periodic) { return n <= 262144 && !periodic ? n : n / 4 + 64; }
+// A target whose pairs do not fit the wavefront's kept ones (finish_keeps) has
+// every round walk, and the whole system stays with the list rounds from 32,768
+// particles on. Limits of n / 4 and n there, uniform systems and spheres:
+//   target 400:  20,000:  800 / 648, 1235 / 655    262,000: 2847 / 2760, 3328 / 3079
+//          500:  20,000:  951 / 892, 1505 / 934     40,000: 1157 / 1119, 1820 / 1406
+//                70,000: 1591 / 2332, 2218 / 1934  262,000: 3247 / 4733, 3990 / 5453
+//        2,000:  20,000: 1981 / 2257, 3032 / 2191  262,000: 7967 / 14569, 9670 / 17297
+int64_t finish_limit(int64_t n, bool periodic, int target) {
+    return n <= (finish_keeps(target) ? 262144 : 32768) && !periodic ? n : n / 4 + 64;
+}
 
 // Adds a finish that started before round `it` to the run's statistics.
 void add_finish(sfcnl_hiter_stats &S, const uint32_t *status, int it, int max_iters) {
@@ -167,7 +176,7 @@ extern "C" int sfcnl_h_iterate(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys,
     for (int it = 0; it < it_opts->max_iters; it++) {
         const bool first = it == 0;
         const bool learned = first && seed && seed->mode == SFCNL_SEED_AFTER_FIRST;  // features take the counts
-        if (!first && (it_opts->recount == 2 || (it_opts->recount == 0 && S.unconverged <= finish_limit(n, make_period(nl_opts->period).on())))) {
+        if (!first && (it_opts->recount == 2 || (it_opts->recount == 0 && S.unconverged <= finish_limit(n, make_period(nl_opts->period).on(), it_opts->target)))) {
             // few moved: all their remaining rounds on the last octree
             int rc = finish_moved_impl(ctx, n, act, d_x, d_y, d_z, d_h, br, d_m, d_rho, d_nnb, it_opts->target,
                                        it_opts->tol, it_opts->max_iters - it, SegTable{}, make_period(nl_opts->period),
@@ -432,7 +441,7 @@ extern "C" int sfcnl_batch_h_iterate(sfcnl_ctx ctx, sfcnl_batch b, const uint64_
     int it = 0;
     while (it < it_opts->max_iters && S.unconverged > 0) {
         int nr = 1;
-        if (it > 0 && (it_opts->recount == 2 || (it_opts->recount == 0 && S.unconverged <= finish_limit(b->n_pad, false)))) {
+        if (it > 0 && (it_opts->recount == 2 || (it_opts->recount == 0 && S.unconverged <= finish_limit(b->n_pad, false, it_opts->target)))) {
             // few moved: all their remaining rounds on the last octree
             int rc = fill_u32(ctx, b->d_sys_moved, b->nsys, 0);
             if (rc) return rc;

@@ -295,6 +295,12 @@ struct ActiveWs {
     const uint4 *cs_rec;
     uint32_t nslots;
 };
+// Of every particle a finishing wavefront keeps up to kKept pairs, those within
+// kReach of its radius, and counts from them.
+constexpr int kKept = 512;
+constexpr float kReach = 1.08f;
+// True if about `target` pairs leave room for that.
+constexpr bool finish_keeps(int target) { return (float)target * (kReach * kReach * kReach) <= (float)kKept; }
 // All remaining rounds of the moved particles (act.p, their number in
 // act.scan[nsc]) of an h-iteration without a list: compacts act.p into
 // act.plist, then every listed particle is counted and updated until it is
