@@ -1520,17 +1520,19 @@ int sfcnl::nlist_build_impl(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys, co
     const float4 *const boxes = reinterpret_cast<const float4 *>(d_bbox);
     const float4 *lvl1 = nullptr, *root = ws.tree.cs_box;
     if (!kept) prof_mark(ctx, kStageOctree, false);
-    if (direct && (n > kDirectFew || per.on())) {
-        rc = box_levels_build(ctx, ws.tree, boxes, nullptr);
-        if (rc) return rc;
-        if (ws.tree.nboxlvl > 0) lvl1 = ws.tree.boxlvl[0];
-        root = ws.tree.nboxlvl > 0 ? ws.tree.boxlvl[ws.tree.nboxlvl - 1] : boxes;
-    }
+    const bool levels = direct && (n > kDirectFew || per.on());  // a direct list's box levels
     if (tree == kTreeNew || tree == kTreeBoxes) {
         rc = tree == kTreeNew
                  ? octree_build(ctx, ws.tree, d_keys, d_x, d_y, d_z, d_h, boxes, seg, st_clear, st_nclear)
                  : octree_geometry(ctx, ws.tree, d_x, d_y, d_z, d_h, boxes, seg);
         if (rc) return rc;
+    } else if (levels) {
+        rc = box_levels_build(ctx, ws.tree, boxes, nullptr);
+        if (rc) return rc;
+    }
+    if (levels) {  // (an octree comes with them)
+        if (ws.tree.nboxlvl > 0) lvl1 = ws.tree.boxlvl[0];
+        root = ws.tree.nboxlvl > 0 ? ws.tree.boxlvl[ws.tree.nboxlvl - 1] : boxes;
     }
     if (per.on() && !kept) {
         k_check_span<<<1, 1, 0, st>>>(root, per, ctx->d_status);
