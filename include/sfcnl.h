@@ -156,7 +156,8 @@ int build_clusters(sfcnl_ctx ctx, int64_t n, const float *d_x, const float *d_y,
  * Super-clusters are laid out in order, so the pool is deterministic.
  *
  * Inputs: SFC-ordered d_keys (from sfc_sort), positions, radii, and the
- * cluster boxes of build_clusters. opts:
+ * cluster boxes of build_clusters. (Small systems' lists come from the boxes
+ * alone, without reading the keys; larger ones need the keys in order.) opts:
  *   cluster_size  4, 8 or 16 (the size given to build_clusters).
  *   compress      0 or 1.
  *   leaf_bucket   octree leaves hold at most this many particles (8..256).
@@ -504,6 +505,8 @@ int sfcnl_batch_h_iterate(sfcnl_ctx ctx, sfcnl_batch b, const uint64_t *d_keys, 
  * events on the context's stream (no synchronisation). Stages:
  *   0 keys, 1 radix sort, 2 gather, 3 clusters, 4 octree, 5 traversal,
  *   6 encode (prefix sum + encoder), 7 pass.
+ * Up to 49,152 particles the keys are made by the sort's first launch: stage 0
+ * is then an empty interval and their time part of stage 1.
  * sfcnl_profile_begin allocates `slots` event pairs per stage; recording past
  * that many calls of a stage is skipped. sfcnl_profile_end waits for the
  * stream, writes per stage the summed milliseconds (h_ms[8]) and the number of

@@ -812,7 +812,9 @@ def batch_h_iterate(ctx: Context, b: Batch, keys, x, y, z, h, target: int = 100,
     """sfcnl_batch_h_iterate on padded SFC-ordered arrays (h updated in
     place). `bufs` (a dict, filled on first use) keeps every buffer for reuse
     across calls; buffers grow and the run resumes on SFCNL_E_CAPACITY.
-    recount: 0 automatic, 1 lists, 2 one wavefront per moved particle."""
+    recount: 0 automatic, 1 lists, 2 one wavefront per moved particle.
+    use_graph: replay the rounds from a HIP graph (with recount 1, where every
+    round builds lists; the other recounts use none)."""
     import numpy as np
     n = b.n_pad
     nsc = n // SC_SIZE
