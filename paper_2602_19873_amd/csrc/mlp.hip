@@ -505,11 +505,14 @@ __global__ __launch_bounds__(256) void k_mlp_init(uint64_t seed, float *__restri
 // the particle lies in a narrow run of keys around it (mostly a few hundred at
 // the coarsest level asked for), so each block stages the keys of its particles
 // and kKeyPad to either side in LDS and searches there, the finer cells inside
-// the coarser ones; ends beyond the window are searched in memory, both of a
-// cell side by side. (Searching the whole array, each step waited on a load:
-// 67 -> 28 us for 1,000,000 uniform particles. The core's cells of a condensed
-// system mostly end beyond the window: Plummer sphere of 30,000 13.9 -> 13.7 us,
-// 15.4 with one search after the other, of 1,000,000 71 -> 51.)
+// the coarser ones; ends beyond the window are searched in memory. (Searching the
+// whole array, each step waited on a load: 67 -> 28 us for 1,000,000 uniform
+// particles.) kFew: both ends of a cell in memory side by side, which pays while
+// the GPU is not full: the core's cells of a condensed system mostly end beyond the
+// window, and one search after the other took longer than searching everything in
+// memory (Plummer spheres of 30,000 / 100,000 particles 13.9 / 16.6 us then, 15.4 /
+// 16.6 one after the other, 13.7 / 14.5 side by side; with the network, uniform
+// systems of 1,000,003 64.3 us one after the other, 66.7 side by side).
 constexpr int kFeatThreads = 256;
 constexpr int kKeyPad = 896;  // 2,048 keys in LDS: 16 KB
 
@@ -563,6 +566,9 @@ __device__ __forceinline__ float diag(float lx, float ly, float lz, float hx, fl
 // multiples of 64): the 8-particle cluster box and the super-cluster box come
 // from min / max over lane groups; absent particles are NaN, which fminf and
 // fmaxf ignore.
+constexpr int64_t kFeatFew = 262144;
+
+template <bool kFew>
 __global__ __launch_bounds__(kFeatThreads) void k_features(int64_t n, const uint64_t *__restrict__ keys,
                                                   const float *__restrict__ x, const float *__restrict__ y,
                                                   const float *__restrict__ z, const float *__restrict__ h,
@@ -623,12 +629,17 @@ __global__ __launch_bounds__(kFeatThreads) void k_features(int64_t n, const uint
         const uint32_t wa = ca > w0 ? ca : w0, wb = cb < w1 ? cb : w1;
         // (particle i is inside: the start is at most i, the end above it)
         const bool fa = wa > ca && in_lds(wa) >= va, fb = wb < cb && in_lds(wb - 1u) < vb;  // beyond the window
-        KeySearch a{ca, wa, va}, b{wb, cb, vb};
-        if (!fa) a.lo = a.hi = lower_bound_key(in_lds, wa, (uint32_t)i, va);
-        if (!fb) b.lo = b.hi = lower_bound_key(in_lds, (uint32_t)i + 1u, wb, vb);
-        if (fa || fb) lower_bounds(in_mem, a, b, (uint32_t)i);
-        ca = a.lo;
-        cb = b.lo;
+        if (kFew) {
+            KeySearch a{ca, wa, va}, b{wb, cb, vb};
+            if (!fa) a.lo = a.hi = lower_bound_key(in_lds, wa, (uint32_t)i, va);
+            if (!fb) b.lo = b.hi = lower_bound_key(in_lds, (uint32_t)i + 1u, wb, vb);
+            if (fa || fb) lower_bounds(in_mem, a, b, (uint32_t)i);
+            ca = a.lo;
+            cb = b.lo;
+        } else {
+            ca = fa ? lower_bound_key(in_mem, ca, wa, va) : lower_bound_key(in_lds, wa, (uint32_t)i, va);
+            cb = fb ? lower_bound_key(in_mem, wb, cb, vb) : lower_bound_key(in_lds, (uint32_t)i + 1u, wb, vb);
+        }
         f[4 + d] = logf(1.0f + (float)(cb - ca)) - lt;
     }
     f[6] = lev - (float)L0;
@@ -711,8 +722,11 @@ extern "C" int sfcnl_mlp_adam(sfcnl_ctx ctx, float *d_params, const float *d_gra
 int sfcnl::features_impl(sfcnl_ctx ctx, int64_t n, const uint64_t *d_keys, const float *d_x, const float *d_y,
                          const float *d_z, const float *d_h, const int32_t *d_nnb, float box_edge, int target,
                          uint16_t *d_feat, const SegTable &seg) {
-    k_features<<<blocks_for(n, kFeatThreads), kFeatThreads, 0, ctx->stream>>>(n, d_keys, d_x, d_y, d_z, d_h, d_nnb, box_edge, target,
-                                                            d_feat, seg);
+    const unsigned g = blocks_for(n, kFeatThreads);
+    if (n <= kFeatFew)
+        k_features<true><<<g, kFeatThreads, 0, ctx->stream>>>(n, d_keys, d_x, d_y, d_z, d_h, d_nnb, box_edge, target, d_feat, seg);
+    else
+        k_features<false><<<g, kFeatThreads, 0, ctx->stream>>>(n, d_keys, d_x, d_y, d_z, d_h, d_nnb, box_edge, target, d_feat, seg);
     SFCNL_LAUNCHED(ctx);
     return SFCNL_OK;
 }
