@@ -25,7 +25,7 @@ METRIC = "nlist build + density pass Mparticles/s at 1 GPU; bytes/particle; % HB
 HBM_PEAK_GBS = 8000.0
 FP32_PEAK_TFLOPS = 157.3      # 256 CU x 2.4 GHz x 128 FP32 lanes (dual-issue) x 2 (FMA)
 
-# Algorithmic work, per unit (stated also in the design doc):
+# Algorithmic work, per unit:
 #   HBM stages: bytes per particle the stage must move at minimum.
 #   ALU stages: FP32 flops (an FMA counts 2) per particle-pair test.
 BYTES_PER_PARTICLE = {

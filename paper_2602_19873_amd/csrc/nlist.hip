@@ -430,12 +430,24 @@ __device__ __forceinline__ uint32_t candidate_mask(uint32_t seen, int lane) {
 // the pairs of what comes near, and leaves the masks in LDS, from which the
 // first wave makes the list. The octree's ten dependent launches and the walk's
 // chain of node reads by one wave take longer than testing every group, whose
-// work grows with n^2. Whole steps, octree against this, clusters of 8 in us:
-// 1,000 particles 95 / 52, 32,768 180 / 103, 65,536 243 / 159, 131,072
-// 283 / 235, 200,000 310 / 394, periodic 50,000 243 / 172, 200,000 373 / 483;
-// clusters of 4: 65,536 276 / 219, 131,072 338 / 672; of 16: 131,072 344 / 255,
-// 262,144 412 / 410. Group boxes (a launch) and 4 instead of 8 waves pay from
-// kDirectFew on: 24,000 123 without, 125 with; 65,536 183 without, 162 with.
+// work grows with n^2. Builds (clusters to pool) in us, octree / this, full
+// lists of some 100 neighbours:
+//                         uniform      1/r sphere   Plummer      Plummer, equal radii
+//   clusters of 8   1,000    86 /  50     81 /  49    106 /  47     89 /  46
+//                  32,768   128 /  60    142 /  59    379 / 124    620 / 160
+//                 131,072   168 / 135    157 / 134    315 / 232   1241 / 565
+//                 196,608   161 / 254    168 / 254    330 / 304   1532 / 900
+//   clusters of 4  65,536   171 / 131    154 / 127    398 / 277   1045 / 446
+//                 131,072   181 / 539    184 / 524    359 / 639   1456 / 1599
+//   clusters of 16 196,608  176 / 164    190 / 172    393 / 282   1506 / 685
+//                 262,144   193 / 230    222 / 230    331 / 278   1805 / 859
+// (half lists, radii of a uniform guess on the sphere and periodic boxes alike).
+// The strict tests of the walk are not needed here: the outskirts of condensed
+// systems, whose boxes let most clusters through, are tested by 4 to 8 waves. Group
+// boxes (a launch) with 4 waves against 8 waves without, from kDirectFew on, full
+// lists: uniform 24,000 56 / 52, 40,000 67 / 73, 65,536 79 / 100; sphere 24,000
+// 56 / 51, 40,000 64 / 71, 65,536 83 / 98; Plummer 24,000 143 / 104, 65,536 206 / 174,
+// 100,000 236 / 260.
 constexpr int kDirectWavesFew = 8, kDirectWavesMany = 4;
 constexpr int64_t kDirectFew = 32768;  // particles: above, 4 waves and group boxes
 constexpr int64_t direct_max(int cs) { return cs == 4 ? 65536 : (cs == 8 ? 131072 : 196608); }
@@ -1064,7 +1076,11 @@ __global__ __launch_bounds__(kWave * (kDirect ? kDirect : kWavesPerBlock)) __att
     // radii 1.12 -> 0.39 ms, as its outermost super-clusters walked for 1 ms;
     // the 1/r sphere of 4,000,037 particles 1439 -> 1143 us. From 128 clusters
     // on with one in four listed: 512 and 2048 clusters 1209 and 1440 us for
-    // the sphere; one in two costs uniform systems 5 %.)
+    // the sphere; one in two costs uniform systems 5 %. Short lists meet the rule
+    // where it pays little: half lists of a sphere of 1,000,000 at 30 neighbours
+    // 278 us against 259 without, at 60 277, by the tests before the filter 266
+    // and 293. One in eight gives 248 there, but 507 instead of 445 us for a
+    // Plummer sphere of 200,000 at 200 neighbours.)
     bool strict = false;
     // does one of the `count` particles from p0 on come near the box?
     auto any_near = [&](uint32_t p0, uint32_t count, const float4 &lo, const float4 &hi) SFC_INLINE {

@@ -92,7 +92,14 @@ __device__ __forceinline__ void sfc_compact(bool keep, uint32_t &mv, uint32_t &j
 //   half, clusters of 4:  d  65536: 265 / 145 / 86 / 67    f 125000: 223 / 133 / 91 / 91
 //                         d 800000: 501 / 422 / 403        f 262144: 248 / 185 / 153 / 163
 // (clusters of 16 behave as clusters of 4; their full lists have four
-// i-registers to share out)
+// i-registers to share out). Lists of few entries gain less, and the largest
+// shared ones lose: half, clusters of 8, density pass in us with 1 / 2 / 4 parts
+//   at 10 neighbours (30 entries)  120000: 37 / 29 / 30  262000: 43 / 40 / 46  1048000: 94 / 101 / 132
+//   at 30 neighbours (42 entries)  120000: 49 / 37 / 36  262000: 59 / 51 / 54  1048000: 133 / 138 / 167
+//   at 60 neighbours (56 entries)  120000: 64 / 45 / 43  262000: 79 / 67 / 67  1048000: 178 / 180 / 209
+// The rule does not see the lists. (Parts that end at once where a list is short
+// cost as much: idle wavefronts of a block hold its LDS, blocks of one wavefront
+// starve the dispatch.)
 inline uint32_t pass_split(int cs, bool half, int64_t nsc) {
     if (!half) return nsc <= 512 && cs == 8 ? 8u : (nsc <= 1600 ? 4u : 1u);
     if (nsc <= (cs == 8 ? 800 : 1600)) return 8u;

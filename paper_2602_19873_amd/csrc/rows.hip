@@ -58,9 +58,20 @@ struct RowArgs {
 
 // Rows per wavefront of the build: a wavefront of 8 shares most, but takes as
 // long as its rows need one after another, so small systems, which leave the GPU
-// half empty, take 4 or 1. Build of 8,000 / 32,000 / 128,000 / 500,009 particles
-// in us with 1: 61, 122, 387, 1,427; with 4: 65, 109, 279, 908; with 8: 83, 117,
-// 280, 843.
+// half empty, take 4 or 1. Builds in us with 1 / 4 / 8, uniform systems at 200
+// neighbours, lists of clusters of 8 (of 4 and 16 alike to within 10 %, the
+// limits the same):
+//   particles      nibble segments      raw indices
+//      8,000         69 /  76 /  95       64 /  66 /  77
+//     11,000         77 /  79 / 100       72 /  69 /  82
+//     32,000        126 / 115 / 121      114 /  96 /  98
+//    110,000        352 / 258 / 262      316 / 206 / 202
+//    160,000        470 / 330 / 325      421 / 255 / 241
+//    500,009      1,465 / 930 / 861    1,365 / 708 / 625
+// (At 50 neighbours nibble segments 52 / 53 / 60, 83 / 72 / 74 and 202 / 145 / 142
+// at 8,000, 32,000 and 110,000. Decoding and testing 8 times, a row per wavefront
+// without the present encoder, took 71, 138, 386 and 1,620 at 8,000, 32,000,
+// 110,000 and 500,009.)
 constexpr int64_t kRows4Min = 12000, kRows8Min = 128000;
 
 // The nibbles of v from its most significant hex digit on, the first in the low
