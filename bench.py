@@ -167,6 +167,18 @@ def read_counters(n):
     return out
 
 
+def stage_counter_bytes(name, counters):
+    """HBM bytes per step of stage `name`, all instances of its kernels; None
+    unless the counters cover every one of them."""
+    total = 0.0
+    for k in STAGE_KERNELS.get(name, ()):
+        hits = [b * l for c, (b, l) in counters.items() if c.split("<")[0] == k]
+        if not hits:
+            return None
+        total += sum(hits)
+    return total or None
+
+
 def read_traffic(kernel, n):
     """HBM bytes per launch of `kernel` (None if not measured for its current source)."""
     rec = read_counters(n).get(kernel.replace(" ", ""))
@@ -707,9 +719,8 @@ def stage_table(prof, st, n, half, counters):
             gbs = byts / (avg * 1e-3) / 1e9
             d.update(bound="hbm", achieved=gbs, peak=HBM_PEAK_GBS, unit="GB/s", frac=gbs / HBM_PEAK_GBS)
         d["bound_ms"] = max(byts / (HBM_PEAK_GBS * 1e9), flops / (FP32_PEAK_TFLOPS * 1e12)) * 1e3
-        ks = STAGE_KERNELS.get(name)
-        if ks and all(k in counters for k in ks):
-            cb = sum(counters[k][0] * counters[k][1] for k in ks)
+        cb = stage_counter_bytes(name, counters)
+        if cb is not None:
             d["counter_bytes"] = cb
             d["counter_frac"] = cb / (avg * 1e-3) / (HBM_PEAK_GBS * 1e9)
         stages[name] = d
