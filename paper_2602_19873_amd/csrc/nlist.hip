@@ -781,33 +781,32 @@ __global__ __launch_bounds__(kWave * (kDirect ? kDirect : kWavesPerBlock)) __att
             const uint64_t R = sfc_ballot(bit && ((hw >> (8 * (k & 3u))) & 0xFFu) != 0u);
             return lane < kBatch ? (uint32_t)(R >> ((8 * lane) & 63)) & 0xFFu : 0u;
         } else {
-            // candidate by candidate: lane l keeps i-particle l and steps through
-            // the candidate's particles, which its quad (CS = 4) or row (CS = 16)
-            // holds (DPP operands): all i-clusters at once, as a candidate that
-            // leaves one tile open mostly leaves all that are not set. (One tile
-            // at a time waited for its particles: 200,000 particles in 200 clumps
-            // with clusters of 4 at 200 neighbours, half list, 520 -> 208 us, 330
-            // by the tests before the filter; 400,000 uniform particles at 30
-            // neighbours, clusters of 4 / 16: 170 / 174 -> 162 / 180. With
-            // clusters of 8 the rounds above are 3 to 20 % faster.)
-            const uint32_t pi = own_p0 + (uint32_t)lane;
-            const float4 ip = particle(pi, true);
+            // candidate by candidate, whose particles a quad (CS = 4) or a row
+            // (CS = 16) holds and hands round as DPP operands. CS = 4: all
+            // i-clusters at once, lane l with i-particle l, as a candidate that
+            // leaves one tile open mostly leaves all that are not set. CS = 16:
+            // the open tiles one by one, row g from the candidate's particle 4g
+            // on, so that four steps make the 16 x 16 pairs (all four i-clusters
+            // at once: 16 steps). The i-particles come from the lanes that loaded
+            // them, but are read again where registers are short (CS = 4,
+            // periodic boxes), and nothing is loaded ahead: held values spilled.
+            // us, by single tiles with both sides read from memory / now, half lists
+            // at 200 neighbours: 200,000 particles in 200 clumps, clusters of 4 / 16,
+            // 515 / 213 and 209 / 186 (clusters of 4 before the filter: 330);
+            // 2,000,000 uniform, clusters of 4 686 / 684, periodic 920 / 889,
+            // clusters of 16 661 / 648, periodic 858 / 849. With clusters of 8
+            // the rounds above are 3 to 20 % faster.
+            constexpr bool kHeld = CS == 16 && !kPbc;
+            const uint32_t rot = CS == 16 ? 4u * ((uint32_t)lane >> 4) : 0u;
+            float4 ih = {};
+            if (kHeld) ih = particle(own_p0 + (uint32_t)lane, true);
             uint32_t out = 0;
-            uint64_t todo = sfc_ballot(aq != 0u);
-            uint32_t c = sfc_readlane(cj, __builtin_ctzll(todo));
-            float4 jn = particle(c * CS + (uint32_t)(lane & (CS - 1)), false);
-            while (todo) {
+            for (uint64_t todo = sfc_ballot(aq != 0u); todo; todo &= todo - 1ull) {
                 const int q = __builtin_ctzll(todo);
-                const float4 jp = jn;
-                const uint32_t cc = c;
-                todo &= todo - 1ull;
-                if (todo) {  // the next candidate's particles load behind this one's tests
-                    c = sfc_readlane(cj, __builtin_ctzll(todo));
-                    jn = particle(c * CS + (uint32_t)(lane & (CS - 1)), false);
-                }
-                const bool own = cc - own_c0 < (uint32_t)kNsub;
-                uint64_t hits = 0;  // bit l: i-particle l has a pair
-                static_for<CS>([&](auto pc) SFC_INLINE {
+                const uint32_t c = sfc_readlane(cj, q), am = sfc_readlane(aq, q);
+                const float4 jp = particle(c * CS + (((uint32_t)lane + rot) & (uint32_t)(CS - 1)), false);
+                // lane's i-particle against particle p of its quad or row, bit by bit
+                auto near = [&](const float4 &ip, auto pc) SFC_INLINE -> uint64_t {
                     constexpr int p = decltype(pc)::value;
                     float dx = group_bcast<CS, p>(jp.x) - ip.x;
                     float dy = group_bcast<CS, p>(jp.y) - ip.y;
@@ -815,16 +814,50 @@ __global__ __launch_bounds__(kWave * (kDirect ? kDirect : kWavesPerBlock)) __att
                     if (kPbc && wraps) wave_min_image(dx, dy, dz, a.per);
                     const float dxx = dx * dx;
                     const float d2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dxx));
-                    uint64_t near = sfc_ballot(d2 < max_sq(group_bcast<CS, p>(jp.w), ip.w));
-                    // the half list keeps j > i, the full list all but i = j
-                    const uint32_t pj = cc * CS + (uint32_t)p;
-                    if (own) near &= sfc_ballot(half ? pj > pi : pj != pi);
-                    hits |= near;
-                });
-                // lane k: i-cluster k's particles
-                const bool hit = lane < kNsub && ((hits >> ((lane * CS) & 63)) & ((1ull << CS) - 1ull)) != 0ull;
-                const uint32_t got = (uint32_t)sfc_ballot(hit);
-                out = lane == q ? got & aq : out;
+                    return sfc_ballot(d2 < max_sq(group_bcast<CS, p>(jp.w), ip.w));
+                };
+                uint32_t got = 0;
+                if constexpr (CS == 16) {
+                    const uint32_t il = (uint32_t)lane & 15u;
+                    for (uint32_t m = am; m; m &= m - 1u) {
+                        const uint32_t t = (uint32_t)__builtin_ctz(m);
+                        float4 ip;
+                        if (kHeld) {
+                            const int from = (int)((16u * t + il) << 2);
+                            ip.x = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(ih.x)));
+                            ip.y = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(ih.y)));
+                            ip.z = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(ih.z)));
+                            ip.w = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(ih.w)));
+                        } else {
+                            ip = particle(own_p0 + 16u * t + il, true);
+                        }
+                        uint64_t hits = 0;
+                        static_for<4>([&](auto pc) SFC_INLINE {
+                            uint64_t r = near(ip, pc);
+                            // the half list keeps j > i, the full list all but i = j
+                            const uint32_t jl = rot + (uint32_t)decltype(pc)::value;
+                            if (c == own_c0 + t) r &= sfc_ballot(half ? jl > il : jl != il);
+                            hits |= r;
+                        });
+                        if (hits) got |= 1u << t;
+                    }
+                } else {
+                    uint32_t pi = own_p0 + (uint32_t)lane;
+                    asm volatile("" : "+v"(pi));  // (or the load is moved out of the loop)
+                    const float4 ip = particle(pi, true);
+                    const bool own = c - own_c0 < (uint32_t)kNsub;
+                    uint64_t hits = 0;  // bit l: i-particle l has a pair
+                    static_for<CS>([&](auto pc) SFC_INLINE {
+                        uint64_t r = near(ip, pc);
+                        const uint32_t pj = c * CS + (uint32_t)decltype(pc)::value;
+                        if (own) r &= sfc_ballot(half ? pj > pi : pj != pi);
+                        hits |= r;
+                    });
+                    // lane k: i-cluster k's particles
+                    const bool hit = lane < kNsub && ((hits >> ((lane * CS) & 63)) & ((1ull << CS) - 1ull)) != 0ull;
+                    got = (uint32_t)sfc_ballot(hit) & am;
+                }
+                out = lane == q ? got : out;
             }
             return out;
         }
